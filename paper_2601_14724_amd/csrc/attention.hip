@@ -527,8 +527,9 @@ template <int D>
 __global__ __launch_bounds__(256, 3) void attn_colsum(ColsumArgs a, int nkb) {
   const int lin = xcd_remap(blockIdx.x, gridDim.x);
   const int kblk = lin % nkb;
-  const int kv_blk = (lin / nkb) % a.Hkv;
-  const int j = lin / (nkb * a.Hkv);
+  const int split = (lin / nkb) % a.splits;
+  const int kv_blk = (lin / (nkb * a.splits)) % a.Hkv;
+  const int j = lin / (nkb * a.splits * a.Hkv);
   const int layer = a.layer_id[j];
   const LayerTable &lt = a.tab[layer];
   const int cur = a.cur[j];
@@ -553,9 +554,13 @@ __global__ __launch_bounds__(256, 3) void attn_colsum(ColsumArgs a, int nkb) {
   }
   // rows below pmask_end may be invisible to some candidate of this wave
   const int pmask_end = kw0 + 63 < T0 ? 0 : (kw0 + 63 - T0) * G + 1;
-  const int p_begin = (k0 < T0 ? 0 : (k0 - T0) * G) & ~(BQS - 1);
-  const int ntq = (P - p_begin + BQS - 1) / BQS;
-  const int nit = ntq;
+  const int p_first = (k0 < T0 ? 0 : (k0 - T0) * G) & ~(BQS - 1);
+  const int ntq = (P - p_first + BQS - 1) / BQS;
+  // this split's share of the block's query tiles (possibly none: it then
+  // writes zeros)
+  const int t_lo = (int)((int64_t)split * ntq / a.splits);
+  const int nit = (int)((int64_t)(split + 1) * ntq / a.splits) - t_lo;
+  const int p_begin = p_first + t_lo * BQS;
 
   const int slot = a.slot[j];
   const uint16_t *q = a.q + slot * a.q_lstride;
@@ -685,9 +690,11 @@ __global__ __launch_bounds__(256, 3) void attn_colsum(ColsumArgs a, int nkb) {
   using Full = std::integral_constant<bool, true>;
   using Edge = std::integral_constant<bool, false>;
   // tiles [0, nfull) lie wholly below P
-  const int nfull = (P - p_begin) / BQS;
-  load_tile(0, Edge{});
-  store_tile(0);
+  const int nfull = min(nit, (P - p_begin) / BQS);
+  if (nit > 0) {
+    load_tile(0, Edge{});
+    store_tile(0);
+  }
   if (nit > 1) {
     load_tile(1, Edge{});
     store_tile(1);
@@ -722,7 +729,7 @@ __global__ __launch_bounds__(256, 3) void attn_colsum(ColsumArgs a, int nkb) {
     __syncthreads();
   }
   for (; it < nit; ++it) step(it, std::integral_constant<bool, false>{});
-  double *part = a.wpart + layer * a.wpart_lstride + (int64_t)kv_blk * a.wpart_hstride;
+  double *part = a.wpart + layer * a.wpart_lstride + (int64_t)(kv_blk * a.splits + split) * a.wpart_hstride;
 #pragma unroll
   for (int kb = 0; kb < 2; ++kb) {
     const double wsum = wacc[kb] + __shfl_xor(wacc[kb], 32);
@@ -730,34 +737,61 @@ __global__ __launch_bounds__(256, 3) void attn_colsum(ColsumArgs a, int nkb) {
   }
 }
 
-// W_i = sum over KV heads of the per-head partial masses, in head order.
-// W_i = the head-order sum of the per-head fp64 partials, rounded to fp32;
-// with it, per block of kNormBlock candidates, the fp64 partial of the
-// attention-score normaliser sum_i alpha_i W_i over the rounded W (thread
-// order within each wave by a fixed butterfly, then the waves in order).
-__global__ __launch_bounds__(kNormBlock) void mass_reduce(ColsumArgs a) {
+// W_i = the sum of the fp64 partials (KV heads, and within a head its splits
+// of the query rows), rounded to fp32; with it, per block of kNormBlock
+// candidates, the fp64 partial of the attention-score normaliser
+// sum_i alpha_i W_i over the rounded W (thread order within each wave by a
+// fixed butterfly, then the waves in order).  A launch with many partials has
+// few candidates, one workgroup a CU at most, and is bound by the latency of
+// its loads: MG = 4 groups of threads then share a candidate's partials (each
+// a contiguous run, eight loads in flight; the runs are added in order).  One
+// layer of 8976 candidates with 20 partials: 4.7 us, 7.7 with one group and
+// one load at a time; 25 layers with 4 partials: 5.2 us with MG = 1, 9.1 with
+// 4, so up to eight partials stay with one thread.
+template <int MG>
+__global__ __launch_bounds__(kNormBlock *MG) void mass_reduce(ColsumArgs a) {
   const int j = blockIdx.y;
   const int layer = a.layer_id[j];
   const int T = a.ncand[j];
   if ((int)blockIdx.x * kNormBlock >= T) return;   // whole block past this layer's end
-  const int i = blockIdx.x * kNormBlock + threadIdx.x;
-  double m = 0.0;
+  __shared__ double run[MG > 1 ? MG - 1 : 1][kNormBlock];
+  __shared__ double red[kNormBlock / 64];
+  const int lc = threadIdx.x % kNormBlock, grp = threadIdx.x / kNormBlock;
+  const int i = blockIdx.x * kNormBlock + lc;
+  const int n = a.Hkv * a.splits;
+  double w = 0.0;
   if (i < T) {
     const double *part = a.wpart + layer * a.wpart_lstride + i;
-    double w = 0.0;
-    for (int kv = 0; kv < a.Hkv; ++kv) w += part[(int64_t)kv * a.wpart_hstride];
-    const float wf = (float)w;
-    a.tab[layer].w[i] = wf;
-    m = mass_over_observers(wf, i, a.T0[j], a.C, a.alpha_mode[j]);
-  }
+    const int x1 = (grp + 1) * n / MG;
+    for (int x0 = grp * n / MG; x0 < x1; x0 += 8) {
+      double v[8];
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) m += __shfl_xor(m, o);
-  __shared__ double red[kNormBlock / 64];
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
+      for (int u = 0; u < 8; ++u) v[u] = x0 + u < x1 ? part[(int64_t)(x0 + u) * a.wpart_hstride] : 0.0;
+#pragma unroll
+      for (int u = 0; u < 8; ++u) w += v[u];
+    }
+  }
+  if constexpr (MG > 1) {
+    if (grp > 0) run[grp - 1][lc] = w;
+    __syncthreads();
+  }
+  double m = 0.0;
+  if (grp == 0) {
+#pragma unroll
+    for (int x = 0; x < MG - 1; ++x) w += run[x][lc];
+    if (i < T) {
+      const float wf = (float)w;
+      a.tab[layer].w[i] = wf;
+      m = mass_over_observers(wf, i, a.T0[j], a.C, a.alpha_mode[j]);
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) m += __shfl_xor(m, o);
+    if ((lc & 63) == 0) red[lc >> 6] = m;
+  }
   __syncthreads();
   if (threadIdx.x == 0) {
     double s = 0.0;
-    for (int w = 0; w < kNormBlock / 64; ++w) s += red[w];
+    for (int x = 0; x < kNormBlock / 64; ++x) s += red[x];
     a.normpart[layer * a.normpart_lstride + blockIdx.x] = s;
   }
 }
@@ -801,7 +835,7 @@ hipError_t launch_attention_stream(const AttnArgs &a, int n_list, int head_dim, 
 hipError_t launch_colsum(const ColsumArgs &a, int n_list, int max_T, int head_dim,
                          hipStream_t s) {
   const int nkb = (max_T + BK - 1) / BK;
-  dim3 grid(nkb * a.Hkv * n_list);
+  dim3 grid(nkb * a.splits * a.Hkv * n_list);
   if (head_dim == 64) {
     hipLaunchKernelGGL(attn_colsum<64>, grid, dim3(256), 0, s, a, nkb);
   } else {
@@ -809,7 +843,9 @@ hipError_t launch_colsum(const ColsumArgs &a, int n_list, int max_T, int head_di
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(mass_reduce, dim3((max_T + kNormBlock - 1) / kNormBlock, n_list), dim3(kNormBlock), 0, s, a);
+  const dim3 rgrid((max_T + kNormBlock - 1) / kNormBlock, n_list);
+  if (a.Hkv * a.splits > 8) hipLaunchKernelGGL(mass_reduce<4>, rgrid, dim3(kNormBlock * 4), 0, s, a);
+  else hipLaunchKernelGGL(mass_reduce<1>, rgrid, dim3(kNormBlock), 0, s, a);
   return hipGetLastError();
 }
 

@@ -83,8 +83,9 @@ int check_config(const hermes_config *c) {
 
 // Workspace layout of `c`; part_blocks < 0 sizes the stream-mode partial
 // state for the most blocks any short pass can write (one per unit plus one
-// per (layer, KV head) pair), else for that many partial blocks.
-Layout layout_of(const hermes_config *c, int64_t part_blocks = -1) {
+// per (layer, KV head) pair), else for that many partial blocks.  `splits`:
+// with each layer's room for sweeps cut along the query rows.
+Layout layout_of(const hermes_config *c, int64_t part_blocks = -1, bool splits = true) {
   Layout s;
   s.lse_lstride = (int64_t)c->n_q_heads * c->max_chunk;
   s.keys_lstride = c->max_cap;
@@ -107,6 +108,7 @@ Layout layout_of(const hermes_config *c, int64_t part_blocks = -1) {
   s.newc = off;
   off = round_up(off + sizeof(int32_t) * 3 * (size_t)s.newc_lstride * c->n_layers);
   s.wpart_lstride = (int64_t)c->n_kv_heads * c->max_cap;
+  if (splits && s.wpart_lstride < kMassPartials) s.wpart_lstride = kMassPartials;
   s.wpart = off;
   off = round_up(off + sizeof(double) * (size_t)s.wpart_lstride * c->n_layers);
   // summary token: fp64 block sums, staged bf16 rows and their metadata
@@ -136,22 +138,24 @@ Layout layout_of(const hermes_config *c, int64_t part_blocks = -1) {
 }
 
 // The layout of `c` in at most `limit` bytes: the default one if it fits,
-// else the same with as many stream-mode partial blocks as the rest leaves
-// (possibly none: short passes then run the plain kernel).  false if even
-// that exceeds `limit`.
+// else without the room for splits and with as many stream-mode partial
+// blocks as the rest leaves (possibly none: short passes then run the plain
+// kernel).  false if even that exceeds `limit`.
 bool layout_within(const hermes_config *c, size_t limit, Layout *out) {
-  const Layout full = layout_of(c);
-  if (full.total <= limit) {
-    *out = full;
-    return true;
+  for (const bool splits : {true, false}) {
+    const Layout full = layout_of(c, -1, splits);
+    if (full.total <= limit) {
+      *out = full;
+      return true;
+    }
   }
-  const Layout none = layout_of(c, 0);
+  const Layout none = layout_of(c, 0, false);
   if (none.total > limit) return false;
   const size_t per_block = (size_t)none.part_rows * (sizeof(uint16_t) * c->head_dim + 2 * sizeof(float));
   int64_t blocks = (int64_t)((limit - none.total) / per_block);
   // the two regions are rounded up separately: back off until it fits
-  while (blocks > 0 && layout_of(c, blocks).total > limit) --blocks;
-  *out = layout_of(c, blocks);
+  while (blocks > 0 && layout_of(c, blocks, false).total > limit) --blocks;
+  *out = layout_of(c, blocks, false);
   return true;
 }
 
@@ -194,6 +198,33 @@ void stream_plan(AttnArgs &at, int n_rows, int G, int Hkv, int n_list, int D, in
   const double per_unit = (double)((total + units - 1) / units);
   const double stream = per_unit + 2.0 + 2.0 + (double)(units + pairs) * nqt * D / (64.0 * 128.0);
   if (stream < 0.9 * plain) at.st_units = (int32_t)units;
+}
+
+// Query-row splits of a mass sweep of n_list layers of at most max_T
+// candidates, and the row length of its partials.  A workgroup alone on its
+// CU takes about 1.5 times as long for a query tile as each of three that
+// share it (0.73 and 0.475 us at head size 128, 784 x 7 rows): a launch of
+// one layer (144 workgroups at 8976 candidates and 4 KV heads) leaves CUs
+// empty and the others waiting for latency.  So the cost of k workgroups a
+// CU is max(3, 2 k) halves of a tile's shared time; each also pays about six
+// tiles for its K fragments and the first tiles of its ring.
+void mass_splits(ColsumArgs &cs, int n_list, int max_T, int64_t partials) {
+  const int G = cs.Hq / cs.Hkv;
+  const int64_t groups = (int64_t)((max_T + kColsumKeysPerBlock - 1) / kColsumKeysPerBlock) * cs.Hkv * n_list;
+  const int64_t tiles = ((int64_t)cs.C * G + 31) / 32;
+  cs.wpart_hstride = max_T;
+  int64_t most = partials / ((int64_t)cs.Hkv * max_T);
+  most = most < tiles ? most : tiles;
+  double best = 0.0;
+  cs.splits = 1;
+  for (int64_t n = 1; n <= most && n <= kMassSplitMax; ++n) {
+    const double k = (double)((groups * n + 255) / 256);
+    const double cost = ((double)((tiles + n - 1) / n) + 6.0) * (2.0 * k > 3.0 ? 2.0 * k : 3.0);
+    if (n == 1 || cost < best) {
+      best = cost;
+      cs.splits = (int32_t)n;
+    }
+  }
 }
 
 // RoPE frequencies theta_j = base^(-2j/d), j < d/2 (rotate-half pairs), in
@@ -690,7 +721,6 @@ static int append_impl(hermes_ctx *ctx, int32_t layer, const void *q, const void
   cs.lse = at.lse;
   cs.wpart = reinterpret_cast<double *>(ctx->ws + ctx->lay.wpart);
   cs.wpart_lstride = ctx->lay.wpart_lstride;
-  cs.wpart_hstride = ctx->max_cap;
   cs.normpart = reinterpret_cast<double *>(ctx->ws + ctx->lay.normpart);
   cs.normpart_lstride = ctx->lay.normpart_lstride;
   cs.q_lstride = q_ls;
@@ -726,6 +756,7 @@ static int append_impl(hermes_ctx *ctx, int32_t layer, const void *q, const void
   rc = ctx->run(HERMES_K_ATTN, s, [&] { return launch_attention(at, (int)list.size(), ctx->D, s); });
   if (rc != HERMES_OK) return rc;
   if (n_cs > 0) {
+    mass_splits(cs, n_cs, max_T, ctx->lay.wpart_lstride);
     rc = ctx->run(HERMES_K_COLSUM, s, [&] { return launch_colsum(cs, n_cs, max_T, ctx->D, s); });
     if (rc != HERMES_OK) return rc;
   }
@@ -811,7 +842,6 @@ int hermes_guidance_score(hermes_ctx *ctx, int32_t layer, const void *q, const v
   cs.lse = at.lse;
   cs.wpart = reinterpret_cast<double *>(ctx->ws + ctx->lay.wpart);
   cs.wpart_lstride = ctx->lay.wpart_lstride;
-  cs.wpart_hstride = ctx->max_cap;
   cs.normpart = reinterpret_cast<double *>(ctx->ws + ctx->lay.normpart);
   cs.normpart_lstride = ctx->lay.normpart_lstride;
   cs.q_lstride = q_ls;
@@ -834,6 +864,7 @@ int hermes_guidance_score(hermes_ctx *ctx, int32_t layer, const void *q, const v
     max_T = ctx->len[l] > max_T ? ctx->len[l] : max_T;
   }
   const int n = (int)list.size();
+  mass_splits(cs, n, max_T, ctx->lay.wpart_lstride);
   stream_plan(at, n_rows, ctx->Hq / ctx->Hkv, ctx->Hkv, n, ctx->D, ctx->lay.part_blocks);
   at.part_rows = ctx->lay.part_rows;
   at.opart = reinterpret_cast<uint16_t *>(ctx->ws + ctx->lay.opart);

@@ -70,9 +70,10 @@ struct AttnArgs {
 
 // Attention-mass sweep: W_i for the candidates i < ncand[j] of layer
 // layer_id[j] (ncand = T0 + C for the chunk's own mass, T0 for a guidance
-// prompt, whose rows are not candidates).  Each KV head's share goes to
-// wpart[layer][kv][i] (fp64), then is summed into the layer's w buffer in
-// head order.
+// prompt, whose rows are not candidates).  Each KV head's share, cut into
+// `splits` ranges of its query rows, goes to wpart[layer][kv * splits +
+// split][i] (fp64, rows of wpart_hstride), then is summed into the layer's w
+// buffer in that order.
 struct ColsumArgs {
   const LayerTable *tab;
   const uint16_t *q, *kn, *vn;
@@ -81,6 +82,7 @@ struct ColsumArgs {
   double *normpart;         // [n_layers][normpart_lstride] fp64 partials of sum_i alpha_i W_i
   int64_t q_lstride, kv_lstride, lse_lstride, wpart_lstride, wpart_hstride, normpart_lstride;
   int32_t Hq, Hkv, C;
+  int32_t splits;           // workgroups that share a block's query rows (1: none)
   float scale_log2;
   int32_t T0[kMaxLayers];
   int32_t ncand[kMaxLayers];
@@ -258,6 +260,8 @@ hipError_t launch_mrope_rank(const RankArgs &a, hipStream_t s);
 // Geometry shared by host sizing and kernels.
 constexpr int kAttnRowsPerBlock = 256;   // packed (row, head) pairs per attention workgroup
 constexpr int kColsumKeysPerBlock = 256; // candidates per workgroup of the sweep
+constexpr int kMassSplitMax = 32;       // ranges a sweep's query rows are cut into at most
+constexpr int64_t kMassPartials = 1024 * 256;   // fp64 partials a layer keeps for them
 constexpr int kSummaryRows = 128;        // candidates per workgroup of the summary sums
 constexpr int kSplitMaxTokens = 64;      // passes of at most this many rows use stream mode
 constexpr int kStreamSlots = 256;        // resident attention workgroups (one per CU)
