@@ -27,8 +27,7 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef short s4 __attribute__((ext_vector_type(4)));
 
 constexpr int AT = 512;                  // attention workgroup: 8 waves, two per SIMD
-constexpr int BM = kAttnRowsPerBlock;    // packed rows per workgroup (8 waves x 32)
-constexpr int BN = 64;                   // keys per tile
+constexpr int BM = kAttnRowsPerBlock;    // packed rows per workgroup with one key group (8 waves x 32)
 constexpr int BK = kColsumKeysPerBlock;  // candidates per sweep workgroup (4 waves x 64)
 constexpr int BQS = 32;                  // packed rows per sweep tile
 constexpr int KPAD = 8;                  // u16 padding of K / Q rows in LDS
@@ -74,20 +73,35 @@ __device__ __forceinline__ int xcd_remap(int i, int n) {
   return x < r ? x * (q + 1) + k : r * (q + 1) + (x - r) * q + k;
 }
 
-// STREAM: balanced short passes (query, guidance prompt).  The key tiles of
+// STREAM: passes whose (entry, KV head, query tile) workgroups would not fill
+// the CUs (one layer's chunk, queries, guidance prompts).  The key tiles of
 // every (entry, KV head) pair, concatenated in pair order (pair k = j Hkv +
 // kv, st_tiles[j] tiles each, entry j's pairs from tile st_off[j]), are cut
 // into st_units equal ranges; unit u is nqt workgroups with consecutive ids
 // (one per query tile, sharing the K/V tiles in their XCD's L2) over tiles
 // [u N / U, (u + 1) N / U).  The workgroup walks its range in one tile loop;
 // where the range leaves a pair it writes the pair's unnormalised partial
-// state (bf16 O, fp32 running maximum and row sum) to partial block (u + k)
+// state (fp32 O, running maximum and row sum) to partial block (u + k)
 // of its query tile (distinct for every (u, k): a later unit only covers
 // later pairs) and switches to the next pair.  attn_combine merges a pair's
 // blocks.  Otherwise: one workgroup per (entry, KV head, query tile) over its
 // whole sequence, writing O (WRITE_O) and the row LSE.
-template <int D, bool STREAM, bool WRITE_O>
+//
+// KG key groups: the workgroup's 8 waves are KG groups of RG = 8 / KG waves; a
+// group holds all of the workgroup's 32 RG packed rows and takes every KG-th
+// key tile, and the groups' states are merged through LDS at the end.  Rows a
+// workgroup shrink by KG, so a launch has KG times the workgroups and each
+// walks a KG-th of the keys: what a launch of few rows needs to fill the CUs,
+// for KG times the K/V staging per row.
+template <int D, int KG, bool STREAM, bool WRITE_O>
 __global__ __launch_bounds__(AT, 1) void attn_fwd(AttnArgs a, int nqt) {
+  static_assert(!STREAM || KG == 1, "stream mode walks one key group");
+  constexpr int RG = 8 / KG;                // 32-row groups (waves of a key group)
+  constexpr int BM = 32 * RG;               // packed rows of the workgroup
+  constexpr int BN = KG <= 2 ? 64 : 32;     // keys per tile
+  constexpr int SUB = BN / 32;
+  constexpr int NBUF = KG == 8 ? 1 : 2;     // (a tile of one wave needs no second buffer)
+  constexpr int GT = 64 * RG;               // threads of a key group
   const int lin = xcd_remap(blockIdx.x, gridDim.x);
   const int qtile = lin % nqt;
   const int C = a.C, Hq = a.Hq, Hkv = a.Hkv;
@@ -96,7 +110,8 @@ __global__ __launch_bounds__(AT, 1) void attn_fwd(AttnArgs a, int nqt) {
   const int p0 = qtile * BM;
   if (p0 >= P) return;
 
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int tid = threadIdx.x % GT, wave = tid >> 6, lane = tid & 63;
+  const int kg = KG == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / GT);
   const int half = lane >> 5, l32 = lane & 31;
 
   // This lane's query row (column n of the S^T tile).
@@ -110,21 +125,26 @@ __global__ __launch_bounds__(AT, 1) void attn_fwd(AttnArgs a, int nqt) {
   const int g = row_ok ? prow - r * G : 0;
   const int pmax = min(p0 + BM, P) - 1;
 
-  // Pair state: entry j, KV head kv, its cache and new rows.
-  int j = 0, kv = 0, T0 = 0, T = 0, vis = -1, vis_min = 0, ntiles = 0, n_pure = 0, first = 0;
+  // Pair state: entry j, KV head kv, its cache and new rows.  The key tiles
+  // are the cache's n_cache (the last one partly filled when T0 is no multiple
+  // of BN), then the new rows': a tile's rows have one uniform base.
+  int j = 0, kv = 0, T0 = 0, ntiles = 0, n_cache = 0, n_pure = 0, first = 0;
   const uint16_t *q = nullptr, *kn = nullptr, *vn = nullptr, *kc = nullptr, *vc = nullptr;
   const int64_t row_stride = (int64_t)Hkv * D;
   constexpr int CH = D / 8;                 // 16-byte chunks per key row and head
-  constexpr int NLD = BN * CH / AT;         // chunks per thread per tensor
-  uint32_t cofs[NLD];
+  constexpr int NLD = BN * CH / GT;         // chunks per thread per tensor
+  static_assert(GT % CH == 0, "a thread's chunks lie in one column");
+  uint32_t cofs = 0;
+  const int cstep = (int)(GT / CH * row_stride * sizeof(uint16_t));
   bf16x8 qf[D / 16];
   // STREAM: this unit's tile range over the concatenated pairs
   int x_lo = 0, x_hi = 0, u = 0;
   if constexpr (STREAM) {
     u = lin / nqt;
-    x_lo = (int)((int64_t)u * a.st_total / a.st_units);
-    x_hi = (int)((int64_t)(u + 1) * a.st_total / a.st_units);
-    if (x_lo >= x_hi) return;
+    // (the 64-bit divisions run on vector registers: back to scalar ones, so
+    // that tile indices, loop bounds and buffer descriptors stay scalar)
+    x_lo = __builtin_amdgcn_readfirstlane((int)((int64_t)u * a.st_total / a.st_units));
+    x_hi = __builtin_amdgcn_readfirstlane((int)((int64_t)(u + 1) * a.st_total / a.st_units));
   }
   auto enter = [&](int jj, int kvv) {
     j = jj;
@@ -132,14 +152,9 @@ __global__ __launch_bounds__(AT, 1) void attn_fwd(AttnArgs a, int nqt) {
     const LayerTable &lt = a.tab[a.layer_id[j]];
     const int cur = a.cur[j];
     T0 = a.T0[j];
-    T = T0 + C;
-    vis = row_ok ? T0 + r : -1;             // last candidate this row sees
-    vis_min = T0 + p0 / G;                  // every row of the block sees keys <= vis_min
-    const int nkeys = T0 + pmax / G + 1;
-    ntiles = (nkeys + BN - 1) / BN;
-    // tiles [0, n_pure) lie wholly in the cache and below every row's causal
-    // limit: they load with plain pointer strides and need no mask
-    n_pure = min(ntiles, T0 / BN);
+    n_pure = T0 / BN;                       // tiles that need no mask
+    n_cache = (T0 + BN - 1) / BN;
+    ntiles = n_cache + (pmax / G) / BN + 1; // the last one a row of the block sees
     const int slot = a.slot[j];
     q = a.q + slot * a.q_lstride;
     kn = a.kn + slot * a.kv_lstride;
@@ -152,20 +167,16 @@ __global__ __launch_bounds__(AT, 1) void attn_fwd(AttnArgs a, int nqt) {
       qf[kk] = row_ok ? *reinterpret_cast<const bf16x8 *>(q + ((int64_t)r * Hq + h) * D + 16 * kk + 8 * half)
                       : bf16x8{};
     }
-    // byte offset of this thread's chunk u inside a key tile of the cache; a
-    // pure tile's loads are then a uniform base plus this 32-bit offset
-#pragma unroll
-    for (int uu = 0; uu < NLD; ++uu) {
-      const int e = tid + uu * AT;
-      cofs[uu] = (uint32_t)(((e / CH) * row_stride + kv * D + (e % CH) * 8) * sizeof(uint16_t));
-    }
+    // byte offset of this thread's first chunk inside a key tile; the others
+    // follow GT / CH rows apart
+    cofs = (uint32_t)(((tid / CH) * row_stride + kv * D + (tid % CH) * 8) * sizeof(uint16_t));
   };
   // the pair holding concatenated tile x (STREAM), its first tile in `first`
   auto locate = [&](int x, int &jj, int &kvv, int &f) {
     int e = 0;
     while (e + 1 < a.st_entries && x >= a.st_off[e + 1]) ++e;
     jj = e;
-    kvv = (x - a.st_off[e]) / a.st_tiles[e];
+    kvv = __builtin_amdgcn_readfirstlane((x - a.st_off[e]) / a.st_tiles[e]);
     f = a.st_off[e] + kvv * a.st_tiles[e];
   };
   if constexpr (STREAM) {
@@ -180,48 +191,56 @@ __global__ __launch_bounds__(AT, 1) void attn_fwd(AttnArgs a, int nqt) {
   // transposed by ds_read_b64_tr_b16.  Row pads keep the K reads (16 B per
   // lane) and the transposed V reads (4 rows x 32 B per 16 lanes) spread
   // over the LDS banks.
-  __shared__ __attribute__((aligned(16))) uint16_t Ks[2][BN][D + KPAD];
-  __shared__ __attribute__((aligned(16))) uint16_t Vs[2][BN][D + VPAD];
+  __shared__ __attribute__((aligned(16))) uint16_t tiles[KG * NBUF * BN * (2 * D + KPAD + VPAD)];
+  uint16_t(*Ks)[BN][D + KPAD] = reinterpret_cast<uint16_t(*)[BN][D + KPAD]>(tiles) + kg * NBUF;
+  uint16_t(*Vs)[BN][D + VPAD] =
+      reinterpret_cast<uint16_t(*)[BN][D + VPAD]>(tiles + KG * NBUF * BN * (D + KPAD)) + kg * NBUF;
   uint4 kreg[NLD], vreg[NLD];
-  // pure tiles load through buffer descriptors whose base is the tile's first
-  // row (scalar arithmetic): each load is the descriptor plus the lane's
-  // 32-bit offset, with no per-lane 64-bit address addition
-  auto load_pure = [&](int k0) {
-    const __amdgpu_buffer_rsrc_t kr = __builtin_amdgcn_make_buffer_rsrc(
-        (void *)(kc + (int64_t)k0 * row_stride), 0, 0x7FFFFFFF, kBufferWord3);
-    const __amdgpu_buffer_rsrc_t vr = __builtin_amdgcn_make_buffer_rsrc(
-        (void *)(vc + (int64_t)k0 * row_stride), 0, 0x7FFFFFFF, kBufferWord3);
+  // Tiles load through buffer descriptors whose base is the tile's first row
+  // (scalar arithmetic): each load is the descriptor plus the lane's 32-bit
+  // offset, with no per-lane 64-bit address addition.
+  auto load_pure = [&](int t) {
+    const int64_t at = (int64_t)t * BN * row_stride;
+    const __amdgpu_buffer_rsrc_t kr =
+        __builtin_amdgcn_make_buffer_rsrc((void *)(kc + at), 0, 0x7FFFFFFF, kBufferWord3);
+    const __amdgpu_buffer_rsrc_t vr =
+        __builtin_amdgcn_make_buffer_rsrc((void *)(vc + at), 0, 0x7FFFFFFF, kBufferWord3);
 #pragma unroll
     for (int uu = 0; uu < NLD; ++uu) {
-      const auto kx = __builtin_amdgcn_raw_buffer_load_b128(kr, (int)cofs[uu], 0, 0);
-      const auto vx = __builtin_amdgcn_raw_buffer_load_b128(vr, (int)cofs[uu], 0, 0);
+      const auto kx = __builtin_amdgcn_raw_buffer_load_b128(kr, (int)cofs, uu * cstep, 0);
+      const auto vx = __builtin_amdgcn_raw_buffer_load_b128(vr, (int)cofs, uu * cstep, 0);
       kreg[uu] = uint4{kx[0], kx[1], kx[2], kx[3]};
       vreg[uu] = uint4{vx[0], vx[1], vx[2], vx[3]};
     }
   };
-  // a tile of any pair (its cache, new rows, lengths and KV head given)
-  auto load_from = [&](int k0, const uint16_t *kcx, const uint16_t *vcx, const uint16_t *knx,
-                       const uint16_t *vnx, int T0x, int Tx, int kvx) {
+  // Any tile: the descriptor ends with the tile's last row, so that rows past
+  // it (and a whole tile past the last one) load as zeros.
+  auto load_any = [&](int t) {
+    const bool fresh = t >= n_cache;
+    const int row0 = (fresh ? t - n_cache : t) * BN;
+    const int rows = max(0, min(BN, (fresh ? C : T0) - row0));
+    const int64_t at = rows > 0 ? row0 * row_stride : 0;
+    const int bytes = rows * (int)(row_stride * sizeof(uint16_t));
+    const __amdgpu_buffer_rsrc_t kr =
+        __builtin_amdgcn_make_buffer_rsrc((void *)((fresh ? kn : kc) + at), 0, bytes, kBufferWord3);
+    const __amdgpu_buffer_rsrc_t vr =
+        __builtin_amdgcn_make_buffer_rsrc((void *)((fresh ? vn : vc) + at), 0, bytes, kBufferWord3);
 #pragma unroll
     for (int uu = 0; uu < NLD; ++uu) {
-      const int e = tid + uu * AT;
-      const int kr = e / CH, ch = e % CH;
-      const int i = k0 + kr;
-      uint4 k4 = {0u, 0u, 0u, 0u}, v4 = {0u, 0u, 0u, 0u};
-      if (i < Tx) {
-        const int64_t off = (i < T0x ? (int64_t)i : (int64_t)(i - T0x)) * row_stride + kvx * D + ch * 8;
-        k4 = gload16((i < T0x ? kcx : knx) + off);
-        v4 = gload16((i < T0x ? vcx : vnx) + off);
-      }
-      kreg[uu] = k4;
-      vreg[uu] = v4;
+      const auto kx = __builtin_amdgcn_raw_buffer_load_b128(kr, (int)cofs + uu * cstep, 0, 0);
+      const auto vx = __builtin_amdgcn_raw_buffer_load_b128(vr, (int)cofs + uu * cstep, 0, 0);
+      kreg[uu] = uint4{kx[0], kx[1], kx[2], kx[3]};
+      vreg[uu] = uint4{vx[0], vx[1], vx[2], vx[3]};
     }
   };
-  auto load_any = [&](int k0) { load_from(k0, kc, vc, kn, vn, T0, T, kv); };
+  // tile t holds a key that some row of the block does not see
+  auto edge = [&](int t) {
+    return t < n_cache ? (t + 1) * BN > T0 : (t - n_cache + 1) * BN - 1 > p0 / G;
+  };
   auto store_tile = [&](int b) {
 #pragma unroll
     for (int uu = 0; uu < NLD; ++uu) {
-      const int e = tid + uu * AT;
+      const int e = tid + uu * GT;
       const int kr = e / CH, ch = e % CH;
       *reinterpret_cast<uint4 *>(&Ks[b][kr][ch * 8]) = kreg[uu];
       *reinterpret_cast<uint4 *>(&Vs[b][kr][ch * 8]) = vreg[uu];
@@ -236,21 +255,17 @@ __global__ __launch_bounds__(AT, 1) void attn_fwd(AttnArgs a, int nqt) {
   float m_lim = (m_run + 8.f) * inv_c;
 
   // transposed-read coordinates of this lane inside its 16-lane group
-  const int g16 = lane >> 4, s16 = lane & 15;
-  const int tr_row = 4 * (g16 >> 1) + (s16 >> 2);
-  const int tr_col = 16 * (g16 & 1) + 4 * (s16 & 3);
+  const int tr_row = 4 * half + ((lane & 15) >> 2);
+  const int tr_col = 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
 
-  // key tile t (keys from k0 = t * BN) of the current pair, in LDS buffer b.
-  // `masked` is a std::integral_constant in the plain kernel's loops (the
-  // mask code folds away per call site) and a uniform bool in stream mode,
-  // whose single instance of this body fits the register budget (two
-  // instances in one loop spill).
+  // key tile t of the current pair, in LDS buffer b.
+  // `masked` is a std::integral_constant: the mask code folds away per call
+  // site.
   auto compute = [&](int b, int t, auto masked) {
-    const int k0 = t * BN;
-    // S^T = K Q^T for two 32-key sub-tiles: lane = query row, register = key.
-    f32x16 s[2];
+    // S^T = K Q^T for SUB 32-key sub-tiles: lane = query row, register = key.
+    f32x16 s[SUB];
 #pragma unroll
-    for (int sub = 0; sub < 2; ++sub) {
+    for (int sub = 0; sub < SUB; ++sub) {
       s[sub] = f32x16{};
 #pragma unroll
       for (int kk = 0; kk < D / 16; ++kk) {
@@ -264,25 +279,27 @@ __global__ __launch_bounds__(AT, 1) void attn_fwd(AttnArgs a, int nqt) {
 #pragma unroll
     for (int i = 0; i < kAheadK; ++i) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
 #pragma unroll
-    for (int i = 0; i < 2 * (D / 16) - kAheadK; ++i) {
+    for (int i = 0; i < SUB * (D / 16) - kAheadK; ++i) {
       __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
       __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
     }
 #pragma unroll
     for (int i = 0; i < kAheadK; ++i) __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
     if (masked) {
+      // last key of the tile that this row sees
+      const int vis = t < n_cache ? T0 - 1 - t * BN : r - (t - n_cache) * BN;
 #pragma unroll
-      for (int sub = 0; sub < 2; ++sub) {
+      for (int sub = 0; sub < SUB; ++sub) {
 #pragma unroll
         for (int jj = 0; jj < 16; ++jj) {
-          const int key = k0 + sub * 32 + 8 * (jj >> 2) + 4 * half + (jj & 3);
+          const int key = sub * 32 + 8 * (jj >> 2) + 4 * half + (jj & 3);
           if (key > vis) s[sub][jj] = -INFINITY;
         }
       }
     }
     float mx = -INFINITY;
 #pragma unroll
-    for (int sub = 0; sub < 2; ++sub) {
+    for (int sub = 0; sub < SUB; ++sub) {
 #pragma unroll
       for (int jj = 0; jj < 16; ++jj) mx = fmaxf(mx, s[sub][jj]);
     }
@@ -308,10 +325,10 @@ __global__ __launch_bounds__(AT, 1) void attn_fwd(AttnArgs a, int nqt) {
       for (int db = 0; db < D / 32; ++db) o[db] *= alpha;
     }
 
-    bf16x8 pf[4];
+    bf16x8 pf[2 * SUB];
     float ls = 0.f;
 #pragma unroll
-    for (int sub = 0; sub < 2; ++sub) {
+    for (int sub = 0; sub < SUB; ++sub) {
 #pragma unroll
       for (int jj = 0; jj < 16; ++jj) {
         const float p = fast_exp2(fmaf(s[sub][jj], c, -m_run));
@@ -331,7 +348,7 @@ __global__ __launch_bounds__(AT, 1) void attn_fwd(AttnArgs a, int nqt) {
 #pragma unroll
     for (int db = 0; db < D / 32; ++db) {
 #pragma unroll
-      for (int qq = 0; qq < 4; ++qq) {
+      for (int qq = 0; qq < 2 * SUB; ++qq) {
         const uint16_t *vp = &Vs[b][16 * qq + tr_row][32 * db + tr_col];
         const s4 lo = lds_tr16(vp);
         const s4 hi = lds_tr16(vp + 8 * (D + VPAD));
@@ -341,7 +358,7 @@ __global__ __launch_bounds__(AT, 1) void attn_fwd(AttnArgs a, int nqt) {
     }
     // the same for O^T += V^T P^T: two transposed reads per MFMA, kAheadV
     // MFMAs ahead
-    constexpr int kPV = (D / 32) * 4;
+    constexpr int kPV = (D / 32) * 2 * SUB;
 #pragma unroll
     for (int i = 0; i < 2 * kAheadV; ++i) __builtin_amdgcn_sched_group_barrier(0x100, 1, 1);
 #pragma unroll
@@ -356,43 +373,42 @@ __global__ __launch_bounds__(AT, 1) void attn_fwd(AttnArgs a, int nqt) {
 
   using NoMask = std::integral_constant<bool, false>;
   using Mask = std::integral_constant<bool, true>;
-  // unnormalised partial state of the current pair into partial block blk:
-  // bf16 O (half the bytes the combine reads back), fp32 running maximum and
-  // row sum (they fix the LSE)
+  // unnormalised partial state of the current pair into partial block blk.
+  // Each 32-row group is stored as the wave holds it ([4-channel group][lane]),
+  // so that both the stores and the combine's loads are contiguous.
   auto flush = [&](int64_t blk) {
     const float l_tot = l_run + __shfl_xor(l_run, 32);
-    if (row_ok) {
-      const int64_t row = blk * a.part_rows + prow;
-      uint16_t *op = a.opart + row * D;
+    if (wave_rows) {
+      const int64_t rg = blk * a.part_groups + (p0 >> 5) + wave;
+      float4 *op = reinterpret_cast<float4 *>(a.opart) + rg * (D / 8) * 64 + lane;
 #pragma unroll
       for (int db = 0; db < D / 32; ++db)
 #pragma unroll
-        for (int grp = 0; grp < 4; ++grp) {
-          const int d0 = 32 * db + 8 * grp + 4 * half;
-          const uint32_t w0 = (uint32_t)f2bf(o[db][4 * grp + 0]) | ((uint32_t)f2bf(o[db][4 * grp + 1]) << 16);
-          const uint32_t w1 = (uint32_t)f2bf(o[db][4 * grp + 2]) | ((uint32_t)f2bf(o[db][4 * grp + 3]) << 16);
-          *reinterpret_cast<uint2 *>(op + d0) = uint2{w0, w1};
-        }
-      if (half == 0) *reinterpret_cast<float2 *>(a.mlpart + 2 * row) = float2{m_run, l_tot};
+        for (int grp = 0; grp < 4; ++grp)
+          op[(4 * db + grp) * 64] = float4{o[db][4 * grp + 0], o[db][4 * grp + 1], o[db][4 * grp + 2],
+                                           o[db][4 * grp + 3]};
+      if (half == 0) *reinterpret_cast<float2 *>(a.mlpart + 2 * (rg * 32 + l32)) = float2{m_run, l_tot};
     }
   };
   if constexpr (STREAM) {
     // One tile loop over the range; leaving a pair (rare) flushes it, moves
     // to the next pair and loads that pair's first tile without prefetch.
+    // (One instance of the tile body: with a loop over pairs around the loops
+    // below, it spills.)
     int t = x_lo - first;
     int pair_n = a.st_tiles[j];
     int k = j * Hkv + kv;
-    if (t < n_pure) load_pure(t * BN); else load_any(t * BN);
+    if (t < n_pure) load_pure(t); else load_any(t);
     int b = 0;
     for (int x = x_lo; x < x_hi; ++x) {
       store_tile(b);
       __syncthreads();
       const bool pair_end = t + 1 == pair_n;
       if (!pair_end && x + 1 < x_hi) {
-        if (t + 1 < n_pure) load_pure((t + 1) * BN); else load_any((t + 1) * BN);
+        if (t + 1 < n_pure) load_pure(t + 1); else load_any(t + 1);
       }
       // tiles past this query tile's own causal limit hold no visible key
-      if (wave_rows && t < ntiles) compute(b, t, (t + 1) * BN - 1 > vis_min);
+      if (wave_rows && t < ntiles) compute(b, t, edge(t));
       if (pair_end && x + 1 < x_hi) {
         flush(u + k);
         if (kv + 1 < Hkv) enter(j, kv + 1); else enter(j + 1, 0);
@@ -412,42 +428,53 @@ __global__ __launch_bounds__(AT, 1) void attn_fwd(AttnArgs a, int nqt) {
     }
     flush(u + k);
     return;
-  } else {
-    // Steady state: the tile and the next one are pure (no branch in the
-    // body); the last pure tile joins the general loop, where it is unmasked.
-    if (n_pure > 0) load_pure(0); else load_any(0);
-    int t = 0;
-    // two tiles per trip, so that the LDS buffer of each is a constant and
-    // its addresses fold into the instructions' offsets
-    for (; t + 2 < n_pure; t += 2) {
-      store_tile(0);
-      __syncthreads();
-      load_pure((t + 1) * BN);
-      if (wave_rows) compute(0, t, NoMask{});
-      store_tile(1);
-      __syncthreads();
-      load_pure((t + 2) * BN);
-      if (wave_rows) compute(1, t + 1, NoMask{});
+  }
+  // Step s covers tiles s KG .. s KG + KG - 1, one for each key group.  Steady
+  // state: this step's tiles and the next one's are pure (no branch in the
+  // body); the last pure step joins the general loop, where it is unmasked.
+  const int steps = (ntiles + KG - 1) / KG, pure_steps = n_pure / KG;
+  auto tile = [&](int s) { return s * KG + kg; };
+  // the group's waves wait for their tile's stores (all groups take the same
+  // steps; a group of one wave only keeps its own order)
+  auto sync = [&] {
+    if constexpr (RG > 1) __syncthreads();
+    else __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  };
+  if (pure_steps > 0) load_pure(tile(0)); else load_any(tile(0));
+  int s = 0;
+  // two steps per trip, so that the LDS buffer of each is a constant and its
+  // addresses fold into the instructions' offsets
+  for (; s + 2 < pure_steps; s += 2) {
+    store_tile(0);
+    sync();
+    load_pure(tile(s + 1));
+    if (wave_rows) compute(0, tile(s), NoMask{});
+    store_tile(NBUF - 1);
+    sync();
+    load_pure(tile(s + 2));
+    if (wave_rows) compute(NBUF - 1, tile(s + 1), NoMask{});
+  }
+  for (; s + 1 < pure_steps; ++s) {
+    store_tile(s % NBUF);
+    sync();
+    load_pure(tile(s + 1));
+    if (wave_rows) compute(s % NBUF, tile(s), NoMask{});
+  }
+  for (; s < steps; ++s) {
+    store_tile(s % NBUF);
+    sync();
+    if (s + 1 < steps) load_any(tile(s + 1));   // (zeros past the last key)
+    const int t = tile(s);
+    if (!wave_rows || (KG > 1 && t >= ntiles)) {
+    } else if (edge(t)) {
+      compute(s % NBUF, t, Mask{});
+    } else {
+      compute(s % NBUF, t, NoMask{});
     }
-    for (; t + 1 < n_pure; ++t) {
-      store_tile(t & 1);
-      __syncthreads();
-      load_pure((t + 1) * BN);
-      if (wave_rows) compute(t & 1, t, NoMask{});
-    }
-    for (; t < ntiles; ++t) {
-      store_tile(t & 1);
-      __syncthreads();
-      if (t + 1 < ntiles) load_any((t + 1) * BN);
-      if (!wave_rows) {
-      } else if ((t + 1) * BN - 1 > vis_min) {
-        compute(t & 1, t, Mask{});
-      } else {
-        compute(t & 1, t, NoMask{});
-      }
-    }
+  }
 
-    const float l_tot = l_run + __shfl_xor(l_run, 32);
+  const float l_tot = l_run + __shfl_xor(l_run, 32);
+  if constexpr (KG == 1) {
     const float inv = 1.f / l_tot;
     if (row_ok) {
       if constexpr (WRITE_O) {
@@ -469,23 +496,80 @@ __global__ __launch_bounds__(AT, 1) void attn_fwd(AttnArgs a, int nqt) {
         a.lse[a.layer_id[j] * a.lse_lstride + (int64_t)kv * P + prow] = m_run + log2f(l_tot);
       }
     }
+  } else {
+    // Merge of the key groups: every wave leaves its (max, sum) and O in LDS
+    // ([4-channel group][lane], as it holds them), then wave kg of a row group
+    // merges and writes the KG-th part of the channels, groups in order.
+    constexpr int NC = D / 8;                 // 4-channel groups of a lane half
+    static_assert(NC % KG == 0 && (8 * NC * 64 * 16 + 8 * 32 * 8) <= (int)sizeof(tiles), "merge state fits");
+    float4 *mo = reinterpret_cast<float4 *>(tiles);
+    float2 *mm = reinterpret_cast<float2 *>(mo + 8 * NC * 64);
+    __syncthreads();   // all tiles are read
+    if constexpr (WRITE_O) {
+#pragma unroll
+      for (int c = 0; c < NC; ++c)
+        mo[((kg * RG + wave) * NC + c) * 64 + lane] = float4{o[c / 4][4 * (c % 4) + 0], o[c / 4][4 * (c % 4) + 1],
+                                                             o[c / 4][4 * (c % 4) + 2], o[c / 4][4 * (c % 4) + 3]};
+    }
+    if (half == 0) mm[(kg * RG + wave) * 32 + l32] = float2{m_run, l_tot};
+    __syncthreads();
+    float mt = -1e30f, wt[KG], lsum = 0.f;
+#pragma unroll
+    for (int x = 0; x < KG; ++x) {
+      const float2 v = mm[(x * RG + wave) * 32 + l32];
+      wt[x] = v.x;
+      mt = fmaxf(mt, v.x);
+    }
+#pragma unroll
+    for (int x = 0; x < KG; ++x) {
+      wt[x] = fast_exp2(wt[x] - mt);
+      lsum += wt[x] * mm[(x * RG + wave) * 32 + l32].y;
+    }
+    if (row_ok) {
+      if constexpr (WRITE_O) {
+        const float inv = 1.f / lsum;
+        uint16_t *orow = a.out + a.slot[j] * a.q_lstride + ((int64_t)r * Hq + kv * G + g) * D + 4 * half;
+#pragma unroll
+        for (int i = 0; i < NC / KG; ++i) {
+          const int c = kg * (NC / KG) + i;
+          float4 t = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+          for (int x = 0; x < KG; ++x) {
+            const float4 y = mo[((x * RG + wave) * NC + c) * 64 + lane];
+            t.x += wt[x] * y.x;
+            t.y += wt[x] * y.y;
+            t.z += wt[x] * y.z;
+            t.w += wt[x] * y.w;
+          }
+          *reinterpret_cast<uint2 *>(orow + 8 * c) =
+              uint2{(uint32_t)f2bf(t.x * inv) | ((uint32_t)f2bf(t.y * inv) << 16),
+                    (uint32_t)f2bf(t.z * inv) | ((uint32_t)f2bf(t.w * inv) << 16)};
+        }
+      }
+      if (a.lse != nullptr && kg == 0 && half == 0)
+        a.lse[a.layer_id[j] * a.lse_lstride + (int64_t)kv * P + prow] = mt + log2f(lsum);
+    }
   }
 }
-
 
 // Merge of a pair's partial blocks: m = max_s m_s, w_s = 2^(m_s - m),
 // O = sum_s w_s O_s / sum_s w_s l_s, LSE = m + log2(sum_s w_s l_s).  Pair
 // k = j Hkv + kv covers concatenated tiles [f, f + n); units u0 (holding
 // tile f) to u1 (holding tile f + n - 1) wrote its blocks u0 + k .. u1 + k.
-// One thread per (packed row, 8 channels), blocks summed in order.
+// A workgroup merges 32 channels of a 32-row group: wave w takes the blocks
+// w, w + 4, ... in order, kCombineAhead of them loaded at once, and the four
+// waves' sums are added in wave order.  The launch is bound by the latency of
+// its loads: with one thread walking all blocks one by one, a pair's 64
+// blocks took 20-31 us.
+constexpr int kCombineAhead = 4;
 template <int D>
 __global__ __launch_bounds__(256) void attn_combine(AttnArgs a) {
   const int j = blockIdx.z, kv = blockIdx.y;
   const int layer = a.layer_id[j];
   const int G = a.Hq / a.Hkv, P = a.C * G;
-  const int e = blockIdx.x * 256 + threadIdx.x;
-  if (e >= P * (D / 8)) return;
-  const int p = e / (D / 8), c8 = e % (D / 8);
+  const int rgi = blockIdx.x / (D / 32), db = blockIdx.x % (D / 32);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int l32 = lane & 31, half = lane >> 5;
   // the unit whose range [u N / U, (u + 1) N / U) holds tile x
   auto unit_of = [&](int64_t x) {
     return (int)(((x + 1) * a.st_units + a.st_total - 1) / a.st_total - 1);
@@ -493,34 +577,86 @@ __global__ __launch_bounds__(256) void attn_combine(AttnArgs a) {
   const int64_t f = a.st_off[j] + (int64_t)kv * a.st_tiles[j];
   const int u0 = unit_of(f);
   const int nsp = unit_of(f + a.st_tiles[j] - 1) - u0 + 1;
-  const int64_t row0 = ((int64_t)u0 + j * a.Hkv + kv) * a.part_rows + p;
-  float m = -INFINITY;
-  for (int s = 0; s < nsp; ++s) m = fmaxf(m, a.mlpart[2 * (row0 + (int64_t)s * a.part_rows)]);
-  float lsum = 0.f, acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  for (int s = 0; s < nsp; ++s) {
-    const int64_t row = row0 + (int64_t)s * a.part_rows;
-    const float w = exp2f(a.mlpart[2 * row] - m);
-    lsum += w * a.mlpart[2 * row + 1];
-    const uint4 x = *reinterpret_cast<const uint4 *>(a.opart + row * D + 8 * c8);
-    const uint32_t xw[4] = {x.x, x.y, x.z, x.w};
+  const int64_t rg0 = ((int64_t)u0 + j * a.Hkv + kv) * a.part_groups + rgi;
+  const float4 *op = reinterpret_cast<const float4 *>(a.opart) + (rg0 * (D / 8) + 4 * db) * 64 + lane;
+  const int64_t ostep = (int64_t)a.part_groups * (D / 8) * 64, mstep = (int64_t)a.part_groups * 32;
+  const float2 *ml = reinterpret_cast<const float2 *>(a.mlpart) + rg0 * 32 + l32;
+
+  float m = -1e30f, l = 0.f;
+  float4 acc[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      acc[2 * i] += w * __uint_as_float(xw[i] << 16);
-      acc[2 * i + 1] += w * __uint_as_float(xw[i] & 0xffff0000u);
+  for (int g = 0; g < 4; ++g) acc[g] = float4{0.f, 0.f, 0.f, 0.f};
+  for (int s0 = wave; s0 < nsp; s0 += 4 * kCombineAhead) {
+    float2 x[kCombineAhead];
+    float4 v[kCombineAhead][4];
+#pragma unroll
+    for (int u = 0; u < kCombineAhead; ++u) {
+      const int s = s0 + 4 * u;
+      if (s >= nsp) {
+        x[u] = float2{-1e30f, 0.f};
+#pragma unroll
+        for (int g = 0; g < 4; ++g) v[u][g] = float4{0.f, 0.f, 0.f, 0.f};
+        continue;
+      }
+      x[u] = ml[s * mstep];
+#pragma unroll
+      for (int g = 0; g < 4; ++g) v[u][g] = op[s * ostep + g * 64];
+    }
+    float mn = m;
+#pragma unroll
+    for (int u = 0; u < kCombineAhead; ++u) mn = fmaxf(mn, x[u].x);
+    const float w0 = exp2f(m - mn);
+    m = mn;
+    l *= w0;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) acc[g] = float4{acc[g].x * w0, acc[g].y * w0, acc[g].z * w0, acc[g].w * w0};
+#pragma unroll
+    for (int u = 0; u < kCombineAhead; ++u) {
+      const float w = exp2f(x[u].x - m);
+      l += w * x[u].y;
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const float4 y = v[u][g];
+        acc[g].x += w * y.x;
+        acc[g].y += w * y.y;
+        acc[g].z += w * y.z;
+        acc[g].w += w * y.w;
+      }
     }
   }
+  __shared__ float4 sacc[4][4][64];
+  __shared__ float2 sml[4][64];
+#pragma unroll
+  for (int g = 0; g < 4; ++g) sacc[wave][g][lane] = acc[g];
+  sml[wave][lane] = float2{m, l};
+  __syncthreads();
+  // wave w finishes the 4-channel group w
+  float mt = sml[0][lane].x, lsum = 0.f;
+#pragma unroll
+  for (int w = 1; w < 4; ++w) mt = fmaxf(mt, sml[w][lane].x);
+  float4 t = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    const float2 x = sml[w][lane];
+    const float4 y = sacc[w][wave][lane];
+    const float e = exp2f(x.x - mt);
+    lsum += e * x.y;
+    t.x += e * y.x;
+    t.y += e * y.y;
+    t.z += e * y.z;
+    t.w += e * y.w;
+  }
+  const int p = rgi * 32 + l32;
+  if (p >= P) return;
   const int r = p / G, h = kv * G + (p - r * G);
   if (a.out != nullptr) {
     const float inv = 1.f / lsum;
-    uint16_t *orow = a.out + a.slot[j] * a.q_lstride + ((int64_t)r * a.Hq + h) * D + 8 * c8;
-    uint32_t w[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-      w[i] = (uint32_t)f2bf(acc[2 * i] * inv) | ((uint32_t)f2bf(acc[2 * i + 1] * inv) << 16);
-    *reinterpret_cast<uint4 *>(orow) = uint4{w[0], w[1], w[2], w[3]};
+    uint16_t *orow = a.out + a.slot[j] * a.q_lstride + ((int64_t)r * a.Hq + h) * D + 32 * db + 8 * wave + 4 * half;
+    *reinterpret_cast<uint2 *>(orow) = uint2{(uint32_t)f2bf(t.x * inv) | ((uint32_t)f2bf(t.y * inv) << 16),
+                                             (uint32_t)f2bf(t.z * inv) | ((uint32_t)f2bf(t.w * inv) << 16)};
   }
-  if (a.lse != nullptr && c8 == 0)
-    a.lse[layer * a.lse_lstride + (int64_t)kv * P + p] = m + log2f(lsum);
+  if (a.lse != nullptr && db == 0 && wave == 0 && half == 0)
+    a.lse[layer * a.lse_lstride + (int64_t)kv * P + p] = mt + log2f(lsum);
 }
 
 template <int D>
@@ -798,38 +934,44 @@ __global__ __launch_bounds__(kNormBlock *MG) void mass_reduce(ColsumArgs a) {
 
 }  // namespace
 
+template <int D, int KG>
+static void plain_pass(const AttnArgs &a, int n_list, hipStream_t s) {
+  constexpr int rows = BM / KG;
+  const int nqt = (a.C * (a.Hq / a.Hkv) + rows - 1) / rows;
+  const dim3 grid(nqt * a.Hkv * n_list);
+  if (a.out != nullptr) hipLaunchKernelGGL((attn_fwd<D, KG, false, true>), grid, dim3(AT), 0, s, a, nqt);
+  else hipLaunchKernelGGL((attn_fwd<D, KG, false, false>), grid, dim3(AT), 0, s, a, nqt);
+}
+
+template <int D>
+static void plain_pass_of(const AttnArgs &a, int n_list, int key_groups, hipStream_t s) {
+  switch (key_groups) {
+    case 8: plain_pass<D, 8>(a, n_list, s); break;
+    case 4: plain_pass<D, 4>(a, n_list, s); break;
+    case 2: plain_pass<D, 2>(a, n_list, s); break;
+    default: plain_pass<D, 1>(a, n_list, s); break;
+  }
+}
+
 hipError_t launch_attention(const AttnArgs &a, int n_list, int head_dim, hipStream_t s) {
+  if (head_dim == 64) plain_pass_of<64>(a, n_list, a.key_groups, s);
+  else plain_pass_of<128>(a, n_list, a.key_groups, s);
+  return hipGetLastError();
+}
+
+template <int D>
+static hipError_t stream_pass(const AttnArgs &a, int n_list, hipStream_t s) {
   const int P = a.C * (a.Hq / a.Hkv);
   const int nqt = (P + BM - 1) / BM;
-  dim3 grid(nqt * a.Hkv * n_list);
-  const bool wo = a.out != nullptr;
-  if (head_dim == 64) {
-    if (wo) hipLaunchKernelGGL((attn_fwd<64, false, true>), grid, dim3(AT), 0, s, a, nqt);
-    else hipLaunchKernelGGL((attn_fwd<64, false, false>), grid, dim3(AT), 0, s, a, nqt);
-  } else {
-    if (wo) hipLaunchKernelGGL((attn_fwd<128, false, true>), grid, dim3(AT), 0, s, a, nqt);
-    else hipLaunchKernelGGL((attn_fwd<128, false, false>), grid, dim3(AT), 0, s, a, nqt);
-  }
+  hipLaunchKernelGGL((attn_fwd<D, 1, true, true>), dim3(a.st_units * nqt), dim3(AT), 0, s, a, nqt);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(attn_combine<D>, dim3(a.part_groups * (D / 32), a.Hkv, n_list), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 
 hipError_t launch_attention_stream(const AttnArgs &a, int n_list, int head_dim, hipStream_t s) {
-  const int P = a.C * (a.Hq / a.Hkv);
-  const int nqt = (P + BM - 1) / BM;
-  dim3 grid(a.st_units * nqt);
-  dim3 cgrid((P * (head_dim / 8) + 255) / 256, a.Hkv, n_list);
-  if (head_dim == 64) {
-    hipLaunchKernelGGL((attn_fwd<64, true, true>), grid, dim3(AT), 0, s, a, nqt);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(attn_combine<64>, cgrid, dim3(256), 0, s, a);
-  } else {
-    hipLaunchKernelGGL((attn_fwd<128, true, true>), grid, dim3(AT), 0, s, a, nqt);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(attn_combine<128>, cgrid, dim3(256), 0, s, a);
-  }
-  return hipGetLastError();
+  return head_dim == 64 ? stream_pass<64>(a, n_list, s) : stream_pass<128>(a, n_list, s);
 }
 
 hipError_t launch_colsum(const ColsumArgs &a, int n_list, int max_T, int head_dim,

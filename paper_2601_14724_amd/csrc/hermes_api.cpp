@@ -24,11 +24,11 @@ size_t round_up(size_t x) { return (x + kAlign - 1) & ~(kAlign - 1); }
 bool aligned(const void *p, size_t a) { return (reinterpret_cast<uintptr_t>(p) % a) == 0; }
 
 struct Layout {
-  size_t tab, lse, keys, kept, normpart, newc, wpart, spart, sumk, sumv, smeta, flag, opart, mlpart, total;
+  size_t tab, lse, keys, kept, normpart, newc, wpart, spart, sumk, sumv, smeta, flag, opart, mlpart, aopart, amlpart, total;
   int64_t lse_lstride, keys_lstride, kept_lstride, wpart_lstride, spart_lstride, normpart_lstride,
       newc_lstride;
-  int32_t part_rows;
-  int64_t part_blocks;      // stream-mode partial blocks of part_rows rows the workspace holds
+  int64_t part_rows;        // stream-mode partial rows of queries and prompts
+  int64_t append_rows;      // and of appends, per layer (layers on different streams do not share them)
 };
 
 int max_budget(const hermes_config *c) {
@@ -81,11 +81,12 @@ int check_config(const hermes_config *c) {
   return HERMES_OK;
 }
 
-// Workspace layout of `c`; part_blocks < 0 sizes the stream-mode partial
-// state for the most blocks any short pass can write (one per unit plus one
-// per (layer, KV head) pair), else for that many partial blocks.  `splits`:
-// with each layer's room for sweeps cut along the query rows.
-Layout layout_of(const hermes_config *c, int64_t part_blocks = -1, bool splits = true) {
+// Workspace layout of `c`; part_rows < 0 sizes the stream-mode partial state
+// for the most rows a short pass can write (256 for each of kStreamSlots
+// workgroups, and a block more for each (layer, KV head) pair), else for that
+// many rows.  `splits`: with each layer's room for appends cut along the keys
+// and sweeps cut along the query rows.
+Layout layout_of(const hermes_config *c, int64_t part_rows = -1, bool splits = true) {
   Layout s;
   s.lse_lstride = (int64_t)c->n_q_heads * c->max_chunk;
   s.keys_lstride = c->max_cap;
@@ -126,21 +127,30 @@ Layout layout_of(const hermes_config *c, int64_t part_blocks = -1, bool splits =
   s.flag = off;
   off = round_up(off + sizeof(int32_t) * 4);
   // stream-mode partial state of short passes (query, guidance prompt)
-  s.part_rows = kSplitMaxTokens * (c->n_q_heads / c->n_kv_heads);
-  s.part_blocks = part_blocks >= 0 ? part_blocks : (int64_t)c->n_layers * c->n_kv_heads + kStreamSlots;
-  const size_t prow = (size_t)s.part_blocks * s.part_rows;
+  const int64_t G = c->n_q_heads / c->n_kv_heads;
+  s.part_rows = part_rows >= 0 ? part_rows
+                               : (int64_t)kStreamSlots * kAttnRowsPerBlock +
+                                     (int64_t)c->n_layers * c->n_kv_heads * kSplitMaxTokens * G;
   s.opart = off;
-  off = round_up(off + sizeof(uint16_t) * prow * c->head_dim);
+  off = round_up(off + sizeof(float) * (size_t)s.part_rows * c->head_dim);
   s.mlpart = off;
-  off = round_up(off + sizeof(float) * prow * 2);
+  off = round_up(off + sizeof(float) * 2 * (size_t)s.part_rows);
+  // and of appends: at most one block for two key tiles, and one for each pair
+  const int64_t blocks = (int64_t)c->n_kv_heads * (((int64_t)c->max_cap + 63) / 64 / 2 + 1);
+  const int64_t rows = (c->max_chunk * G + 31) / 32 * 32;
+  s.append_rows = !splits ? 0 : rows > kAppendPartRows / blocks ? kAppendPartRows : blocks * rows;
+  s.aopart = off;
+  off = round_up(off + sizeof(float) * (size_t)s.append_rows * c->head_dim * c->n_layers);
+  s.amlpart = off;
+  off = round_up(off + sizeof(float) * 2 * (size_t)s.append_rows * c->n_layers);
   s.total = off;
   return s;
 }
 
 // The layout of `c` in at most `limit` bytes: the default one if it fits,
-// else without the room for splits and with as many stream-mode partial
-// blocks as the rest leaves (possibly none: short passes then run the plain
-// kernel).  false if even that exceeds `limit`.
+// else without the room for splits and with as many stream-mode partial rows
+// as the rest leaves (possibly none: short passes then run the plain kernel).
+// false if even that exceeds `limit`.
 bool layout_within(const hermes_config *c, size_t limit, Layout *out) {
   for (const bool splits : {true, false}) {
     const Layout full = layout_of(c, -1, splits);
@@ -151,53 +161,88 @@ bool layout_within(const hermes_config *c, size_t limit, Layout *out) {
   }
   const Layout none = layout_of(c, 0, false);
   if (none.total > limit) return false;
-  const size_t per_block = (size_t)none.part_rows * (sizeof(uint16_t) * c->head_dim + 2 * sizeof(float));
-  int64_t blocks = (int64_t)((limit - none.total) / per_block);
+  int64_t rows = (int64_t)((limit - none.total) / (sizeof(float) * (c->head_dim + 2)));
   // the two regions are rounded up separately: back off until it fits
-  while (blocks > 0 && layout_of(c, blocks, false).total > limit) --blocks;
-  *out = layout_of(c, blocks, false);
+  while (rows > 0 && layout_of(c, rows, false).total > limit) rows = rows > 64 ? rows - 64 : 0;
+  *out = layout_of(c, rows, false);
   return true;
 }
 
-// Stream plan of a short pass (n_rows <= kSplitMaxTokens rows per entry over
-// caches of at.T0[j] tokens).  The plain kernel runs one workgroup per
-// (entry, KV head, query tile) over its whole cache, so the entry with the
-// longest cache sets the time while the other CUs idle.  Stream mode cuts
-// the concatenated key tiles of all pairs into U equal ranges, U units of
-// nqt workgroups filling one round of kStreamSlots, so every CU gets the same
-// number of tiles; it pays a partial write per (unit, pair) touched and the
-// combine launch.  Costs in key-tile times: a round also pays about two
-// tiles of fixed work (query load, epilogue), the combine about two, and the
-// partial writes about one tile per 64 * 128 / D workgroup blocks.  Stream
-// mode is used when it promises at least 10% over the plain kernel and the
-// workspace holds its U + pairs - 1 partial blocks.  Fills the st_* fields
-// (st_units = 0 for the plain kernel).
-void stream_plan(AttnArgs &at, int n_rows, int G, int Hkv, int n_list, int D, int64_t max_blocks) {
-  const int nqt = (n_rows * G + kAttnRowsPerBlock - 1) / kAttnRowsPerBlock;
+// How a pass of n_rows rows per entry over caches of at.T0[j] tokens is cut
+// into workgroups, with room for part_rows partial rows.  Three ways, of which
+// the cheapest by the estimate below is taken:
+//  - the plain kernel with one key group: a workgroup per (entry, KV head, 256
+//    packed rows) over its whole sequence.  Few of them leave CUs idle, and
+//    the entry with the longest cache sets the time;
+//  - with 2, 4 or 8 key groups: that many times the workgroups, each of a
+//    2nd, 4th or 8th of the rows and steps, whose K/V tiles serve fewer rows;
+//  - stream mode: the concatenated key tiles of all pairs in U equal ranges, U
+//    units of a workgroup per 256 rows, so every CU gets the same number of
+//    tiles; it pays a partial write and read per (unit, pair) touched and the
+//    combine launch.
+// Costs are in steps of the plain kernel (a 64-key tile of 256 rows: 1.42 us
+// at head size 128 while CUs are idle, 1.8 us with all busy).  A launch takes
+// one step of a round of kStreamSlots workgroups after the other, each round
+// with two more for its queries and epilogue.  Measured against one key group
+// a step over 2 / 4 / 8 of them costs 1.09-1.17 / 1.37-1.65 / 1.7-2.1 (28
+// layers of 8976 tokens; one layer), a stream step 1.1 (head size 128) or 1.25
+// (64), and the partials' traffic 0.27 a MB on top of 4 for the combine.  One
+// layer, us, key groups 1 / 2 / 4 / 8 and stream mode: 784 rows on 8192 tokens
+// 200 / 119 / 173 / 163 / 110, 784 on 1568 63 / 41 / 55 / 57 / 46, 196 on 6144
+// 141 / 83 / 60 / 41 / 31 (28 query heads, 4 KV heads of 128); 784 on 4096 84 /
+// 48 / 33 / 35 / 34, 196 on 1024 24 / 17 / 10 / 7 / 12 (14 and 2 of 64).
+// Fills key_groups and the st_* fields (st_units = 0 for the plain kernel).
+void attention_plan(AttnArgs &at, int n_rows, int G, int Hkv, int n_list, int D, int64_t part_rows) {
+  const int64_t P = (int64_t)n_rows * G;
+  const int64_t pairs = (int64_t)n_list * Hkv;
+  at.key_groups = 1;
   at.st_units = 0;
   at.st_entries = n_list;
+  at.part_groups = (int32_t)((P + 31) / 32);
   int64_t total = 0;
   int max_tiles = 1;
   for (int j = 0; j < n_list; ++j) {
-    const int tiles = (at.T0[j] + n_rows + 63) / 64;
+    const int tiles = (at.T0[j] + 63) / 64 + (n_rows + 63) / 64;
     at.st_tiles[j] = tiles;
     at.st_off[j] = (int32_t)total;
     total += (int64_t)Hkv * tiles;
     max_tiles = tiles > max_tiles ? tiles : max_tiles;
   }
+  auto rounds = [](int64_t w) { return (double)((w + kStreamSlots - 1) / kStreamSlots); };
+  static const double kStep[4] = {1.0, 1.12, 1.5, 1.9};
+  double best = 0.0;
+  for (int e = 0; e < 4; ++e) {
+    const int64_t rows = kAttnRowsPerBlock >> e;
+    // a pair's only workgroup takes its keys from HBM: a step over eight
+    // groups then costs twice as much (1 row on 4096..16384 tokens, 28 layers:
+    // 199 us, 125 in stream mode)
+    const double step = P <= rows && e > 0 ? 2.0 * kStep[e] : kStep[e];
+    const double cost = rounds((P + rows - 1) / rows * pairs) * ((double)((max_tiles + (1 << e) - 1) >> e) * step + 2.0);
+    if (e == 0 || cost < best) {
+      best = cost;
+      at.key_groups = 1 << e;
+    }
+  }
+  if (total > INT32_MAX / 2) return;
   at.st_off[n_list] = (int32_t)total;
   at.st_total = (int32_t)total;
-  if (n_rows > kSplitMaxTokens || total > INT32_MAX / 2) return;
-  const int64_t pairs = (int64_t)n_list * Hkv;
-  int64_t units = kStreamSlots / nqt;
-  units = units < total ? units : total;
-  units = units < max_blocks - pairs + 1 ? units : max_blocks - pairs + 1;
-  if (units < 2) return;
-  auto rounds = [](int64_t w) { return (double)((w + kStreamSlots - 1) / kStreamSlots); };
-  const double plain = rounds((int64_t)nqt * pairs) * (max_tiles + 2.0);
-  const double per_unit = (double)((total + units - 1) / units);
-  const double stream = per_unit + 2.0 + 2.0 + (double)(units + pairs) * nqt * D / (64.0 * 128.0);
-  if (stream < 0.9 * plain) at.st_units = (int32_t)units;
+  const int64_t nqt = (P + kAttnRowsPerBlock - 1) / kAttnRowsPerBlock;
+  const int64_t most = part_rows / (32 * (int64_t)at.part_groups) - pairs + 1;
+  const double step = D == 128 ? 1.1 : 1.25;
+  const double mb = 32e-6 * at.part_groups * 4 * (D + 2);   // of a unit's partial rows
+  // one and two full rounds of workgroups, and parts of one (their partials
+  // cost less)
+  static const int kNum[8] = {8, 4, 3, 2, 4, 1, 2, 1}, kDen[8] = {4, 4, 4, 4, 6, 3, 8, 6};
+  for (int c = 0; c < 8; ++c) {
+    const int64_t units = kStreamSlots * kNum[c] / (kDen[c] * nqt);
+    if (units < 2 || units > most || units > total) continue;
+    const double cost = rounds(units * nqt) * ((double)((total + units - 1) / units) * step + 2.0) + 4.0 +
+                        0.27 * mb * (double)(units + pairs);
+    if (cost < best) {
+      best = cost;
+      at.st_units = (int32_t)units;
+    }
+  }
 }
 
 // Query-row splits of a mass sweep of n_list layers of at most max_T
@@ -751,9 +796,21 @@ static int append_impl(hermes_ctx *ctx, int32_t layer, const void *q, const void
     }
   }
 
+  {
+    // all layers' partial rows for a call on all of them, else the layer's own
+    const int64_t rows = ctx->lay.append_rows;
+    const int64_t first = layer == HERMES_ALL_LAYERS ? 0 : layer * rows;
+    attention_plan(at, n_new, ctx->Hq / ctx->Hkv, ctx->Hkv, (int)list.size(), ctx->D,
+                rows * (int64_t)list.size());
+    at.opart = reinterpret_cast<float *>(ctx->ws + ctx->lay.aopart) + first * ctx->D;
+    at.mlpart = reinterpret_cast<float *>(ctx->ws + ctx->lay.amlpart) + first * 2;
+  }
   int rc = ctx->run(HERMES_K_APPEND, s, [&] { return launch_append(ap, s); });
   if (rc != HERMES_OK) return rc;
-  rc = ctx->run(HERMES_K_ATTN, s, [&] { return launch_attention(at, (int)list.size(), ctx->D, s); });
+  rc = ctx->run(HERMES_K_ATTN, s, [&] {
+    return at.st_units > 0 ? launch_attention_stream(at, (int)list.size(), ctx->D, s)
+                           : launch_attention(at, (int)list.size(), ctx->D, s);
+  });
   if (rc != HERMES_OK) return rc;
   if (n_cs > 0) {
     mass_splits(cs, n_cs, max_T, ctx->lay.wpart_lstride);
@@ -865,9 +922,8 @@ int hermes_guidance_score(hermes_ctx *ctx, int32_t layer, const void *q, const v
   }
   const int n = (int)list.size();
   mass_splits(cs, n, max_T, ctx->lay.wpart_lstride);
-  stream_plan(at, n_rows, ctx->Hq / ctx->Hkv, ctx->Hkv, n, ctx->D, ctx->lay.part_blocks);
-  at.part_rows = ctx->lay.part_rows;
-  at.opart = reinterpret_cast<uint16_t *>(ctx->ws + ctx->lay.opart);
+  attention_plan(at, n_rows, ctx->Hq / ctx->Hkv, ctx->Hkv, n, ctx->D, ctx->lay.part_rows);
+  at.opart = reinterpret_cast<float *>(ctx->ws + ctx->lay.opart);
   at.mlpart = reinterpret_cast<float *>(ctx->ws + ctx->lay.mlpart);
   const int rc = ctx->run(HERMES_K_GUIDE, s, [&] {
     hipError_t e = at.st_units > 0 ? launch_attention_stream(at, n, ctx->D, s)
@@ -1112,9 +1168,8 @@ int hermes_query_attend(hermes_ctx *ctx, int32_t layer, const void *q, const voi
     at.cur[n] = ctx->cur[l];
     ++n;
   }
-  stream_plan(at, n_q, ctx->Hq / ctx->Hkv, ctx->Hkv, n, ctx->D, ctx->lay.part_blocks);
-  at.part_rows = ctx->lay.part_rows;
-  at.opart = reinterpret_cast<uint16_t *>(ctx->ws + ctx->lay.opart);
+  attention_plan(at, n_q, ctx->Hq / ctx->Hkv, ctx->Hkv, n, ctx->D, ctx->lay.part_rows);
+  at.opart = reinterpret_cast<float *>(ctx->ws + ctx->lay.opart);
   at.mlpart = reinterpret_cast<float *>(ctx->ws + ctx->lay.mlpart);
   return ctx->run(HERMES_K_QUERY, s, [&] {
     return at.st_units > 0 ? launch_attention_stream(at, n, ctx->D, s)

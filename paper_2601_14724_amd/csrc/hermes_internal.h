@@ -53,19 +53,20 @@ struct AttnArgs {
   int8_t layer_id[kMaxLayers];
   int8_t slot[kMaxLayers];      // index of the layer's inputs in the stacked tensors
   int8_t cur[kMaxLayers];
-  // Stream mode (short passes): the key tiles of every (entry, KV head) pair,
-  // concatenated in pair order (entry j's Hkv pairs of st_tiles[j] tiles each
-  // start at tile st_off[j]; st_total tiles in all), are cut into st_units
-  // equal ranges of nqt workgroups each.  Unit u writes the unnormalised O
-  // (bf16), running maximum and row sum (fp32) of each pair k it touches to
-  // opart / mlpart block u + k ([block][part_rows]); a combine kernel merges
-  // each pair's blocks.  st_units = 0: the plain kernel, one workgroup per
-  // (entry, KV head, query tile).
-  int32_t st_units, st_total, st_entries, part_rows;
+  // Stream mode: the key tiles of every (entry, KV head) pair, concatenated in
+  // pair order (entry j's Hkv pairs of st_tiles[j] tiles each start at tile
+  // st_off[j]; st_total tiles in all), are cut into st_units equal ranges of
+  // nqt workgroups each.  Unit u writes the unnormalised O, running maximum
+  // and row sum (fp32) of each pair k it touches to opart / mlpart block u + k
+  // of part_groups 32-row groups; a combine kernel merges each pair's blocks.
+  // st_units = 0: the plain kernel, one workgroup per (entry, KV head, query
+  // tile).
+  int32_t st_units, st_total, st_entries, part_groups;
+  int32_t key_groups;       // plain kernel: 1, 2, 4 or 8 groups of waves that share the keys (256 / key_groups rows a workgroup)
   int32_t st_off[kMaxLayers + 1];
   int32_t st_tiles[kMaxLayers];
-  uint16_t *opart;          // [..][part_rows][d] bf16 (unnormalised; its scale is in mlpart)
-  float *mlpart;            // [..][part_rows][2] fp32 (max, sum)
+  float *opart;             // [..][part_groups][d / 8][64 lanes][4 channels] fp32 (unnormalised; scale in mlpart)
+  float *mlpart;            // [..][part_groups * 32][2] fp32 (max, sum)
 };
 
 // Attention-mass sweep: W_i for the candidates i < ncand[j] of layer
@@ -263,7 +264,8 @@ constexpr int kColsumKeysPerBlock = 256; // candidates per workgroup of the swee
 constexpr int kMassSplitMax = 32;       // ranges a sweep's query rows are cut into at most
 constexpr int64_t kMassPartials = 1024 * 256;   // fp64 partials a layer keeps for them
 constexpr int kSummaryRows = 128;        // candidates per workgroup of the summary sums
-constexpr int kSplitMaxTokens = 64;      // passes of at most this many rows use stream mode
+constexpr int kSplitMaxTokens = 64;      // rows of a query or prompt that the workspace holds the stream state of
+constexpr int64_t kAppendPartRows = 81920;   // partial rows of stream-mode appends a layer keeps at most
 constexpr int kStreamSlots = 256;        // resident attention workgroups (one per CU)
 constexpr int kNormBlock = 256;         // candidates per fp64 partial of the score normaliser
 
