@@ -79,7 +79,7 @@ __device__ __forceinline__ int xcd_remap(int i, int n) {
 // kv, st_tiles[j] tiles each, entry j's pairs from tile st_off[j]), are cut
 // into st_units equal ranges; unit u is nqt workgroups with consecutive ids
 // (one per query tile, sharing the K/V tiles in their XCD's L2) over tiles
-// [u N / U, (u + 1) N / U).  The workgroup walks its range in one tile loop;
+// [u N / U, (u + 1) N / U).  The workgroup walks its range pair by pair;
 // where the range leaves a pair it writes the pair's unnormalised partial
 // state (fp32 O, running maximum and row sum) to partial block (u + k)
 // of its query tile (distinct for every (u, k): a later unit only covers
@@ -87,22 +87,30 @@ __device__ __forceinline__ int xcd_remap(int i, int n) {
 // blocks.  Otherwise: one workgroup per (entry, KV head, query tile) over its
 // whole sequence, writing O (WRITE_O) and the row LSE.
 //
-// KG key groups: the workgroup's 8 waves are KG groups of RG = 8 / KG waves; a
-// group holds all of the workgroup's 32 RG packed rows and takes every KG-th
+// KG key groups: the workgroup's NW waves are KG groups of RG = NW / KG waves;
+// a group holds all of the workgroup's 32 RG packed rows and takes every KG-th
 // key tile, and the groups' states are merged through LDS at the end.  Rows a
 // workgroup shrink by KG, so a launch has KG times the workgroups and each
 // walks a KG-th of the keys: what a launch of few rows needs to fill the CUs,
 // for KG times the K/V staging per row.
-template <int D, int KG, bool STREAM, bool WRITE_O>
-__global__ __launch_bounds__(AT, 1) void attn_fwd(AttnArgs a, int nqt) {
-  static_assert(!STREAM || KG == 1, "stream mode walks one key group");
-  constexpr int RG = 8 / KG;                // 32-row groups (waves of a key group)
+//
+// SPLIT: passes whose packed rows fit one workgroup (a few tokens: decoding).
+// No two workgroups share a key, so the pass is bound by HBM, and by latency
+// where a CU has little to read.  Each pair's steps are cut into st_tiles[j]
+// ranges of st_units steps, one workgroup each (entry j's from st_off[j]), of
+// four waves so that two of them share a CU: one's start and end hide behind
+// the other's loads.  Each writes its partial state as in stream mode.
+enum { PLAIN = 0, STREAMED = 1, SPLIT = 2 };
+template <int D, int NW, int KG, int MODE, bool WRITE_O>
+__global__ __launch_bounds__(64 * NW, NW == 8 ? 1 : 2) void attn_fwd(AttnArgs a, int nqt) {
+  constexpr bool STREAM = MODE == STREAMED;
+  constexpr int RG = NW / KG;               // 32-row groups (waves of a key group)
   constexpr int BM = 32 * RG;               // packed rows of the workgroup
-  constexpr int BN = KG <= 2 ? 64 : 32;     // keys per tile
+  constexpr int BN = KG <= NW / 4 ? 64 : 32;   // keys per tile
   constexpr int SUB = BN / 32;
-  constexpr int NBUF = KG == 8 ? 1 : 2;     // (a tile of one wave needs no second buffer)
+  constexpr int NBUF = RG == 1 ? 1 : 2;     // (a tile of one wave needs no second buffer)
   constexpr int GT = 64 * RG;               // threads of a key group
-  const int lin = xcd_remap(blockIdx.x, gridDim.x);
+  const int lin = MODE == SPLIT ? (int)blockIdx.x : xcd_remap(blockIdx.x, gridDim.x);
   const int qtile = lin % nqt;
   const int C = a.C, Hq = a.Hq, Hkv = a.Hkv;
   const int G = Hq / Hkv;
@@ -171,17 +179,24 @@ __global__ __launch_bounds__(AT, 1) void attn_fwd(AttnArgs a, int nqt) {
     // follow GT / CH rows apart
     cofs = (uint32_t)(((tid / CH) * row_stride + kv * D + (tid % CH) * 8) * sizeof(uint16_t));
   };
-  // the pair holding concatenated tile x (STREAM), its first tile in `first`
+  // the pair holding concatenated tile x (STREAM) or range x (SPLIT), its
+  // first one in `f`
   auto locate = [&](int x, int &jj, int &kvv, int &f) {
+    // (no branch, so the search stays scalar: with a loop, or a load under a
+    // condition, the loops below need 60 more vector registers and spill)
     int e = 0;
-    while (e + 1 < a.st_entries && x >= a.st_off[e + 1]) ++e;
+#pragma unroll
+    for (int b = kMaxLayers / 2; b > 0; b >>= 1) {
+      const int at = a.st_off[e + b];       // (unused entries are not taken)
+      e += (int)(e + b < a.st_entries) & (int)(x >= at) ? b : 0;
+    }
     jj = e;
     kvv = __builtin_amdgcn_readfirstlane((x - a.st_off[e]) / a.st_tiles[e]);
     f = a.st_off[e] + kvv * a.st_tiles[e];
   };
-  if constexpr (STREAM) {
+  if constexpr (MODE != PLAIN) {
     int jj, kvv;
-    locate(x_lo, jj, kvv, first);
+    locate(STREAM ? x_lo : lin, jj, kvv, first);
     enter(jj, kvv);
   } else {
     enter(lin / (nqt * Hkv), (lin / nqt) % Hkv);
@@ -373,162 +388,98 @@ __global__ __launch_bounds__(AT, 1) void attn_fwd(AttnArgs a, int nqt) {
 
   using NoMask = std::integral_constant<bool, false>;
   using Mask = std::integral_constant<bool, true>;
-  // unnormalised partial state of the current pair into partial block blk.
-  // Each 32-row group is stored as the wave holds it ([4-channel group][lane]),
-  // so that both the stores and the combine's loads are contiguous.
-  auto flush = [&](int64_t blk) {
-    const float l_tot = l_run + __shfl_xor(l_run, 32);
-    if (wave_rows) {
-      const int64_t rg = blk * a.part_groups + (p0 >> 5) + wave;
-      float4 *op = reinterpret_cast<float4 *>(a.opart) + rg * (D / 8) * 64 + lane;
-#pragma unroll
-      for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-        for (int grp = 0; grp < 4; ++grp)
-          op[(4 * db + grp) * 64] = float4{o[db][4 * grp + 0], o[db][4 * grp + 1], o[db][4 * grp + 2],
-                                           o[db][4 * grp + 3]};
-      if (half == 0) *reinterpret_cast<float2 *>(a.mlpart + 2 * (rg * 32 + l32)) = float2{m_run, l_tot};
+  // Steps [s0, s0 + n) of the current pair: step x covers tiles x KG .. x KG +
+  // KG - 1, one for each key group.  Steady state: this step's tiles and the
+  // next one's are pure (no branch in the body); the last pure step joins the
+  // general loop, where it is unmasked.
+  auto walk = [&](int s0, int n) {
+    int steps = (ntiles + KG - 1) / KG, pure_steps = n_pure / KG, tile0 = kg;
+    if constexpr (MODE != PLAIN) {
+      steps = min(steps - s0, n);
+      pure_steps = min(pure_steps - s0, steps);
+      tile0 += s0 * KG;
     }
-  };
-  if constexpr (STREAM) {
-    // One tile loop over the range; leaving a pair (rare) flushes it, moves
-    // to the next pair and loads that pair's first tile without prefetch.
-    // (One instance of the tile body: with a loop over pairs around the loops
-    // below, it spills.)
-    int t = x_lo - first;
-    int pair_n = a.st_tiles[j];
-    int k = j * Hkv + kv;
-    if (t < n_pure) load_pure(t); else load_any(t);
-    int b = 0;
-    for (int x = x_lo; x < x_hi; ++x) {
-      store_tile(b);
-      __syncthreads();
-      const bool pair_end = t + 1 == pair_n;
-      if (!pair_end && x + 1 < x_hi) {
-        if (t + 1 < n_pure) load_pure(t + 1); else load_any(t + 1);
-      }
-      // tiles past this query tile's own causal limit hold no visible key
-      if (wave_rows && t < ntiles) compute(b, t, edge(t));
-      if (pair_end && x + 1 < x_hi) {
-        flush(u + k);
-        if (kv + 1 < Hkv) enter(j, kv + 1); else enter(j + 1, 0);
-        pair_n = a.st_tiles[j];
-        ++k;
-#pragma unroll
-        for (int db = 0; db < D / 32; ++db) o[db] = f32x16{};
-        m_run = -1e30f;
-        m_lim = (m_run + 8.f) * inv_c;
-        l_run = 0.f;
-        t = 0;
-        if (n_pure > 0) load_pure(0); else load_any(0);
+    auto tile = [&](int s) { return s * KG + tile0; };
+    // the group's waves wait for their tile's stores (all groups take the same
+    // steps; a group of one wave only keeps its own order)
+    auto sync = [&] {
+      if constexpr (RG > 1) __syncthreads();
+      else __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    };
+    if (pure_steps > 0) load_pure(tile(0)); else load_any(tile(0));
+    int s = 0;
+    // two steps per trip, so that the LDS buffer of each is a constant and its
+    // addresses fold into the instructions' offsets
+    for (; s + 2 < pure_steps; s += 2) {
+      store_tile(0);
+      sync();
+      load_pure(tile(s + 1));
+      if (wave_rows) compute(0, tile(s), NoMask{});
+      store_tile(NBUF - 1);
+      sync();
+      load_pure(tile(s + 2));
+      if (wave_rows) compute(NBUF - 1, tile(s + 1), NoMask{});
+    }
+    for (; s + 1 < pure_steps; ++s) {
+      store_tile(s % NBUF);
+      sync();
+      load_pure(tile(s + 1));
+      if (wave_rows) compute(s % NBUF, tile(s), NoMask{});
+    }
+    for (; s < steps; ++s) {
+      store_tile(s % NBUF);
+      sync();
+      if (s + 1 < steps) load_any(tile(s + 1));   // (zeros past the last key)
+      const int t = tile(s);
+      if (!wave_rows || (KG > 1 && t >= ntiles)) {
+      } else if (edge(t)) {
+        compute(s % NBUF, t, Mask{});
       } else {
-        ++t;
+        compute(s % NBUF, t, NoMask{});
       }
-      b ^= 1;
     }
-    flush(u + k);
-    return;
-  }
-  // Step s covers tiles s KG .. s KG + KG - 1, one for each key group.  Steady
-  // state: this step's tiles and the next one's are pure (no branch in the
-  // body); the last pure step joins the general loop, where it is unmasked.
-  const int steps = (ntiles + KG - 1) / KG, pure_steps = n_pure / KG;
-  auto tile = [&](int s) { return s * KG + kg; };
-  // the group's waves wait for their tile's stores (all groups take the same
-  // steps; a group of one wave only keeps its own order)
-  auto sync = [&] {
-    if constexpr (RG > 1) __syncthreads();
-    else __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
   };
-  if (pure_steps > 0) load_pure(tile(0)); else load_any(tile(0));
-  int s = 0;
-  // two steps per trip, so that the LDS buffer of each is a constant and its
-  // addresses fold into the instructions' offsets
-  for (; s + 2 < pure_steps; s += 2) {
-    store_tile(0);
-    sync();
-    load_pure(tile(s + 1));
-    if (wave_rows) compute(0, tile(s), NoMask{});
-    store_tile(NBUF - 1);
-    sync();
-    load_pure(tile(s + 2));
-    if (wave_rows) compute(NBUF - 1, tile(s + 1), NoMask{});
-  }
-  for (; s + 1 < pure_steps; ++s) {
-    store_tile(s % NBUF);
-    sync();
-    load_pure(tile(s + 1));
-    if (wave_rows) compute(s % NBUF, tile(s), NoMask{});
-  }
-  for (; s < steps; ++s) {
-    store_tile(s % NBUF);
-    sync();
-    if (s + 1 < steps) load_any(tile(s + 1));   // (zeros past the last key)
-    const int t = tile(s);
-    if (!wave_rows || (KG > 1 && t >= ntiles)) {
-    } else if (edge(t)) {
-      compute(s % NBUF, t, Mask{});
+  // The key groups' states merge through LDS: every wave leaves its (max, sum)
+  // and O there ([4-channel group][lane], as it holds them), then wave kg of a
+  // row group merges the KG-th part of the channels, groups in order.  mt and
+  // lsum are the merged (max, sum); fn(c, x) gets channel group c.
+  constexpr int NC = D / 8;                   // 4-channel groups of a lane half
+  auto own = [&](int c) {
+    return float4{o[c / 4][4 * (c % 4) + 0], o[c / 4][4 * (c % 4) + 1], o[c / 4][4 * (c % 4) + 2],
+                  o[c / 4][4 * (c % 4) + 3]};
+  };
+  auto merge = [&](float &mt, float &lsum, auto fn) {
+    const float l_tot = l_run + __shfl_xor(l_run, 32);
+    if constexpr (KG == 1) {
+      mt = m_run;
+      lsum = l_tot;
+#pragma unroll
+      for (int c = 0; c < NC; ++c) fn(c, own(c));
     } else {
-      compute(s % NBUF, t, NoMask{});
-    }
-  }
-
-  const float l_tot = l_run + __shfl_xor(l_run, 32);
-  if constexpr (KG == 1) {
-    const float inv = 1.f / l_tot;
-    if (row_ok) {
+      static_assert(NC % KG == 0 && (NW * NC * 64 * 16 + NW * 32 * 8) <= (int)sizeof(tiles), "merge state fits");
+      float4 *mo = reinterpret_cast<float4 *>(tiles);
+      float2 *mm = reinterpret_cast<float2 *>(mo + NW * NC * 64);
+      __syncthreads();   // all tiles are read
       if constexpr (WRITE_O) {
-        uint16_t *orow = a.out + a.slot[j] * a.q_lstride + ((int64_t)r * Hq + kv * G + g) * D;
 #pragma unroll
-        for (int db = 0; db < D / 32; ++db) {
-#pragma unroll
-          for (int grp = 0; grp < 4; ++grp) {
-            const int d0 = 32 * db + 8 * grp + 4 * half;
-            const uint32_t w0 = (uint32_t)f2bf(o[db][4 * grp + 0] * inv) |
-                                ((uint32_t)f2bf(o[db][4 * grp + 1] * inv) << 16);
-            const uint32_t w1 = (uint32_t)f2bf(o[db][4 * grp + 2] * inv) |
-                                ((uint32_t)f2bf(o[db][4 * grp + 3] * inv) << 16);
-            *reinterpret_cast<uint2 *>(orow + d0) = uint2{w0, w1};
-          }
-        }
+        for (int c = 0; c < NC; ++c) mo[((kg * RG + wave) * NC + c) * 64 + lane] = own(c);
       }
-      if (a.lse != nullptr && half == 0) {
-        a.lse[a.layer_id[j] * a.lse_lstride + (int64_t)kv * P + prow] = m_run + log2f(l_tot);
+      if (half == 0) mm[(kg * RG + wave) * 32 + l32] = float2{m_run, l_tot};
+      __syncthreads();
+      float wt[KG];
+      mt = -1e30f;
+      lsum = 0.f;
+#pragma unroll
+      for (int x = 0; x < KG; ++x) {
+        wt[x] = mm[(x * RG + wave) * 32 + l32].x;
+        mt = fmaxf(mt, wt[x]);
       }
-    }
-  } else {
-    // Merge of the key groups: every wave leaves its (max, sum) and O in LDS
-    // ([4-channel group][lane], as it holds them), then wave kg of a row group
-    // merges and writes the KG-th part of the channels, groups in order.
-    constexpr int NC = D / 8;                 // 4-channel groups of a lane half
-    static_assert(NC % KG == 0 && (8 * NC * 64 * 16 + 8 * 32 * 8) <= (int)sizeof(tiles), "merge state fits");
-    float4 *mo = reinterpret_cast<float4 *>(tiles);
-    float2 *mm = reinterpret_cast<float2 *>(mo + 8 * NC * 64);
-    __syncthreads();   // all tiles are read
-    if constexpr (WRITE_O) {
 #pragma unroll
-      for (int c = 0; c < NC; ++c)
-        mo[((kg * RG + wave) * NC + c) * 64 + lane] = float4{o[c / 4][4 * (c % 4) + 0], o[c / 4][4 * (c % 4) + 1],
-                                                             o[c / 4][4 * (c % 4) + 2], o[c / 4][4 * (c % 4) + 3]};
-    }
-    if (half == 0) mm[(kg * RG + wave) * 32 + l32] = float2{m_run, l_tot};
-    __syncthreads();
-    float mt = -1e30f, wt[KG], lsum = 0.f;
-#pragma unroll
-    for (int x = 0; x < KG; ++x) {
-      const float2 v = mm[(x * RG + wave) * 32 + l32];
-      wt[x] = v.x;
-      mt = fmaxf(mt, v.x);
-    }
-#pragma unroll
-    for (int x = 0; x < KG; ++x) {
-      wt[x] = fast_exp2(wt[x] - mt);
-      lsum += wt[x] * mm[(x * RG + wave) * 32 + l32].y;
-    }
-    if (row_ok) {
+      for (int x = 0; x < KG; ++x) {
+        wt[x] = fast_exp2(wt[x] - mt);
+        lsum += wt[x] * mm[(x * RG + wave) * 32 + l32].y;
+      }
       if constexpr (WRITE_O) {
-        const float inv = 1.f / lsum;
-        uint16_t *orow = a.out + a.slot[j] * a.q_lstride + ((int64_t)r * Hq + kv * G + g) * D + 4 * half;
 #pragma unroll
         for (int i = 0; i < NC / KG; ++i) {
           const int c = kg * (NC / KG) + i;
@@ -541,21 +492,71 @@ __global__ __launch_bounds__(AT, 1) void attn_fwd(AttnArgs a, int nqt) {
             t.z += wt[x] * y.z;
             t.w += wt[x] * y.w;
           }
-          *reinterpret_cast<uint2 *>(orow + 8 * c) =
-              uint2{(uint32_t)f2bf(t.x * inv) | ((uint32_t)f2bf(t.y * inv) << 16),
-                    (uint32_t)f2bf(t.z * inv) | ((uint32_t)f2bf(t.w * inv) << 16)};
+          fn(c, t);
         }
       }
-      if (a.lse != nullptr && kg == 0 && half == 0)
-        a.lse[a.layer_id[j] * a.lse_lstride + (int64_t)kv * P + prow] = mt + log2f(lsum);
     }
+  };
+  // unnormalised partial state of the current pair into partial block blk.
+  // Each 32-row group is stored as the wave holds it ([4-channel group][lane]),
+  // so that both the stores and the combine's loads are contiguous.
+  auto flush = [&](int64_t blk) {
+    const int64_t rg = blk * a.part_groups + (p0 >> 5) + wave;
+    float4 *op = reinterpret_cast<float4 *>(a.opart) + rg * NC * 64 + lane;
+    float mt, lsum;
+    merge(mt, lsum, [&](int c, float4 x) {
+      if (wave_rows) op[c * 64] = x;
+    });
+    if (wave_rows && kg == 0 && half == 0)
+      *reinterpret_cast<float2 *>(a.mlpart + 2 * (rg * 32 + l32)) = float2{mt, lsum};
+  };
+  if constexpr (STREAM) {
+    // Pair by pair over the range, each with the loops of the plain kernel (4%
+    // faster than one loop over all tiles with the mask decided at run time).
+    // No early exit and one way out of the loop: a return in it, or before it,
+    // cost 50-70 vector registers and spilled.
+    int t = x_lo - first, k = j * Hkv + kv, x = x_lo;
+    do {
+      const int n = min(a.st_tiles[j] - t, x_hi - x);
+      walk(t, n);
+      flush(u + k);
+      x += n;
+      t = 0;
+      ++k;
+      if (x < x_hi) {
+        if (kv + 1 < Hkv) enter(j, kv + 1); else enter(j + 1, 0);
+#pragma unroll
+        for (int db = 0; db < D / 32; ++db) o[db] = f32x16{};
+        m_run = -1e30f;
+        m_lim = (m_run + 8.f) * inv_c;
+        l_run = 0.f;
+        __syncthreads();   // the last tile (or the merge) may still be read from the buffers that the next one takes
+      }
+    } while (x < x_hi);
+  } else if constexpr (MODE == SPLIT) {
+    walk((lin - first) * a.st_units, a.st_units);
+    flush(lin);
+  } else {
+    walk(0, ntiles);
+    uint16_t *orow = a.out + a.slot[j] * a.q_lstride + ((int64_t)r * Hq + kv * G + g) * D + 4 * half;
+    float mt, lsum;
+    merge(mt, lsum, [&](int c, float4 x) {
+      const float inv = 1.f / lsum;
+      if (WRITE_O && row_ok)
+        *reinterpret_cast<uint2 *>(orow + 8 * c) =
+            uint2{(uint32_t)f2bf(x.x * inv) | ((uint32_t)f2bf(x.y * inv) << 16),
+                  (uint32_t)f2bf(x.z * inv) | ((uint32_t)f2bf(x.w * inv) << 16)};
+    });
+    if (row_ok && a.lse != nullptr && kg == 0 && half == 0)
+      a.lse[a.layer_id[j] * a.lse_lstride + (int64_t)kv * P + prow] = mt + log2f(lsum);
   }
 }
 
 // Merge of a pair's partial blocks: m = max_s m_s, w_s = 2^(m_s - m),
 // O = sum_s w_s O_s / sum_s w_s l_s, LSE = m + log2(sum_s w_s l_s).  Pair
 // k = j Hkv + kv covers concatenated tiles [f, f + n); units u0 (holding
-// tile f) to u1 (holding tile f + n - 1) wrote its blocks u0 + k .. u1 + k.
+// tile f) to u1 (holding tile f + n - 1) wrote its blocks u0 + k .. u1 + k.  In
+// split mode f and n count ranges and the blocks are f .. f + n - 1.
 // A workgroup merges 32 channels of a 32-row group: wave w takes the blocks
 // w, w + 4, ... in order, kCombineAhead of them loaded at once, and the four
 // waves' sums are added in wave order.  The launch is bound by the latency of
@@ -575,9 +576,9 @@ __global__ __launch_bounds__(256) void attn_combine(AttnArgs a) {
     return (int)(((x + 1) * a.st_units + a.st_total - 1) / a.st_total - 1);
   };
   const int64_t f = a.st_off[j] + (int64_t)kv * a.st_tiles[j];
-  const int u0 = unit_of(f);
-  const int nsp = unit_of(f + a.st_tiles[j] - 1) - u0 + 1;
-  const int64_t rg0 = ((int64_t)u0 + j * a.Hkv + kv) * a.part_groups + rgi;
+  const int u0 = a.split ? (int)f : unit_of(f);
+  const int nsp = a.split ? a.st_tiles[j] : unit_of(f + a.st_tiles[j] - 1) - u0 + 1;
+  const int64_t rg0 = ((int64_t)u0 + (a.split ? 0 : j * a.Hkv + kv)) * a.part_groups + rgi;
   const float4 *op = reinterpret_cast<const float4 *>(a.opart) + (rg0 * (D / 8) + 4 * db) * 64 + lane;
   const int64_t ostep = (int64_t)a.part_groups * (D / 8) * 64, mstep = (int64_t)a.part_groups * 32;
   const float2 *ml = reinterpret_cast<const float2 *>(a.mlpart) + rg0 * 32 + l32;
@@ -939,8 +940,8 @@ static void plain_pass(const AttnArgs &a, int n_list, hipStream_t s) {
   constexpr int rows = BM / KG;
   const int nqt = (a.C * (a.Hq / a.Hkv) + rows - 1) / rows;
   const dim3 grid(nqt * a.Hkv * n_list);
-  if (a.out != nullptr) hipLaunchKernelGGL((attn_fwd<D, KG, false, true>), grid, dim3(AT), 0, s, a, nqt);
-  else hipLaunchKernelGGL((attn_fwd<D, KG, false, false>), grid, dim3(AT), 0, s, a, nqt);
+  if (a.out != nullptr) hipLaunchKernelGGL((attn_fwd<D, 8, KG, PLAIN, true>), grid, dim3(AT), 0, s, a, nqt);
+  else hipLaunchKernelGGL((attn_fwd<D, 8, KG, PLAIN, false>), grid, dim3(AT), 0, s, a, nqt);
 }
 
 template <int D>
@@ -960,18 +961,25 @@ hipError_t launch_attention(const AttnArgs &a, int n_list, int head_dim, hipStre
 }
 
 template <int D>
-static hipError_t stream_pass(const AttnArgs &a, int n_list, hipStream_t s) {
+static hipError_t parted_pass(const AttnArgs &a, int n_list, hipStream_t s) {
   const int P = a.C * (a.Hq / a.Hkv);
-  const int nqt = (P + BM - 1) / BM;
-  hipLaunchKernelGGL((attn_fwd<D, 1, true, true>), dim3(a.st_units * nqt), dim3(AT), 0, s, a, nqt);
+  if (a.split) {
+    const dim3 grid(a.st_off[n_list]), block(256);
+    if (P <= 32) hipLaunchKernelGGL((attn_fwd<D, 4, 4, SPLIT, true>), grid, block, 0, s, a, 1);
+    else if (P <= 64) hipLaunchKernelGGL((attn_fwd<D, 4, 2, SPLIT, true>), grid, block, 0, s, a, 1);
+    else hipLaunchKernelGGL((attn_fwd<D, 4, 1, SPLIT, true>), grid, block, 0, s, a, 1);
+  } else {
+    const int nqt = (P + BM - 1) / BM;
+    hipLaunchKernelGGL((attn_fwd<D, 8, 1, STREAMED, true>), dim3(a.st_units * nqt), dim3(AT), 0, s, a, nqt);
+  }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(attn_combine<D>, dim3(a.part_groups * (D / 32), a.Hkv, n_list), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 
-hipError_t launch_attention_stream(const AttnArgs &a, int n_list, int head_dim, hipStream_t s) {
-  return head_dim == 64 ? stream_pass<64>(a, n_list, s) : stream_pass<128>(a, n_list, s);
+hipError_t launch_attention_parted(const AttnArgs &a, int n_list, int head_dim, hipStream_t s) {
+  return head_dim == 64 ? parted_pass<64>(a, n_list, s) : parted_pass<128>(a, n_list, s);
 }
 
 hipError_t launch_colsum(const ColsumArgs &a, int n_list, int max_T, int head_dim,

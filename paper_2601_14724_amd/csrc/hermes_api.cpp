@@ -28,7 +28,8 @@ struct Layout {
   int64_t lse_lstride, keys_lstride, kept_lstride, wpart_lstride, spart_lstride, normpart_lstride,
       newc_lstride;
   int64_t part_rows;        // stream-mode partial rows of queries and prompts
-  int64_t append_rows;      // and of appends, per layer (layers on different streams do not share them)
+  int64_t append_rows;      // and of appends, for each of append_slots streams (see append_slot)
+  int append_slots;
 };
 
 int max_budget(const hermes_config *c) {
@@ -84,9 +85,9 @@ int check_config(const hermes_config *c) {
 // Workspace layout of `c`; part_rows < 0 sizes the stream-mode partial state
 // for the most rows a short pass can write (256 for each of kStreamSlots
 // workgroups, and a block more for each (layer, KV head) pair), else for that
-// many rows.  `splits`: with each layer's room for appends cut along the keys
-// and sweeps cut along the query rows.
-Layout layout_of(const hermes_config *c, int64_t part_rows = -1, bool splits = true) {
+// many rows.  slots: streams that appends cut along the keys have room for;
+// with none there is no room for sweeps cut along the query rows either.
+Layout layout_of(const hermes_config *c, int64_t part_rows = -1, int slots = kAppendSlots) {
   Layout s;
   s.lse_lstride = (int64_t)c->n_q_heads * c->max_chunk;
   s.keys_lstride = c->max_cap;
@@ -109,7 +110,7 @@ Layout layout_of(const hermes_config *c, int64_t part_rows = -1, bool splits = t
   s.newc = off;
   off = round_up(off + sizeof(int32_t) * 3 * (size_t)s.newc_lstride * c->n_layers);
   s.wpart_lstride = (int64_t)c->n_kv_heads * c->max_cap;
-  if (splits && s.wpart_lstride < kMassPartials) s.wpart_lstride = kMassPartials;
+  if (slots > 0 && s.wpart_lstride < kMassPartials) s.wpart_lstride = kMassPartials;
   s.wpart = off;
   off = round_up(off + sizeof(double) * (size_t)s.wpart_lstride * c->n_layers);
   // summary token: fp64 block sums, staged bf16 rows and their metadata
@@ -136,13 +137,14 @@ Layout layout_of(const hermes_config *c, int64_t part_rows = -1, bool splits = t
   s.mlpart = off;
   off = round_up(off + sizeof(float) * 2 * (size_t)s.part_rows);
   // and of appends: at most one block for two key tiles, and one for each pair
-  const int64_t blocks = (int64_t)c->n_kv_heads * (((int64_t)c->max_cap + 63) / 64 / 2 + 1);
+  const int64_t blocks = (int64_t)c->n_layers * c->n_kv_heads * (((int64_t)c->max_cap + 63) / 64 / 2 + 1);
   const int64_t rows = (c->max_chunk * G + 31) / 32 * 32;
-  s.append_rows = !splits ? 0 : rows > kAppendPartRows / blocks ? kAppendPartRows : blocks * rows;
+  s.append_slots = slots;
+  s.append_rows = slots == 0 ? 0 : rows > kAppendPartRows / blocks ? kAppendPartRows : blocks * rows;
   s.aopart = off;
-  off = round_up(off + sizeof(float) * (size_t)s.append_rows * c->head_dim * c->n_layers);
+  off = round_up(off + sizeof(float) * (size_t)s.append_rows * c->head_dim * slots);
   s.amlpart = off;
-  off = round_up(off + sizeof(float) * 2 * (size_t)s.append_rows * c->n_layers);
+  off = round_up(off + sizeof(float) * 2 * (size_t)s.append_rows * slots);
   s.total = off;
   return s;
 }
@@ -152,30 +154,35 @@ Layout layout_of(const hermes_config *c, int64_t part_rows = -1, bool splits = t
 // as the rest leaves (possibly none: short passes then run the plain kernel).
 // false if even that exceeds `limit`.
 bool layout_within(const hermes_config *c, size_t limit, Layout *out) {
-  for (const bool splits : {true, false}) {
-    const Layout full = layout_of(c, -1, splits);
+  for (int slots = kAppendSlots; slots >= 0; --slots) {
+    const Layout full = layout_of(c, -1, slots);
     if (full.total <= limit) {
       *out = full;
       return true;
     }
   }
-  const Layout none = layout_of(c, 0, false);
+  const Layout none = layout_of(c, 0, 0);
   if (none.total > limit) return false;
   int64_t rows = (int64_t)((limit - none.total) / (sizeof(float) * (c->head_dim + 2)));
   // the two regions are rounded up separately: back off until it fits
-  while (rows > 0 && layout_of(c, rows, false).total > limit) rows = rows > 64 ? rows - 64 : 0;
-  *out = layout_of(c, rows, false);
+  while (rows > 0 && layout_of(c, rows, 0).total > limit) rows = rows > 64 ? rows - 64 : 0;
+  *out = layout_of(c, rows, 0);
   return true;
 }
 
 // How a pass of n_rows rows per entry over caches of at.T0[j] tokens is cut
-// into workgroups, with room for part_rows partial rows.  Three ways, of which
+// into workgroups, with room for part_rows partial rows.  Four ways, of which
 // the cheapest by the estimate below is taken:
 //  - the plain kernel with one key group: a workgroup per (entry, KV head, 256
 //    packed rows) over its whole sequence.  Few of them leave CUs idle, and
 //    the entry with the longest cache sets the time;
 //  - with 2, 4 or 8 key groups: that many times the workgroups, each of a
 //    2nd, 4th or 8th of the rows and steps, whose K/V tiles serve fewer rows;
+//  - split mode, for up to kSplitRows packed rows: each pair's keys in ranges of
+//    equal length, at most two workgroups a CU, and the combine launch.  One
+//    row on 2048..6144 tokens of 28 layers takes 42 us (50 in stream mode, 57
+//    with eight key groups), 16 rows 55 (79); a cache that eight key groups
+//    walk in a step stays with them (256 tokens: 5.5 us, 7.5 split);
 //  - stream mode: the concatenated key tiles of all pairs in U equal ranges, U
 //    units of a workgroup per 256 rows, so every CU gets the same number of
 //    tiles; it pays a partial write and read per (unit, pair) touched and the
@@ -196,6 +203,7 @@ void attention_plan(AttnArgs &at, int n_rows, int G, int Hkv, int n_list, int D,
   const int64_t P = (int64_t)n_rows * G;
   const int64_t pairs = (int64_t)n_list * Hkv;
   at.key_groups = 1;
+  at.split = 0;
   at.st_units = 0;
   at.st_entries = n_list;
   at.part_groups = (int32_t)((P + 31) / 32);
@@ -224,6 +232,31 @@ void attention_plan(AttnArgs &at, int n_rows, int G, int Hkv, int n_list, int D,
     }
   }
   if (total > INT32_MAX / 2) return;
+  if (P <= kSplitRows) {
+    const int keys = P <= 32 ? 128 : 64;    // of a step
+    auto steps_of = [&](int j) { return (at.T0[j] + keys - 1) / keys + (n_rows + keys - 1) / keys; };
+    int64_t all = 0, ranges = 0;
+    for (int j = 0; j < n_list; ++j) all += (int64_t)Hkv * steps_of(j);
+    // the shortest ranges that are one round (two workgroups a CU)
+    int64_t L = (all + 2 * kStreamSlots - 1) / (2 * kStreamSlots);
+    for (;; L += 1 + L / 16) {
+      ranges = 0;
+      for (int j = 0; j < n_list; ++j) ranges += Hkv * ((steps_of(j) + L - 1) / L);
+      if (ranges <= 2 * kStreamSlots || ranges <= pairs) break;
+    }
+    if (6.0 + 1.2 * (double)L < best && ranges * 32 * at.part_groups <= part_rows) {
+      int64_t off = 0;
+      for (int j = 0; j < n_list; ++j) {
+        at.st_tiles[j] = (int32_t)((steps_of(j) + L - 1) / L);
+        at.st_off[j] = (int32_t)off;
+        off += (int64_t)Hkv * at.st_tiles[j];
+      }
+      at.st_off[n_list] = (int32_t)off;
+      at.split = 1;
+      at.st_units = (int32_t)L;
+      return;
+    }
+  }
   at.st_off[n_list] = (int32_t)total;
   at.st_total = (int32_t)total;
   const int64_t nqt = (P + kAttnRowsPerBlock - 1) / kAttnRowsPerBlock;
@@ -325,6 +358,33 @@ struct hermes_ctx {
   int static_dev = -1;  // device whose static scratch is the workspace (-1: the caller's)
   std::vector<EventPair> used[HERMES_K_COUNT];
   std::vector<EventPair> pool;
+  // Partial rows of appends belong to the stream that first took the slot, for
+  // the context's life: calls on one stream follow each other, and layers
+  // appended on different streams never share them (streams beyond the slots,
+  // the per-thread default stream, whose handle names a stream of each thread,
+  // and captured calls, which may be replayed on any stream, run without).
+  hipStream_t slot_stream[kAppendSlots] = {};
+  bool slot_taken[kAppendSlots] = {};
+
+  int append_slot(hipStream_t s) const {
+    if (s == hipStreamPerThread) return -1;
+    for (int i = 0; i < lay.append_slots; ++i)
+      if (!slot_taken[i] || slot_stream[i] == s) return i;
+    return -1;
+  }
+  bool take_slot(int i, hipStream_t s) {
+    if (s != nullptr) {
+      hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+      if (hipStreamIsCapturing(s, &status) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+      }
+      if (status != hipStreamCaptureStatusNone) return false;
+    }
+    slot_taken[i] = true;
+    slot_stream[i] = s;
+    return true;
+  }
 
   int prof_begin(int id, hipStream_t s, EventPair *ep) {
     if (!prof) return HERMES_OK;
@@ -797,18 +857,18 @@ static int append_impl(hermes_ctx *ctx, int32_t layer, const void *q, const void
   }
 
   {
-    // all layers' partial rows for a call on all of them, else the layer's own
-    const int64_t rows = ctx->lay.append_rows;
-    const int64_t first = layer == HERMES_ALL_LAYERS ? 0 : layer * rows;
-    attention_plan(at, n_new, ctx->Hq / ctx->Hkv, ctx->Hkv, (int)list.size(), ctx->D,
-                rows * (int64_t)list.size());
+    const int n = (int)list.size(), G = ctx->Hq / ctx->Hkv;
+    const int slot = ctx->append_slot(s);
+    attention_plan(at, n_new, G, ctx->Hkv, n, ctx->D, slot < 0 ? 0 : ctx->lay.append_rows);
+    if (at.st_units > 0 && !ctx->take_slot(slot, s)) attention_plan(at, n_new, G, ctx->Hkv, n, ctx->D, 0);
+    const int64_t first = slot < 0 ? 0 : slot * ctx->lay.append_rows;
     at.opart = reinterpret_cast<float *>(ctx->ws + ctx->lay.aopart) + first * ctx->D;
     at.mlpart = reinterpret_cast<float *>(ctx->ws + ctx->lay.amlpart) + first * 2;
   }
   int rc = ctx->run(HERMES_K_APPEND, s, [&] { return launch_append(ap, s); });
   if (rc != HERMES_OK) return rc;
   rc = ctx->run(HERMES_K_ATTN, s, [&] {
-    return at.st_units > 0 ? launch_attention_stream(at, (int)list.size(), ctx->D, s)
+    return at.st_units > 0 ? launch_attention_parted(at, (int)list.size(), ctx->D, s)
                            : launch_attention(at, (int)list.size(), ctx->D, s);
   });
   if (rc != HERMES_OK) return rc;
@@ -926,7 +986,7 @@ int hermes_guidance_score(hermes_ctx *ctx, int32_t layer, const void *q, const v
   at.opart = reinterpret_cast<float *>(ctx->ws + ctx->lay.opart);
   at.mlpart = reinterpret_cast<float *>(ctx->ws + ctx->lay.mlpart);
   const int rc = ctx->run(HERMES_K_GUIDE, s, [&] {
-    hipError_t e = at.st_units > 0 ? launch_attention_stream(at, n, ctx->D, s)
+    hipError_t e = at.st_units > 0 ? launch_attention_parted(at, n, ctx->D, s)
                                    : launch_attention(at, n, ctx->D, s);
     if (e != hipSuccess) return e;
     return launch_colsum(cs, n, max_T, ctx->D, s);
@@ -1172,7 +1232,7 @@ int hermes_query_attend(hermes_ctx *ctx, int32_t layer, const void *q, const voi
   at.opart = reinterpret_cast<float *>(ctx->ws + ctx->lay.opart);
   at.mlpart = reinterpret_cast<float *>(ctx->ws + ctx->lay.mlpart);
   return ctx->run(HERMES_K_QUERY, s, [&] {
-    return at.st_units > 0 ? launch_attention_stream(at, n, ctx->D, s)
+    return at.st_units > 0 ? launch_attention_parted(at, n, ctx->D, s)
                            : launch_attention(at, n, ctx->D, s);
   });
 }

@@ -59,8 +59,12 @@ struct AttnArgs {
   // nqt workgroups each.  Unit u writes the unnormalised O, running maximum
   // and row sum (fp32) of each pair k it touches to opart / mlpart block u + k
   // of part_groups 32-row groups; a combine kernel merges each pair's blocks.
+  // Split mode (`split`): pair k's steps (of 128 keys, or 64 with more than 32
+  // packed rows) are cut into st_tiles[j] ranges of st_units steps, entry j's
+  // ranges from st_off[j]; range x writes block x.
   // st_units = 0: the plain kernel, one workgroup per (entry, KV head, query
   // tile).
+  int32_t split;
   int32_t st_units, st_total, st_entries, part_groups;
   int32_t key_groups;       // plain kernel: 1, 2, 4 or 8 groups of waves that share the keys (256 / key_groups rows a workgroup)
   int32_t st_off[kMaxLayers + 1];
@@ -228,7 +232,7 @@ void static_workspace_release(int device);
 
 // Launchers (return the hipError_t of the launch).
 hipError_t launch_attention(const AttnArgs &a, int n_list, int head_dim, hipStream_t s);
-hipError_t launch_attention_stream(const AttnArgs &a, int n_list, int head_dim, hipStream_t s);
+hipError_t launch_attention_parted(const AttnArgs &a, int n_list, int head_dim, hipStream_t s);
 hipError_t launch_colsum(const ColsumArgs &a, int n_list, int max_T, int head_dim,
                          hipStream_t s);
 hipError_t launch_select(const SelectArgs &a, hipStream_t s);
@@ -265,8 +269,10 @@ constexpr int kMassSplitMax = 32;       // ranges a sweep's query rows are cut i
 constexpr int64_t kMassPartials = 1024 * 256;   // fp64 partials a layer keeps for them
 constexpr int kSummaryRows = 128;        // candidates per workgroup of the summary sums
 constexpr int kSplitMaxTokens = 64;      // rows of a query or prompt that the workspace holds the stream state of
-constexpr int64_t kAppendPartRows = 81920;   // partial rows of stream-mode appends a layer keeps at most
+constexpr int64_t kAppendPartRows = 131072;  // partial rows of appends at most (68 MB at head size 128),
+constexpr int kAppendSlots = 2;              // for each of this many streams
 constexpr int kStreamSlots = 256;        // resident attention workgroups (one per CU)
+constexpr int kSplitRows = 128;          // packed rows of a split-mode workgroup at most
 constexpr int kNormBlock = 256;         // candidates per fp64 partial of the score normaliser
 
 }  // namespace hermes

@@ -1,6 +1,5 @@
 """The ways an attention pass is cut into workgroups, against the fp64 oracle:
-one, two, four and eight key groups and stream mode, one layer at a time, at
-sizes where a cut can go wrong (a cache that ends inside a tile or on its edge,
+one, two, four and eight key groups, stream mode and split mode, at sizes where a cut can go wrong (a cache that ends inside a tile or on its edge,
 fewer tiles than key groups, a last query tile of a few rows), and the mass
 sweep cut along the query rows.  The bars are the parity suite's: outputs to
 bf16, W to 1e-3."""
@@ -29,6 +28,43 @@ SHAPES = [
     ("stream_d128", 28, 4, 128, 6144, 196),
     ("stream_g9", 9, 1, 128, 2001, 64),
 ]
+
+
+QUERIES = [
+    # name, layers, Hq, Hkv, d, lengths of the caches, rows (packed rows 1 .. 128: split mode)
+    ("one_row_d64", 2, 2, 2, 64, (129, 1000), 1),
+    ("one_row_of_seven_heads", 3, 28, 4, 128, (700, 2048, 2049), 1),
+    ("32_packed_rows", 2, 8, 2, 128, (1, 1500), 8),
+    ("33_packed_rows", 2, 33, 3, 64, (640, 3000), 3),
+    ("64_packed_rows", 2, 8, 1, 128, (1023, 2500), 8),
+    ("65_packed_rows", 2, 13, 1, 128, (900, 2047), 5),
+    ("128_packed_rows", 2, 4, 4, 64, (500, 1601), 128),
+    ("129_packed_rows", 2, 3, 1, 128, (900, 4000), 43),
+]
+
+
+@pytest.mark.parametrize("name,L,Hq,Hkv,d,lens,rows", QUERIES)
+def test_query_cuts_match_oracle(name, L, Hq, Hkv, d, lens, rows):
+    """Queries over caches of unequal lengths, all layers in one call and one
+    by one."""
+    from paper_2601_14724_amd import hermes as H
+    say(f"[cuts] query {name}: {Hq}/{Hkv} d={d} lens={lens} rows={rows}")
+    init, host = [], []
+    for l, n in enumerate(lens):
+        wl = wk.custom(name, 400 + rows, L, Hq, Hkv, d, n, 1, (n,) * L, query_len=rows, anchor_period=29)
+        c, q = wk.gen_cache(wl, l), wk.gen_query(wl, l)
+        host.append((c, q))
+        init.append((streaming.bf16_tensor(c["k"], "cuda"), streaming.bf16_tensor(c["v"], "cuda"),
+                     torch.from_numpy(c["pos"]).cuda()))
+    kv = H.HermesKV(L, Hq, Hkv, d, [max(lens)] * L, rows, init=init)
+    t = {k: streaming.bf16_tensor(np.stack([q[k] for _, q in host]), "cuda") for k in ("q", "k", "v")}
+    both = kv.query(t["q"], t["k"], t["v"])
+    for l, (c, q) in enumerate(host):
+        o, _ = orc.chunk_attention(f64(q["q"]), f64(c["k"]), f64(c["v"]), f64(q["k"]), f64(q["v"]), want_w=False)
+        check_o(both[l].float().cpu().numpy(), o, f"[cuts] query {name} layer {l} of {L}")
+        alone = kv.query(t["q"][l], t["k"][l], t["v"][l], layer=l)
+        check_o(alone.float().cpu().numpy(), o, f"[cuts] query {name} layer {l} alone")
+    kv.close()
 
 
 @pytest.mark.parametrize("name,Hq,Hkv,d,T0,C", SHAPES)
