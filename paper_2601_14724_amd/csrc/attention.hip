@@ -73,6 +73,39 @@ __device__ __forceinline__ int xcd_remap(int i, int n) {
   return x < r ? x * (q + 1) + k : r * (q + 1) + (x - r) * q + k;
 }
 
+// Appends: this workgroup's share (the id-th of n) of the copy of the new K/V
+// rows and positions into the caches.  Nothing in the launch reads those rows
+// of the caches, so the copy rides with it: a launch of its own took 4-5 us a
+// layer, 20 us over 28 layers of 784 rows.  It comes last in the kernel, where
+// a pass that copies nothing does not wait for the test (in front it cost a
+// query 0.5 us).
+__device__ __forceinline__ void copy_share(const AttnArgs &a, int D, int id, int n) {
+  const int entries = a.st_entries, threads = blockDim.x;
+  const int per = a.C * (a.Hkv * D / 8);    // 16-byte pieces of an entry's K (or V)
+  // every entry has its own workgroups, or a workgroup has several entries
+  const int first = n < entries ? id : id % entries, step = min(n, entries);
+  const int share = n < entries ? 0 : id / entries;
+  const int shares = n < entries ? 1 : (n - first + entries - 1) / entries;
+  for (int j = first; j < entries; j += step) {
+    const LayerTable &L = a.tab[a.layer_id[j]];
+    const int cur = a.cur[j], T0 = a.T0[j];
+    const uint16_t *kn = a.kn + a.slot[j] * a.kv_lstride, *vn = a.vn + a.slot[j] * a.kv_lstride;
+    uint16_t *kd = L.k[cur] + (int64_t)T0 * a.Hkv * D, *vd = L.v[cur] + (int64_t)T0 * a.Hkv * D;
+    for (int x = share * threads + threadIdx.x; x < per; x += shares * threads) {
+      *reinterpret_cast<uint4 *>(kd + 8 * (int64_t)x) = gload16(kn + 8 * (int64_t)x);
+      *reinterpret_cast<uint4 *>(vd + 8 * (int64_t)x) = gload16(vn + 8 * (int64_t)x);
+      if (x < a.C) {   // (an entry has more pieces than rows)
+        L.pos[cur][T0 + x] = a.pos[x];
+        if (L.rpos[cur] != nullptr) L.rpos[cur][T0 + x] = a.rope_pos != nullptr ? a.rope_pos[x] : a.pos[x];
+        if (L.rpos_h[cur] != nullptr) {   // M-RoPE: h and w beside t
+          L.rpos_h[cur][T0 + x] = a.rope_h[x];
+          L.rpos_w[cur][T0 + x] = a.rope_w[x];
+        }
+      }
+    }
+  }
+}
+
 // STREAM: passes whose (entry, KV head, query tile) workgroups would not fill
 // the CUs (one layer's chunk, queries, guidance prompts).  The key tiles of
 // every (entry, KV head) pair, concatenated in pair order (pair k = j Hkv +
@@ -117,7 +150,6 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 1 : 2) void attn_fwd(AttnArgs a,
   const int P = C * G;
   const int p0 = qtile * BM;
   if (p0 >= P) return;
-
   const int tid = threadIdx.x % GT, wave = tid >> 6, lane = tid & 63;
   const int kg = KG == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / GT);
   const int half = lane >> 5, l32 = lane & 31;
@@ -550,6 +582,7 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 1 : 2) void attn_fwd(AttnArgs a,
     if (row_ok && a.lse != nullptr && kg == 0 && half == 0)
       a.lse[a.layer_id[j] * a.lse_lstride + (int64_t)kv * P + prow] = mt + log2f(lsum);
   }
+  if (a.pos != nullptr) copy_share(a, D, lin, gridDim.x);
 }
 
 // Merge of a pair's partial blocks: m = max_s m_s, w_s = 2^(m_s - m),

@@ -1,5 +1,4 @@
-// Data movement kernels for gfx950: the append copy of a chunk's K/V rows
-// into the cache tail, and the order-preserving gather of kept rows
+// Data movement kernel for gfx950: the order-preserving gather of kept rows
 // (Sec. 3.2: K_l = K_l[I_l], V_l = V_l[I_l]) into the other buffer of each
 // layer's ping-pong pair.  Rows are token-major (Hkv * d bf16 per row), moved
 // in 16-byte pieces so every wave issues fully coalesced 1 KiB transactions.
@@ -9,33 +8,6 @@ namespace hermes {
 namespace {
 
 constexpr int NT = 256;
-
-__global__ __launch_bounds__(NT) void append_rows(AppendArgs a) {
-  const int jj = blockIdx.y;
-  const int l = a.layer_id[jj];
-  const LayerTable &L = a.tab[l];
-  const int cur = a.cur[jj];
-  const int T0 = a.T0[jj];
-  const int pieces = a.row_elems / 8;
-  const int total = a.C * pieces;
-  const uint16_t *kn = a.kn + a.slot[jj] * a.kv_lstride;
-  const uint16_t *vn = a.vn + a.slot[jj] * a.kv_lstride;
-  uint16_t *kd = L.k[cur] + (int64_t)T0 * a.row_elems;
-  uint16_t *vd = L.v[cur] + (int64_t)T0 * a.row_elems;
-  for (int e = blockIdx.x * NT + threadIdx.x; e < total; e += gridDim.x * NT) {
-    const int64_t off = (int64_t)e * 8;
-    *reinterpret_cast<uint4 *>(kd + off) = *reinterpret_cast<const uint4 *>(kn + off);
-    *reinterpret_cast<uint4 *>(vd + off) = *reinterpret_cast<const uint4 *>(vn + off);
-  }
-  for (int e = blockIdx.x * NT + threadIdx.x; e < a.C; e += gridDim.x * NT) {
-    L.pos[cur][T0 + e] = a.pos[e];
-    if (L.rpos[cur] != nullptr) L.rpos[cur][T0 + e] = a.rope_pos != nullptr ? a.rope_pos[e] : a.pos[e];
-    if (L.rpos_h[cur] != nullptr) {   // M-RoPE: h and w beside t
-      L.rpos_h[cur][T0 + e] = a.rope_h[e];
-      L.rpos_w[cur][T0 + e] = a.rope_w[e];
-    }
-  }
-}
 
 __global__ __launch_bounds__(NT) void gather_rows(GatherArgs a) {
   const int jj = blockIdx.y;
@@ -72,13 +44,6 @@ __global__ __launch_bounds__(NT) void gather_rows(GatherArgs a) {
 }
 
 }  // namespace
-
-hipError_t launch_append(const AppendArgs &a, hipStream_t s) {
-  const int pieces = a.row_elems / 8;
-  const int blocks = (a.C * pieces + NT - 1) / NT;
-  hipLaunchKernelGGL(append_rows, dim3(blocks, a.n_list), dim3(NT), 0, s, a);
-  return hipGetLastError();
-}
 
 hipError_t launch_gather(const GatherArgs &a, hipStream_t s) {
   const int pieces = a.row_elems / 8;

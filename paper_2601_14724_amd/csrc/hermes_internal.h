@@ -40,12 +40,17 @@ struct LayerTable {
 // Chunk (or query) attention: launch entry j covers layer layer_id[j], reads
 // cached rows [0, T0[j]) of buffer cur[j] and new rows from the stacked inputs
 // at slot j (stride *_lstride elements), writes out (if non-null) and lse (if
-// non-null).
+// non-null).  n_list entries.
 struct AttnArgs {
   const LayerTable *tab;
   const uint16_t *q, *kn, *vn;
   uint16_t *out;
   float *lse;               // [n_layers][Hkv][C*G] log2-domain row LSE, or null
+  // Appends (pos non-null): the launch also copies the new rows and their
+  // positions into rows [T0, T0 + C) of the current buffer.
+  const int32_t *pos;
+  const int32_t *rope_pos;  // RoPE positions of the new rows (null: = pos); t with M-RoPE
+  const int32_t *rope_h, *rope_w;   // M-RoPE h and w of the new rows (null unless three axes)
   int64_t q_lstride, kv_lstride, lse_lstride;
   int32_t Hq, Hkv, C;
   float scale_log2;         // sm_scale * log2(e)
@@ -65,7 +70,7 @@ struct AttnArgs {
   // st_units = 0: the plain kernel, one workgroup per (entry, KV head, query
   // tile).
   int32_t split;
-  int32_t st_units, st_total, st_entries, part_groups;
+  int32_t st_units, st_total, st_entries, part_groups;   // (st_entries: the launch's entries, in every mode)
   int32_t key_groups;       // plain kernel: 1, 2, 4 or 8 groups of waves that share the keys (256 / key_groups rows a workgroup)
   int32_t st_off[kMaxLayers + 1];
   int32_t st_tiles[kMaxLayers];
@@ -205,22 +210,6 @@ struct RankArgs {
   int8_t has_sum[kMaxLayers];
 };
 
-// Append copy: new K/V rows and positions into rows [T0, T0 + C) of the
-// current buffer of each listed layer.
-struct AppendArgs {
-  const LayerTable *tab;
-  const uint16_t *kn, *vn;
-  const int32_t *pos;
-  const int32_t *rope_pos;  // RoPE positions of the new rows (null: = pos); t with M-RoPE
-  const int32_t *rope_h, *rope_w;   // M-RoPE h and w of the new rows (null unless three axes)
-  int64_t kv_lstride;
-  int32_t row_elems, C, n_list;
-  int32_t T0[kMaxLayers];
-  int8_t layer_id[kMaxLayers];
-  int8_t slot[kMaxLayers];
-  int8_t cur[kMaxLayers];
-};
-
 // Device scratch of the no-allocation context entry point (scratch.hip):
 // kStaticWorkspaceBytes per GPU.  acquire looks up the array's address on the
 // current device (once per device) and marks it owned: HERMES_ESTATE while
@@ -255,7 +244,6 @@ struct CheckArgs {
 
 hipError_t launch_check(const CheckArgs &a, hipStream_t s);
 hipError_t launch_gather(const GatherArgs &a, hipStream_t s);
-hipError_t launch_append(const AppendArgs &a, hipStream_t s);
 hipError_t launch_topk(const float *keys, int n, int k, int32_t *out, hipStream_t s);
 hipError_t launch_summary(const SummaryArgs &a, int max_T, hipStream_t s);
 hipError_t launch_decide(const DecideArgs &a, hipStream_t s);
