@@ -127,12 +127,14 @@ __device__ __forceinline__ void copy_share(const AttnArgs &a, int D, int id, int
 // walks a KG-th of the keys: what a launch of few rows needs to fill the CUs,
 // for KG times the K/V staging per row.
 //
-// SPLIT: passes whose packed rows fit one workgroup (a few tokens: decoding).
-// No two workgroups share a key, so the pass is bound by HBM, and by latency
-// where a CU has little to read.  Each pair's steps are cut into st_tiles[j]
-// ranges of st_units steps, one workgroup each (entry j's from st_off[j]), of
-// four waves so that two of them share a CU: one's start and end hide behind
-// the other's loads.  Each writes its partial state as in stream mode.
+// SPLIT: each pair's steps are cut into st_tiles[j] ranges of st_units steps
+// (entry j's from st_off[j]), each nqt workgroups with consecutive ids, one for
+// each query tile.  Each writes its partial state as in stream mode.  A pass of
+// a few rows then fills the CUs with less partial state than stream mode's
+// 256-row workgroups write.  Where the packed rows fit one workgroup (a few
+// tokens: decoding) no two workgroups share a key, so the pass is bound by HBM,
+// and by latency where a CU has little to read: it takes workgroups of four
+// waves, two a CU, so that one's start and end hide behind the other's loads.
 enum { PLAIN = 0, STREAMED = 1, SPLIT = 2 };
 template <int D, int NW, int KG, int MODE, bool WRITE_O>
 __global__ __launch_bounds__(64 * NW, NW == 8 ? 1 : 2) void attn_fwd(AttnArgs a, int nqt) {
@@ -143,8 +145,10 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 1 : 2) void attn_fwd(AttnArgs a,
   constexpr int SUB = BN / 32;
   constexpr int NBUF = RG == 1 ? 1 : 2;     // (a tile of one wave needs no second buffer)
   constexpr int GT = 64 * RG;               // threads of a key group
-  const int lin = MODE == SPLIT ? (int)blockIdx.x : xcd_remap(blockIdx.x, gridDim.x);
+  constexpr bool ONE_TILE = MODE == SPLIT && NW == 4;   // (nqt is 1, no K/V tile is shared)
+  const int lin = ONE_TILE ? (int)blockIdx.x : xcd_remap(blockIdx.x, gridDim.x);
   const int qtile = lin % nqt;
+  const int unit = ONE_TILE ? lin : lin / nqt;
   const int C = a.C, Hq = a.Hq, Hkv = a.Hkv;
   const int G = Hq / Hkv;
   const int P = C * G;
@@ -180,7 +184,7 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 1 : 2) void attn_fwd(AttnArgs a,
   // STREAM: this unit's tile range over the concatenated pairs
   int x_lo = 0, x_hi = 0, u = 0;
   if constexpr (STREAM) {
-    u = lin / nqt;
+    u = unit;
     // (the 64-bit divisions run on vector registers: back to scalar ones, so
     // that tile indices, loop bounds and buffer descriptors stay scalar)
     x_lo = __builtin_amdgcn_readfirstlane((int)((int64_t)u * a.st_total / a.st_units));
@@ -228,7 +232,7 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 1 : 2) void attn_fwd(AttnArgs a,
   };
   if constexpr (MODE != PLAIN) {
     int jj, kvv;
-    locate(STREAM ? x_lo : lin, jj, kvv, first);
+    locate(STREAM ? x_lo : unit, jj, kvv, first);
     enter(jj, kvv);
   } else {
     enter(lin / (nqt * Hkv), (lin / nqt) % Hkv);
@@ -566,8 +570,8 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 1 : 2) void attn_fwd(AttnArgs a,
       }
     } while (x < x_hi);
   } else if constexpr (MODE == SPLIT) {
-    walk((lin - first) * a.st_units, a.st_units);
-    flush(lin);
+    walk((unit - first) * a.st_units, a.st_units);
+    flush(unit);
   } else {
     walk(0, ntiles);
     uint16_t *orow = a.out + a.slot[j] * a.q_lstride + ((int64_t)r * Hq + kv * G + g) * D + 4 * half;
@@ -996,7 +1000,13 @@ hipError_t launch_attention(const AttnArgs &a, int n_list, int head_dim, hipStre
 template <int D>
 static hipError_t parted_pass(const AttnArgs &a, int n_list, hipStream_t s) {
   const int P = a.C * (a.Hq / a.Hkv);
-  if (a.split) {
+  if (a.split == 2) {
+    const int nqt = (P + BM / a.key_groups - 1) / (BM / a.key_groups);
+    const dim3 grid(a.st_off[n_list] * nqt);
+    if (a.key_groups == 2) hipLaunchKernelGGL((attn_fwd<D, 8, 2, SPLIT, true>), grid, dim3(AT), 0, s, a, nqt);
+    else if (a.key_groups == 4) hipLaunchKernelGGL((attn_fwd<D, 8, 4, SPLIT, true>), grid, dim3(AT), 0, s, a, nqt);
+    else hipLaunchKernelGGL((attn_fwd<D, 8, 8, SPLIT, true>), grid, dim3(AT), 0, s, a, nqt);
+  } else if (a.split == 1) {
     const dim3 grid(a.st_off[n_list]), block(256);
     if (P <= 32) hipLaunchKernelGGL((attn_fwd<D, 4, 4, SPLIT, true>), grid, block, 0, s, a, 1);
     else if (P <= 64) hipLaunchKernelGGL((attn_fwd<D, 4, 2, SPLIT, true>), grid, block, 0, s, a, 1);

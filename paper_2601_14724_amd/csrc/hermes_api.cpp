@@ -136,8 +136,8 @@ Layout layout_of(const hermes_config *c, int64_t part_rows = -1, int slots = kAp
   off = round_up(off + sizeof(float) * (size_t)s.part_rows * c->head_dim);
   s.mlpart = off;
   off = round_up(off + sizeof(float) * 2 * (size_t)s.part_rows);
-  // and of appends: at most one block for two key tiles, and one for each pair
-  const int64_t blocks = (int64_t)c->n_layers * c->n_kv_heads * (((int64_t)c->max_cap + 63) / 64 / 2 + 1);
+  // and of appends: at most one block for two key tiles, and two more a pair
+  const int64_t blocks = (int64_t)c->n_layers * c->n_kv_heads * (((int64_t)c->max_cap + 63) / 64 / 2 + 2);
   const int64_t rows = (c->max_chunk * G + 31) / 32 * 32;
   s.append_slots = slots;
   s.append_rows = slots == 0 ? 0 : rows > kAppendPartRows / blocks ? kAppendPartRows : blocks * rows;
@@ -178,15 +178,12 @@ bool layout_within(const hermes_config *c, size_t limit, Layout *out) {
 //    the entry with the longest cache sets the time;
 //  - with 2, 4 or 8 key groups: that many times the workgroups, each of a
 //    2nd, 4th or 8th of the rows and steps, whose K/V tiles serve fewer rows;
-//  - split mode, for up to kSplitRows packed rows: each pair's keys in ranges of
-//    equal length, at most two workgroups a CU, and the combine launch.  One
-//    row on 2048..6144 tokens of 28 layers takes 42 us (50 in stream mode, 57
-//    with eight key groups), 16 rows 55 (79); a cache that eight key groups
-//    walk in a step stays with them (256 tokens: 5.5 us, 7.5 split);
+//  - split mode: each pair's keys in ranges of equal length, partial states
+//    and the combine launch.  Up to kSplitRows packed rows take workgroups of
+//    four waves, at most two a CU; more rows take 2, 4 or 8 key groups, one a CU;
 //  - stream mode: the concatenated key tiles of all pairs in U equal ranges, U
 //    units of a workgroup per 256 rows, so every CU gets the same number of
-//    tiles; it pays a partial write and read per (unit, pair) touched and the
-//    combine launch.
+//    tiles whatever the pairs' lengths, for more partial state.
 // Costs are in steps of the plain kernel (a 64-key tile of 256 rows: 1.42 us
 // at head size 128 while CUs are idle, 1.8 us with all busy).  A launch takes
 // one step of a round of kStreamSlots workgroups after the other, each round
@@ -194,11 +191,14 @@ bool layout_within(const hermes_config *c, size_t limit, Layout *out) {
 // a step over 2 / 4 / 8 of them costs 1.09-1.17 / 1.37-1.65 / 1.7-2.1 (28
 // layers of 8976 tokens; one layer), a stream step 1.1 (head size 128) or 1.25
 // (64), and the partials' traffic 0.27 a MB on top of 4 for the combine.  One
-// layer, us, key groups 1 / 2 / 4 / 8 and stream mode: 784 rows on 8192 tokens
-// 200 / 119 / 173 / 163 / 110, 784 on 1568 63 / 41 / 55 / 57 / 46, 196 on 6144
-// 141 / 83 / 60 / 41 / 31 (28 query heads, 4 KV heads of 128); 784 on 4096 84 /
-// 48 / 33 / 35 / 34, 196 on 1024 24 / 17 / 10 / 7 / 12 (14 and 2 of 64).
-// Fills key_groups and the st_* fields (st_units = 0 for the plain kernel).
+// layer, us, key groups 1 / 2 / 4 / 8, stream, split where it is taken: 784
+// rows on 8192 tokens 200 / 119 / 173 / 163 / 110, 784 on 1568 63 / 41 / 55 /
+// 57 / 46, 196 on 6144 141 / 83 / 60 / 41 / 33 / 32, 64 on 4096 95 / 58 / 45 /
+// 28 / 24 / 18 (28 query heads, 4 KV heads of 128); 784 on 4096 84 / 48 / 33 /
+// 35 / 34, 196 on 1024 24 / 17 / 10 / 7 / 12 (14 and 2 of 64).  28 layers of
+// 2048..6144 tokens: one row 57 with eight key groups, 50 stream, 43 split; 16
+// rows 79 stream, 63 split; 64 rows 175 with one key group, 152 stream.
+// Fills key_groups, split and the st_* fields (st_units = 0: the plain kernel).
 void attention_plan(AttnArgs &at, int n_rows, int G, int Hkv, int n_list, int D, int64_t part_rows) {
   const int64_t P = (int64_t)n_rows * G;
   const int64_t pairs = (int64_t)n_list * Hkv;
@@ -232,49 +232,79 @@ void attention_plan(AttnArgs &at, int n_rows, int G, int Hkv, int n_list, int D,
     }
   }
   if (total > INT32_MAX / 2) return;
-  if (P <= kSplitRows) {
-    const int keys = P <= 32 ? 128 : 64;    // of a step
-    auto steps_of = [&](int j) { return (at.T0[j] + keys - 1) / keys + (n_rows + keys - 1) / keys; };
-    int64_t all = 0, ranges = 0;
-    for (int j = 0; j < n_list; ++j) all += (int64_t)Hkv * steps_of(j);
-    // the shortest ranges that are one round (two workgroups a CU)
-    int64_t L = (all + 2 * kStreamSlots - 1) / (2 * kStreamSlots);
-    for (;; L += 1 + L / 16) {
-      ranges = 0;
-      for (int j = 0; j < n_list; ++j) ranges += Hkv * ((steps_of(j) + L - 1) / L);
-      if (ranges <= 2 * kStreamSlots || ranges <= pairs) break;
+  const double mb = 32e-6 * at.part_groups * 4 * (D + 2);   // of one partial block
+  const int64_t most = part_rows / (32 * (int64_t)at.part_groups);
+  const int plain_groups = at.key_groups;
+  int64_t range = 0;                        // split mode: steps of a range
+  int range_keys = 0;                       // and keys of a step
+  auto steps_of = [&](int j, int keys) { return (at.T0[j] + keys - 1) / keys + (n_rows + keys - 1) / keys; };
+  // The shortest ranges of steps of `keys` keys that make at most `room` of
+  // them; *count gets how many.
+  auto shortest = [&](int keys, int64_t room, int64_t *count) {
+    int64_t all = 0;
+    for (int j = 0; j < n_list; ++j) all += (int64_t)Hkv * steps_of(j, keys);
+    for (int64_t L = room > 0 ? (all + room - 1) / room : all;; L += 1 + L / 16) {
+      *count = 0;
+      for (int j = 0; j < n_list; ++j) *count += Hkv * ((steps_of(j, keys) + L - 1) / L);
+      if (*count <= room || *count <= pairs) return L;
     }
-    if (6.0 + 1.2 * (double)L < best && ranges * 32 * at.part_groups <= part_rows) {
-      int64_t off = 0;
-      for (int j = 0; j < n_list; ++j) {
-        at.st_tiles[j] = (int32_t)((steps_of(j) + L - 1) / L);
-        at.st_off[j] = (int32_t)off;
-        off += (int64_t)Hkv * at.st_tiles[j];
-      }
-      at.st_off[n_list] = (int32_t)off;
+  };
+  int64_t count = 0;
+  if (P <= kSplitRows) {
+    const int keys = P <= 32 ? 128 : 64;
+    const int64_t L = shortest(keys, 2 * kStreamSlots, &count);
+    const double cost = 6.0 + 1.2 * (double)L;
+    if (cost < best && count <= most) {
+      best = cost;
       at.split = 1;
-      at.st_units = (int32_t)L;
-      return;
+      range = L;
+      range_keys = keys;
+    }
+  } else {
+    for (int e = 1; e < 4; ++e) {
+      const int64_t rows = kAttnRowsPerBlock >> e, nqt = (P + rows - 1) / rows;
+      const int keys = e == 3 ? 256 : 128;
+      if (nqt * pairs > kStreamSlots / 2) continue;   // (no two ranges a pair)
+      const int64_t L = shortest(keys, kStreamSlots / nqt, &count);
+      const double cost = (double)(L * keys) * kStep[e] / (64 << e) + 6.0 + 0.27 * mb * (double)count;
+      if (cost < best && count <= most) {
+        best = cost;
+        at.split = 2;
+        at.key_groups = 1 << e;
+        range = L;
+        range_keys = keys;
+      }
     }
   }
-  at.st_off[n_list] = (int32_t)total;
-  at.st_total = (int32_t)total;
   const int64_t nqt = (P + kAttnRowsPerBlock - 1) / kAttnRowsPerBlock;
-  const int64_t most = part_rows / (32 * (int64_t)at.part_groups) - pairs + 1;
   const double step = D == 128 ? 1.1 : 1.25;
-  const double mb = 32e-6 * at.part_groups * 4 * (D + 2);   // of a unit's partial rows
   // one and two full rounds of workgroups, and parts of one (their partials
   // cost less)
   static const int kNum[8] = {8, 4, 3, 2, 4, 1, 2, 1}, kDen[8] = {4, 4, 4, 4, 6, 3, 8, 6};
-  for (int c = 0; c < 8; ++c) {
+  for (int c = 0; c < 8 && P > kSplitRows; ++c) {
     const int64_t units = kStreamSlots * kNum[c] / (kDen[c] * nqt);
-    if (units < 2 || units > most || units > total) continue;
+    if (units < 2 || units + pairs - 1 > most || units > total) continue;
     const double cost = rounds(units * nqt) * ((double)((total + units - 1) / units) * step + 2.0) + 4.0 +
                         0.27 * mb * (double)(units + pairs);
     if (cost < best) {
       best = cost;
       at.st_units = (int32_t)units;
     }
+  }
+  if (at.st_units > 0) {
+    at.split = 0;
+    at.key_groups = plain_groups;
+    at.st_off[n_list] = (int32_t)total;
+    at.st_total = (int32_t)total;
+  } else if (at.split) {
+    int64_t off = 0;
+    for (int j = 0; j < n_list; ++j) {
+      at.st_tiles[j] = (int32_t)((steps_of(j, range_keys) + range - 1) / range);
+      at.st_off[j] = (int32_t)off;
+      off += (int64_t)Hkv * at.st_tiles[j];
+    }
+    at.st_off[n_list] = (int32_t)off;
+    at.st_units = (int32_t)range;
   }
 }
 

@@ -64,14 +64,16 @@ struct AttnArgs {
   // nqt workgroups each.  Unit u writes the unnormalised O, running maximum
   // and row sum (fp32) of each pair k it touches to opart / mlpart block u + k
   // of part_groups 32-row groups; a combine kernel merges each pair's blocks.
-  // Split mode (`split`): pair k's steps (of 128 keys, or 64 with more than 32
-  // packed rows) are cut into st_tiles[j] ranges of st_units steps, entry j's
-  // ranges from st_off[j]; range x writes block x.
+  // Split mode (`split`): pair k's steps are cut into st_tiles[j] ranges of
+  // st_units steps, entry j's ranges from st_off[j]; range x writes block x.
+  // split 1: up to kSplitRows packed rows, workgroups of four waves, steps of
+  // 128 keys (64 with more than 32 rows); split 2: key_groups key groups, steps
+  // of 128 keys (256 with 8 groups).
   // st_units = 0: the plain kernel, one workgroup per (entry, KV head, query
   // tile).
   int32_t split;
   int32_t st_units, st_total, st_entries, part_groups;   // (st_entries: the launch's entries, in every mode)
-  int32_t key_groups;       // plain kernel: 1, 2, 4 or 8 groups of waves that share the keys (256 / key_groups rows a workgroup)
+  int32_t key_groups;       // 1, 2, 4 or 8 groups of waves that share the keys (256 / key_groups rows a workgroup)
   int32_t st_off[kMaxLayers + 1];
   int32_t st_tiles[kMaxLayers];
   float *opart;             // [..][part_groups][d / 8][64 lanes][4 channels] fp32 (unnormalised; scale in mlpart)

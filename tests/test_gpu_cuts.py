@@ -24,9 +24,14 @@ SHAPES = [
     ("eight_groups_fewer_tiles", 8, 2, 64, 257, 1),
     ("eight_groups_d64", 14, 2, 64, 1024, 196),
     ("eight_groups_d128", 6, 3, 128, 191, 65),
-    ("stream_d64", 14, 2, 64, 4000, 300),
-    ("stream_d128", 28, 4, 128, 6144, 196),
-    ("stream_g9", 9, 1, 128, 2001, 64),
+    ("split_two_groups_d64", 14, 2, 64, 4000, 300),
+    ("split_two_groups_or_stream_d128", 28, 4, 128, 6144, 196),
+    ("split_four_groups_d128", 28, 4, 128, 2600, 130),
+    ("split_four_groups_d64", 14, 2, 64, 2300, 64),
+    ("split_eight_groups_d128", 9, 1, 128, 2001, 64),
+    ("split_eight_groups_d64", 8, 1, 64, 1900, 200),
+    ("split_four_waves", 12, 3, 64, 1300, 1),
+    ("stream_d64", 14, 2, 64, 3000, 1200),
 ]
 
 
@@ -40,6 +45,7 @@ QUERIES = [
     ("65_packed_rows", 2, 13, 1, 128, (900, 2047), 5),
     ("128_packed_rows", 2, 4, 4, 64, (500, 1601), 128),
     ("129_packed_rows", 2, 3, 1, 128, (900, 4000), 43),
+    ("four_groups_unequal", 2, 28, 4, 128, (700, 4001), 64),
 ]
 
 
