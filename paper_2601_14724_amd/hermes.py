@@ -128,8 +128,18 @@ def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
     return None if t is None else t.data_ptr()
 
 
+# The current stream's handle without building a torch.cuda.Stream object for
+# each call (2.8 us, a fifth of a one-token query's host time).
+try:
+    from torch._C import _cuda_getCurrentRawStream as _raw_stream, _cuda_getDevice as _device
+except ImportError:   # a torch without a GPU build
+    _raw_stream = None
+
+
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_device())
 
 
 def _need(t: torch.Tensor, dtype: torch.dtype, shape: tuple, name: str) -> None:
