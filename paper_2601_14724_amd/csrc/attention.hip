@@ -598,8 +598,9 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 1 : 2) void attn_fwd(AttnArgs a,
 // w, w + 4, ... in order, kCombineAhead of them loaded at once, and the four
 // waves' sums are added in wave order.  The launch is bound by the latency of
 // its loads: with one thread walking all blocks one by one, a pair's 64
-// blocks took 20-31 us.
-constexpr int kCombineAhead = 4;
+// blocks took 20-31 us, now 4-6.  784 rows of one layer (40 MB of partials):
+// 12.5 us with 4 loaded at once, 10.5 with 2 (more waves fit), 17 with 8.
+constexpr int kCombineAhead = 2;
 template <int D>
 __global__ __launch_bounds__(256) void attn_combine(AttnArgs a) {
   const int j = blockIdx.z, kv = blockIdx.y;
