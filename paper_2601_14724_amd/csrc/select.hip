@@ -1,5 +1,6 @@
 // Scoring, cross-layer smoothing and TopK selection for gfx950, in two
-// launches over the layers over budget:
+// launches over the layers over budget (one, score_select, when no layer has
+// more candidates than a scoring workgroup takes):
 //   score_keys   importance S^l_i by class (Sec. 3.1): recency
 //                R_i = e^{-k(T-1-i)}/Z (shallow), attention A_i = alpha_i W_i
 //                normalised to sum 1 (deep), (1 - omega_l) A + omega_l R
@@ -500,13 +501,12 @@ __device__ __forceinline__ double mass_scaled(float w, int i, int T0, int C, int
 constexpr int MU = 2;
 constexpr int MCH = NT * MU;
 
-__global__ __launch_bounds__(NT) void score_keys(SelectArgs a) {
-  __shared__ __align__(16) uint32_t s_buf[kLdsPos];   // positions of layer l+1
-  __shared__ __align__(16) uint32_t s_w1[kLdsPos];    // W of layer l+1 as bits
+// Block `blk` of layer l: keys[i] for its candidates i (in global memory or LDS);
+// s_buf and s_w1 hold the positions and W (as bits) of layer l+1.
+__device__ __forceinline__ void score_block(const SelectArgs &a, int l, int blk, uint32_t *s_buf, uint32_t *s_w1,
+                                            uint32_t *keys) {
   const int tid = threadIdx.x;
-  const int l = a.layer_id[blockIdx.y];
   const int T = a.len[l];
-  if ((int)blockIdx.x * MCH >= T) return;   // whole block past the layer's end (uniform)
   const LayerTable &L0 = a.tab[l];
   const int C = a.C;
   const int T0 = T - C;
@@ -540,7 +540,7 @@ __global__ __launch_bounds__(NT) void score_keys(SelectArgs a) {
   Partials q0 = {nullptr, 0, 0.0, 0.0}, q1 = {nullptr, 0, 0.0, 0.0};
   if (needA0) q0 = load_partials(a.normpart + l * a.normpart_lstride, nb0);
   if (needA1) q1 = load_partials(a.normpart + (l + 1) * a.normpart_lstride, nb1);
-  const int i0 = blockIdx.x * MCH + tid * MU;
+  const int i0 = blk * MCH + tid * MU;
   float wv[MU];
   int pv[MU];
 #pragma unroll
@@ -580,7 +580,6 @@ __global__ __launch_bounds__(NT) void score_keys(SelectArgs a) {
   const double inv_sa0 = sa0 > 0.0 ? 1.0 / sa0 : 0.0, inv_sa1 = sa1 > 0.0 ? 1.0 / sa1 : 0.0;
   const double inv_z0 = a.inv_z[l], inv_z1 = has_next ? a.inv_z[l + 1] : 0.0;
   const double ek = a.ek, inv_c = a.inv_c;
-  uint32_t *keys = a.keys + l * a.keys_lstride;
   int jp0 = -1, jp1 = -1;
   double rv0 = 0.0, rv1 = 0.0;
 #pragma unroll
@@ -604,7 +603,13 @@ __global__ __launch_bounds__(NT) void score_keys(SelectArgs a) {
     keys[i] = __builtin_bit_cast(uint32_t, f);
     if (L0.s_dbg != nullptr) L0.s_dbg[i] = f;
   }
+}
 
+__global__ __launch_bounds__(NT) void score_keys(SelectArgs a) {
+  __shared__ __align__(16) uint32_t s_buf[kLdsPos], s_w1[kLdsPos];
+  const int l = a.layer_id[blockIdx.y];
+  if ((int)blockIdx.x * MCH >= a.len[l]) return;   // whole block past the layer's end (uniform)
+  score_block(a, l, blockIdx.x, s_buf, s_w1, a.keys + l * a.keys_lstride);
 }
 
 // TopK of keys[0..T) (M < T) into out (and out2 if non-null): staged in LDS
@@ -650,6 +655,36 @@ __global__ __launch_bounds__(NT) void select_kept(SelectArgs a) {
               big);
 }
 
+// 1 and 2 in one launch, where one workgroup scores a whole layer (T <= MCH):
+// the keys stay in LDS.  Both launches are bound by latency; for one layer of
+// 1220 candidates they took 4.4 + 10.1 us, this one 9.8.  A longer
+// layer keeps the two: one workgroup would score it alone (28 layers of 8976:
+// 32 us against 26).
+__global__ __launch_bounds__(NT) void score_select(SelectArgs a) {
+  __shared__ __align__(16) uint32_t s_buf[kLdsPos], s_w1[kLdsPos];
+  __shared__ SelectShared sh;
+  __shared__ uint32_t keys[MCH];
+  const int l = a.layer_id[blockIdx.x];
+  const LayerTable &L0 = a.tab[l];
+  const int T = a.len[l], M = L0.budget;
+  if (T <= M) return;
+  score_block(a, l, 0, s_buf, s_w1, keys);
+  __syncthreads();
+  // (keys is free once the radix passes are done and takes the kept list)
+  select_top_regs<MU>(keys, T, M, reinterpret_cast<int32_t *>(keys), nullptr, sh);
+  __syncthreads();
+  int32_t *out = a.kept + l * a.kept_lstride, *out2 = L0.kept_dbg;
+#pragma unroll
+  for (int u = 0; u < MU; ++u) {
+    const int i = u * NT + threadIdx.x;
+    if (i < M) {
+      const int32_t x = static_cast<int32_t>(keys[i]);
+      out[i] = x;
+      if (out2 != nullptr) out2[i] = x;
+    }
+  }
+}
+
 __global__ __launch_bounds__(NT) void topk_keys(const uint32_t *keys, int n, int k, int32_t *out) {
   __shared__ SelectShared sh;
   __shared__ uint32_t big[kLdsKeys];
@@ -665,6 +700,10 @@ __global__ __launch_bounds__(NT) void topk_keys(const uint32_t *keys, int n, int
 hipError_t launch_select(const SelectArgs &a, hipStream_t s) {
   int max_T = 0;
   for (int j = 0; j < a.n_list; ++j) max_T = max(max_T, a.len[a.layer_id[j]]);
+  if (max_T <= MCH) {
+    hipLaunchKernelGGL(score_select, dim3(a.n_list), dim3(NT), 0, s, a);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(score_keys, dim3((max_T + MCH - 1) / MCH, a.n_list), dim3(NT), 0, s, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
