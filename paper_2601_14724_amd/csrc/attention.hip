@@ -87,10 +87,11 @@ __device__ __forceinline__ void copy_share(const AttnArgs &a, int D, int id, int
   const int share = n < entries ? 0 : id / entries;
   const int shares = n < entries ? 1 : (n - first + entries - 1) / entries;
   for (int j = first; j < entries; j += step) {
-    const LayerTable &L = a.tab[a.layer_id[j]];
-    const int cur = a.cur[j], T0 = a.T0[j];
-    const uint16_t *kn = a.kn + a.slot[j] * a.kv_lstride, *vn = a.vn + a.slot[j] * a.kv_lstride;
-    uint16_t *kd = L.k[cur] + (int64_t)T0 * a.Hkv * D, *vd = L.v[cur] + (int64_t)T0 * a.Hkv * D;
+    const AttnEntry &en = a.e[j];
+    const LayerTable &L = a.tab[en.layer];
+    const int cur = en.cur, T0 = en.T0;
+    const uint16_t *kn = a.kn + en.slot * a.kv_lstride, *vn = a.vn + en.slot * a.kv_lstride;
+    uint16_t *kd = en.k + (int64_t)T0 * a.Hkv * D, *vd = en.v + (int64_t)T0 * a.Hkv * D;
     for (int x = share * threads + threadIdx.x; x < per; x += shares * threads) {
       *reinterpret_cast<uint4 *>(kd + 8 * (int64_t)x) = gload16(kn + 8 * (int64_t)x);
       *reinterpret_cast<uint4 *>(vd + 8 * (int64_t)x) = gload16(vn + 8 * (int64_t)x);
@@ -109,7 +110,7 @@ __device__ __forceinline__ void copy_share(const AttnArgs &a, int D, int id, int
 // STREAM: passes whose (entry, KV head, query tile) workgroups would not fill
 // the CUs (one layer's chunk, queries, guidance prompts).  The key tiles of
 // every (entry, KV head) pair, concatenated in pair order (pair k = j Hkv +
-// kv, st_tiles[j] tiles each, entry j's pairs from tile st_off[j]), are cut
+// kv, e[j].st_tiles tiles each, entry j's pairs from tile e[j].st_off), are cut
 // into st_units equal ranges; unit u is nqt workgroups with consecutive ids
 // (one per query tile, sharing the K/V tiles in their XCD's L2) over tiles
 // [u N / U, (u + 1) N / U).  The workgroup walks its range pair by pair;
@@ -127,8 +128,8 @@ __device__ __forceinline__ void copy_share(const AttnArgs &a, int D, int id, int
 // walks a KG-th of the keys: what a launch of few rows needs to fill the CUs,
 // for KG times the K/V staging per row.
 //
-// SPLIT: each pair's steps are cut into st_tiles[j] ranges of st_units steps
-// (entry j's from st_off[j]), each nqt workgroups with consecutive ids, one for
+// SPLIT: each pair's steps are cut into e[j].st_tiles ranges of st_units steps
+// (entry j's from e[j].st_off), each nqt workgroups with consecutive ids, one for
 // each query tile.  Each writes its partial state as in stream mode.  A pass of
 // a few rows then fills the CUs with less partial state than stream mode's
 // 256-row workgroups write.  Where the packed rows fit one workgroup (a few
@@ -193,18 +194,17 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 1 : 2) void attn_fwd(AttnArgs a,
   auto enter = [&](int jj, int kvv) {
     j = jj;
     kv = kvv;
-    const LayerTable &lt = a.tab[a.layer_id[j]];
-    const int cur = a.cur[j];
-    T0 = a.T0[j];
+    const AttnEntry &en = a.e[j];
+    T0 = en.T0;
     n_pure = T0 / BN;                       // tiles that need no mask
     n_cache = (T0 + BN - 1) / BN;
     ntiles = n_cache + (pmax / G) / BN + 1; // the last one a row of the block sees
-    const int slot = a.slot[j];
+    const int slot = en.slot;
     q = a.q + slot * a.q_lstride;
     kn = a.kn + slot * a.kv_lstride;
     vn = a.vn + slot * a.kv_lstride;
-    kc = lt.k[cur];
-    vc = lt.v[cur];
+    kc = en.k;
+    vc = en.v;
     const int h = kv * G + g;
 #pragma unroll
     for (int kk = 0; kk < D / 16; ++kk) {
@@ -223,12 +223,12 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 1 : 2) void attn_fwd(AttnArgs a,
     int e = 0;
 #pragma unroll
     for (int b = kMaxLayers / 2; b > 0; b >>= 1) {
-      const int at = a.st_off[e + b];       // (unused entries are not taken)
+      const int at = a.e[min(e + b, a.st_entries - 1)].st_off;
       e += (int)(e + b < a.st_entries) & (int)(x >= at) ? b : 0;
     }
     jj = e;
-    kvv = __builtin_amdgcn_readfirstlane((x - a.st_off[e]) / a.st_tiles[e]);
-    f = a.st_off[e] + kvv * a.st_tiles[e];
+    kvv = __builtin_amdgcn_readfirstlane((x - a.e[e].st_off) / a.e[e].st_tiles);
+    f = a.e[e].st_off + kvv * a.e[e].st_tiles;
   };
   if constexpr (MODE != PLAIN) {
     int jj, kvv;
@@ -553,7 +553,7 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 1 : 2) void attn_fwd(AttnArgs a,
     // cost 50-70 vector registers and spilled.
     int t = x_lo - first, k = j * Hkv + kv, x = x_lo;
     do {
-      const int n = min(a.st_tiles[j] - t, x_hi - x);
+      const int n = min(a.e[j].st_tiles - t, x_hi - x);
       walk(t, n);
       flush(u + k);
       x += n;
@@ -574,7 +574,7 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 1 : 2) void attn_fwd(AttnArgs a,
     flush(unit);
   } else {
     walk(0, ntiles);
-    uint16_t *orow = a.out + a.slot[j] * a.q_lstride + ((int64_t)r * Hq + kv * G + g) * D + 4 * half;
+    uint16_t *orow = a.out + a.e[j].slot * a.q_lstride + ((int64_t)r * Hq + kv * G + g) * D + 4 * half;
     float mt, lsum;
     merge(mt, lsum, [&](int c, float4 x) {
       const float inv = 1.f / lsum;
@@ -584,7 +584,7 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 1 : 2) void attn_fwd(AttnArgs a,
                   (uint32_t)f2bf(x.z * inv) | ((uint32_t)f2bf(x.w * inv) << 16)};
     });
     if (row_ok && a.lse != nullptr && kg == 0 && half == 0)
-      a.lse[a.layer_id[j] * a.lse_lstride + (int64_t)kv * P + prow] = mt + log2f(lsum);
+      a.lse[a.e[j].layer * a.lse_lstride + (int64_t)kv * P + prow] = mt + log2f(lsum);
   }
   if (a.pos != nullptr) copy_share(a, D, lin, gridDim.x);
 }
@@ -604,7 +604,7 @@ constexpr int kCombineAhead = 2;
 template <int D>
 __global__ __launch_bounds__(256) void attn_combine(AttnArgs a) {
   const int j = blockIdx.z, kv = blockIdx.y;
-  const int layer = a.layer_id[j];
+  const int layer = a.e[j].layer;
   const int G = a.Hq / a.Hkv, P = a.C * G;
   const int rgi = blockIdx.x / (D / 32), db = blockIdx.x % (D / 32);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -613,9 +613,9 @@ __global__ __launch_bounds__(256) void attn_combine(AttnArgs a) {
   auto unit_of = [&](int64_t x) {
     return (int)(((x + 1) * a.st_units + a.st_total - 1) / a.st_total - 1);
   };
-  const int64_t f = a.st_off[j] + (int64_t)kv * a.st_tiles[j];
+  const int64_t f = a.e[j].st_off + (int64_t)kv * a.e[j].st_tiles;
   const int u0 = a.split ? (int)f : unit_of(f);
-  const int nsp = a.split ? a.st_tiles[j] : unit_of(f + a.st_tiles[j] - 1) - u0 + 1;
+  const int nsp = a.split ? a.e[j].st_tiles : unit_of(f + a.e[j].st_tiles - 1) - u0 + 1;
   const int64_t rg0 = ((int64_t)u0 + (a.split ? 0 : j * a.Hkv + kv)) * a.part_groups + rgi;
   const float4 *op = reinterpret_cast<const float4 *>(a.opart) + (rg0 * (D / 8) + 4 * db) * 64 + lane;
   const int64_t ostep = (int64_t)a.part_groups * (D / 8) * 64, mstep = (int64_t)a.part_groups * 32;
@@ -690,7 +690,7 @@ __global__ __launch_bounds__(256) void attn_combine(AttnArgs a) {
   const int r = p / G, h = kv * G + (p - r * G);
   if (a.out != nullptr) {
     const float inv = 1.f / lsum;
-    uint16_t *orow = a.out + a.slot[j] * a.q_lstride + ((int64_t)r * a.Hq + h) * D + 32 * db + 8 * wave + 4 * half;
+    uint16_t *orow = a.out + a.e[j].slot * a.q_lstride + ((int64_t)r * a.Hq + h) * D + 32 * db + 8 * wave + 4 * half;
     *reinterpret_cast<uint2 *>(orow) = uint2{(uint32_t)f2bf(t.x * inv) | ((uint32_t)f2bf(t.y * inv) << 16),
                                              (uint32_t)f2bf(t.z * inv) | ((uint32_t)f2bf(t.w * inv) << 16)};
   }
@@ -705,14 +705,13 @@ __global__ __launch_bounds__(256, 3) void attn_colsum(ColsumArgs a, int nkb) {
   const int split = (lin / nkb) % a.splits;
   const int kv_blk = (lin / (nkb * a.splits)) % a.Hkv;
   const int j = lin / (nkb * a.splits * a.Hkv);
-  const int layer = a.layer_id[j];
-  const LayerTable &lt = a.tab[layer];
-  const int cur = a.cur[j];
-  const int T0 = a.T0[j];
+  const MassEntry &en = a.e[j];
+  const int layer = en.layer;
+  const int T0 = en.T0;
   const int C = a.C, Hq = a.Hq, Hkv = a.Hkv;
   const int G = Hq / Hkv;
   const int P = C * G;
-  const int T = a.ncand[j];        // candidates: T0 + C, or T0 for a prompt
+  const int T = en.ncand;          // candidates: T0 + C, or T0 for a prompt
   const int k0 = kblk * BK;
   if (k0 >= T) return;
 
@@ -737,10 +736,10 @@ __global__ __launch_bounds__(256, 3) void attn_colsum(ColsumArgs a, int nkb) {
   const int nit = (int)((int64_t)(split + 1) * ntq / a.splits) - t_lo;
   const int p_begin = p_first + t_lo * BQS;
 
-  const int slot = a.slot[j];
+  const int slot = en.slot;
   const uint16_t *q = a.q + slot * a.q_lstride;
   const uint16_t *kn = a.kn + slot * a.kv_lstride;
-  const uint16_t *kc = lt.k[cur];
+  const uint16_t *kc = en.k;
   const float *lse_l = a.lse + layer * a.lse_lstride;
   const float c = a.scale_log2;
 
@@ -926,8 +925,9 @@ __global__ __launch_bounds__(256, 3) void attn_colsum(ColsumArgs a, int nkb) {
 template <int MG>
 __global__ __launch_bounds__(kNormBlock *MG) void mass_reduce(ColsumArgs a) {
   const int j = blockIdx.y;
-  const int layer = a.layer_id[j];
-  const int T = a.ncand[j];
+  const MassEntry &en = a.e[j];
+  const int layer = en.layer;
+  const int T = en.ncand;
   if ((int)blockIdx.x * kNormBlock >= T) return;   // whole block past this layer's end
   __shared__ double run[MG > 1 ? MG - 1 : 1][kNormBlock];
   __shared__ double red[kNormBlock / 64];
@@ -956,8 +956,8 @@ __global__ __launch_bounds__(kNormBlock *MG) void mass_reduce(ColsumArgs a) {
     for (int x = 0; x < MG - 1; ++x) w += run[x][lc];
     if (i < T) {
       const float wf = (float)w;
-      a.tab[layer].w[i] = wf;
-      m = mass_over_observers(wf, i, a.T0[j], a.C, a.alpha_mode[j]);
+      en.w[i] = wf;
+      m = mass_over_observers(wf, i, en.T0, a.C, en.alpha_mode);
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) m += __shfl_xor(m, o);
@@ -1003,12 +1003,12 @@ static hipError_t parted_pass(const AttnArgs &a, int n_list, hipStream_t s) {
   const int P = a.C * (a.Hq / a.Hkv);
   if (a.split == 2) {
     const int nqt = (P + BM / a.key_groups - 1) / (BM / a.key_groups);
-    const dim3 grid(a.st_off[n_list] * nqt);
+    const dim3 grid(a.e[n_list].st_off * nqt);
     if (a.key_groups == 2) hipLaunchKernelGGL((attn_fwd<D, 8, 2, SPLIT, true>), grid, dim3(AT), 0, s, a, nqt);
     else if (a.key_groups == 4) hipLaunchKernelGGL((attn_fwd<D, 8, 4, SPLIT, true>), grid, dim3(AT), 0, s, a, nqt);
     else hipLaunchKernelGGL((attn_fwd<D, 8, 8, SPLIT, true>), grid, dim3(AT), 0, s, a, nqt);
   } else if (a.split == 1) {
-    const dim3 grid(a.st_off[n_list]), block(256);
+    const dim3 grid(a.e[n_list].st_off), block(256);
     if (P <= 32) hipLaunchKernelGGL((attn_fwd<D, 4, 4, SPLIT, true>), grid, block, 0, s, a, 1);
     else if (P <= 64) hipLaunchKernelGGL((attn_fwd<D, 4, 2, SPLIT, true>), grid, block, 0, s, a, 1);
     else hipLaunchKernelGGL((attn_fwd<D, 4, 1, SPLIT, true>), grid, block, 0, s, a, 1);

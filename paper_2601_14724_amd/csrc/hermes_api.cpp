@@ -170,7 +170,7 @@ bool layout_within(const hermes_config *c, size_t limit, Layout *out) {
   return true;
 }
 
-// How a pass of n_rows rows per entry over caches of at.T0[j] tokens is cut
+// How a pass of n_rows rows per entry over caches of at.e[j].T0 tokens is cut
 // into workgroups, with room for part_rows partial rows.  Four ways, of which
 // the cheapest by the estimate below is taken:
 //  - the plain kernel with one key group: a workgroup per (entry, KV head, 256
@@ -210,9 +210,9 @@ void attention_plan(AttnArgs &at, int n_rows, int G, int Hkv, int n_list, int D,
   int64_t total = 0;
   int max_tiles = 1;
   for (int j = 0; j < n_list; ++j) {
-    const int tiles = (at.T0[j] + 63) / 64 + (n_rows + 63) / 64;
-    at.st_tiles[j] = tiles;
-    at.st_off[j] = (int32_t)total;
+    const int tiles = (at.e[j].T0 + 63) / 64 + (n_rows + 63) / 64;
+    at.e[j].st_tiles = tiles;
+    at.e[j].st_off = (int32_t)total;
     total += (int64_t)Hkv * tiles;
     max_tiles = tiles > max_tiles ? tiles : max_tiles;
   }
@@ -237,7 +237,7 @@ void attention_plan(AttnArgs &at, int n_rows, int G, int Hkv, int n_list, int D,
   const int plain_groups = at.key_groups;
   int64_t range = 0;                        // split mode: steps of a range
   int range_keys = 0;                       // and keys of a step
-  auto steps_of = [&](int j, int keys) { return (at.T0[j] + keys - 1) / keys + (n_rows + keys - 1) / keys; };
+  auto steps_of = [&](int j, int keys) { return (at.e[j].T0 + keys - 1) / keys + (n_rows + keys - 1) / keys; };
   // The shortest ranges of steps of `keys` keys that make at most `room` of
   // them; *count gets how many.
   auto shortest = [&](int keys, int64_t room, int64_t *count) {
@@ -294,16 +294,16 @@ void attention_plan(AttnArgs &at, int n_rows, int G, int Hkv, int n_list, int D,
   if (at.st_units > 0) {
     at.split = 0;
     at.key_groups = plain_groups;
-    at.st_off[n_list] = (int32_t)total;
+    at.e[n_list].st_off = (int32_t)total;
     at.st_total = (int32_t)total;
   } else if (at.split) {
     int64_t off = 0;
     for (int j = 0; j < n_list; ++j) {
-      at.st_tiles[j] = (int32_t)((steps_of(j, range_keys) + range - 1) / range);
-      at.st_off[j] = (int32_t)off;
-      off += (int64_t)Hkv * at.st_tiles[j];
+      at.e[j].st_tiles = (int32_t)((steps_of(j, range_keys) + range - 1) / range);
+      at.e[j].st_off = (int32_t)off;
+      off += (int64_t)Hkv * at.e[j].st_tiles;
     }
-    at.st_off[n_list] = (int32_t)off;
+    at.e[n_list].st_off = (int32_t)off;
     at.st_units = (int32_t)range;
   }
 }
@@ -395,6 +395,17 @@ struct hermes_ctx {
   // and captured calls, which may be replayed on any stream, run without).
   hipStream_t slot_stream[kAppendSlots] = {};
   bool slot_taken[kAppendSlots] = {};
+
+  AttnEntry attn_entry(int l, int slot) const {
+    const int c = cur[l];
+    return AttnEntry{static_cast<uint16_t *>(bufs[l].k[c]), static_cast<uint16_t *>(bufs[l].v[c]), len[l], 0, 0,
+                     (int8_t)l, (int8_t)slot, (int8_t)c, 0};
+  }
+
+  MassEntry mass_entry(int l, int slot, int ncand, int alpha) const {
+    return MassEntry{static_cast<const uint16_t *>(bufs[l].k[cur[l]]), bufs[l].w, len[l], ncand, (int8_t)l,
+                     (int8_t)slot, (int8_t)alpha, 0};
+  }
 
   int append_slot(hipStream_t s) const {
     if (s == hipStreamPerThread) return -1;
@@ -839,10 +850,8 @@ static int append_impl(hermes_ctx *ctx, int32_t layer, const void *q, const void
 
   ColsumArgs cs;
   std::memset(&cs, 0, sizeof(cs));
-  cs.tab = ctx->d_tab;
   cs.q = at.q;
   cs.kn = at.kn;
-  cs.vn = at.vn;
   cs.lse = at.lse;
   cs.wpart = reinterpret_cast<double *>(ctx->ws + ctx->lay.wpart);
   cs.wpart_lstride = ctx->lay.wpart_lstride;
@@ -860,17 +869,9 @@ static int append_impl(hermes_ctx *ctx, int32_t layer, const void *q, const void
   for (size_t j = 0; j < list.size(); ++j) {
     const int l = list[j];
     const int8_t slot = (int8_t)(layer == HERMES_ALL_LAYERS ? l : 0);
-    at.T0[j] = ctx->len[l];
-    at.layer_id[j] = (int8_t)l;
-    at.slot[j] = slot;
-    at.cur[j] = ctx->cur[l];
+    at.e[j] = ctx->attn_entry(l, slot);
     if (need_w(l)) {
-      cs.T0[n_cs] = ctx->len[l];
-      cs.ncand[n_cs] = ctx->len[l] + n_new;
-      cs.layer_id[n_cs] = (int8_t)l;
-      cs.slot[n_cs] = slot;
-      cs.cur[n_cs] = ctx->cur[l];
-      cs.alpha_mode[n_cs] = (int8_t)ctx->alpha_mode;
+      cs.e[n_cs] = ctx->mass_entry(l, slot, ctx->len[l] + n_new, ctx->alpha_mode);
       max_T = ctx->len[l] + n_new > max_T ? ctx->len[l] + n_new : max_T;
       ++n_cs;
     }
@@ -973,10 +974,8 @@ int hermes_guidance_score(hermes_ctx *ctx, int32_t layer, const void *q, const v
   at.scale_log2 = scale_log2;
   ColsumArgs cs;
   std::memset(&cs, 0, sizeof(cs));
-  cs.tab = ctx->d_tab;
   cs.q = at.q;
   cs.kn = at.kn;
-  cs.vn = at.vn;
   cs.lse = at.lse;
   cs.wpart = reinterpret_cast<double *>(ctx->ws + ctx->lay.wpart);
   cs.wpart_lstride = ctx->lay.wpart_lstride;
@@ -993,12 +992,8 @@ int hermes_guidance_score(hermes_ctx *ctx, int32_t layer, const void *q, const v
   for (size_t j = 0; j < list.size(); ++j) {
     const int l = list[j];
     const int8_t slot = (int8_t)(layer == HERMES_ALL_LAYERS ? l : 0);
-    at.T0[j] = cs.T0[j] = ctx->len[l];
-    cs.ncand[j] = ctx->len[l];
-    at.layer_id[j] = cs.layer_id[j] = (int8_t)l;
-    at.slot[j] = cs.slot[j] = slot;
-    at.cur[j] = cs.cur[j] = ctx->cur[l];
-    cs.alpha_mode[j] = 1;   // every prompt row sees every candidate: A = W / sum W
+    at.e[j] = ctx->attn_entry(l, slot);
+    cs.e[j] = ctx->mass_entry(l, slot, ctx->len[l], 1);   // every prompt row sees every candidate: A = W / sum W
     max_T = ctx->len[l] > max_T ? ctx->len[l] : max_T;
   }
   const int n = (int)list.size();
@@ -1243,10 +1238,7 @@ int hermes_query_attend(hermes_ctx *ctx, int32_t layer, const void *q, const voi
   int n = 0;
   for (int l = 0; l < L; ++l) {
     if (layer != HERMES_ALL_LAYERS && l != layer) continue;
-    at.T0[n] = ctx->len[l];
-    at.layer_id[n] = (int8_t)l;
-    at.slot[n] = (int8_t)(layer == HERMES_ALL_LAYERS ? l : 0);
-    at.cur[n] = ctx->cur[l];
+    at.e[n] = ctx->attn_entry(l, layer == HERMES_ALL_LAYERS ? l : 0);
     ++n;
   }
   attention_plan(at, n_q, ctx->Hq / ctx->Hkv, ctx->Hkv, n, ctx->D, ctx->lay.part_rows);

@@ -37,10 +37,21 @@ struct LayerTable {
   double omega;
 };
 
-// Chunk (or query) attention: launch entry j covers layer layer_id[j], reads
-// cached rows [0, T0[j]) of buffer cur[j] and new rows from the stacked inputs
-// at slot j (stride *_lstride elements), writes out (if non-null) and lse (if
-// non-null).  n_list entries.
+// What an attention launch needs of one entry (layer), in one piece: the
+// launch's first loads are then one 32-byte read of its arguments, with no
+// read of the layer table behind it (a one-token query took 14.7 us a layer
+// with an array for each field and the pointers in the layer table, 13.4 so).
+struct AttnEntry {
+  uint16_t *k, *v;          // the current buffer of the layer's cache
+  int32_t T0;               // its cached rows
+  int32_t st_off, st_tiles; // stream and split mode, see AttnArgs
+  int8_t layer, slot, cur;  // slot: index of the layer's inputs in the stacked tensors
+  int8_t pad_;
+};
+
+// Chunk (or query) attention: entry e[j] reads the T0 cached rows of its layer
+// and new rows from the stacked inputs at its slot (stride *_lstride elements),
+// writes out (if non-null) and lse (if non-null).
 struct AttnArgs {
   const LayerTable *tab;
   const uint16_t *q, *kn, *vn;
@@ -54,18 +65,14 @@ struct AttnArgs {
   int64_t q_lstride, kv_lstride, lse_lstride;
   int32_t Hq, Hkv, C;
   float scale_log2;         // sm_scale * log2(e)
-  int32_t T0[kMaxLayers];
-  int8_t layer_id[kMaxLayers];
-  int8_t slot[kMaxLayers];      // index of the layer's inputs in the stacked tensors
-  int8_t cur[kMaxLayers];
   // Stream mode: the key tiles of every (entry, KV head) pair, concatenated in
-  // pair order (entry j's Hkv pairs of st_tiles[j] tiles each start at tile
-  // st_off[j]; st_total tiles in all), are cut into st_units equal ranges of
+  // pair order (entry j's Hkv pairs of e[j].st_tiles tiles each start at tile
+  // e[j].st_off; st_total tiles in all), are cut into st_units equal ranges of
   // nqt workgroups each.  Unit u writes the unnormalised O, running maximum
   // and row sum (fp32) of each pair k it touches to opart / mlpart block u + k
   // of part_groups 32-row groups; a combine kernel merges each pair's blocks.
-  // Split mode (`split`): pair k's steps are cut into st_tiles[j] ranges of
-  // st_units steps, entry j's ranges from st_off[j]; range x writes block x.
+  // Split mode (`split`): pair k's steps are cut into e[j].st_tiles ranges of
+  // st_units steps, entry j's ranges from e[j].st_off; range x writes block x.
   // split 1: up to kSplitRows packed rows, workgroups of four waves, steps of
   // 128 keys (64 with more than 32 rows); split 2: key_groups key groups, steps
   // of 128 keys (256 with 8 groups).
@@ -74,21 +81,29 @@ struct AttnArgs {
   int32_t split;
   int32_t st_units, st_total, st_entries, part_groups;   // (st_entries: the launch's entries, in every mode)
   int32_t key_groups;       // 1, 2, 4 or 8 groups of waves that share the keys (256 / key_groups rows a workgroup)
-  int32_t st_off[kMaxLayers + 1];
-  int32_t st_tiles[kMaxLayers];
   float *opart;             // [..][part_groups][d / 8][64 lanes][4 channels] fp32 (unnormalised; scale in mlpart)
   float *mlpart;            // [..][part_groups * 32][2] fp32 (max, sum)
+  AttnEntry e[kMaxLayers + 1];   // (the last one used has only st_off)
 };
 
-// Attention-mass sweep: W_i for the candidates i < ncand[j] of layer
-// layer_id[j] (ncand = T0 + C for the chunk's own mass, T0 for a guidance
-// prompt, whose rows are not candidates).  Each KV head's share, cut into
+// What a mass sweep needs of one entry, in one piece as in AttnEntry.
+struct MassEntry {
+  const uint16_t *k;        // the current buffer of the layer's cache
+  float *w;                 // the layer's mass
+  int32_t T0, ncand;
+  int8_t layer, slot;
+  int8_t alpha_mode;        // weighting of the normaliser partials (0 per observer, 1 plain)
+  int8_t pad_;
+};
+
+// Attention-mass sweep: W_i for the candidates i < ncand of each entry's layer
+// (ncand = T0 + C for the chunk's own mass, T0 for a guidance prompt, whose
+// rows are not candidates).  Each KV head's share, cut into
 // `splits` ranges of its query rows, goes to wpart[layer][kv * splits +
 // split][i] (fp64, rows of wpart_hstride), then is summed into the layer's w
 // buffer in that order.
 struct ColsumArgs {
-  const LayerTable *tab;
-  const uint16_t *q, *kn, *vn;
+  const uint16_t *q, *kn;
   const float *lse;
   double *wpart;
   double *normpart;         // [n_layers][normpart_lstride] fp64 partials of sum_i alpha_i W_i
@@ -96,12 +111,7 @@ struct ColsumArgs {
   int32_t Hq, Hkv, C;
   int32_t splits;           // workgroups that share a block's query rows (1: none)
   float scale_log2;
-  int32_t T0[kMaxLayers];
-  int32_t ncand[kMaxLayers];
-  int8_t layer_id[kMaxLayers];
-  int8_t slot[kMaxLayers];
-  int8_t cur[kMaxLayers];
-  int8_t alpha_mode[kMaxLayers];   // weighting of the normaliser partials (0 per observer, 1 plain)
+  MassEntry e[kMaxLayers];
 };
 
 // Scoring, smoothing and selection; one workgroup per listed layer.  len and
