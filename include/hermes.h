@@ -28,6 +28,12 @@
  *    HIP launch returns HERMES_EHIP and poisons the context: later calls
  *    return HERMES_ESTATE until it is destroyed and re-initialised.
  *  - One context is driven by one host thread at a time.
+ *    Layers may be appended, and queries run, on different streams.  A context
+ *    has room for the partial results of one stream's queries and of two
+ *    streams' appends (and those streams' queries); further streams and
+ *    captured calls take cuts without partial results, except that their
+ *    queries and guidance prompts of up to 64 rows share the first room and so
+ *    have to follow other queries and prompts of the context on the device.
  */
 #ifndef HERMES_H
 #define HERMES_H

@@ -413,18 +413,50 @@ struct hermes_ctx {
       if (!slot_taken[i] || slot_stream[i] == s) return i;
     return -1;
   }
+  static bool capturing(hipStream_t s) {   // (or not known to be no capture)
+    if (s == nullptr) return false;
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return true;
+  }
   bool take_slot(int i, hipStream_t s) {
-    if (s != nullptr) {
-      hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
-      if (hipStreamIsCapturing(s, &status) != hipSuccess) {
-        (void)hipGetLastError();
-        return false;
-      }
-      if (status != hipStreamCaptureStatusNone) return false;
-    }
+    if (capturing(s)) return false;
     slot_taken[i] = true;
     slot_stream[i] = s;
     return true;
+  }
+
+  // The query room (opart, mlpart) likewise belongs to the stream that first
+  // takes it; queries and prompts on another stream use its append room.  Where
+  // a stream has neither, passes of up to kSplitMaxTokens rows share the query
+  // room, so they have to follow each other on the device, and longer ones run
+  // without.
+  hipStream_t query_stream = nullptr;
+  bool query_taken = false;
+
+  void query_plan(AttnArgs &at, int n_rows, int n, hipStream_t s) {
+    auto plan = [&](int64_t rows, size_t o, size_t ml, int64_t first) {
+      attention_plan(at, n_rows, Hq / Hkv, Hkv, n, D, rows);
+      at.opart = reinterpret_cast<float *>(ws + o) + first * D;
+      at.mlpart = reinterpret_cast<float *>(ws + ml) + first * 2;
+    };
+    plan(lay.part_rows, lay.opart, lay.mlpart, 0);
+    if (at.st_units == 0) return;
+    const bool once = s == hipStreamPerThread || capturing(s);   // no stream that a room could belong to
+    if (!once && (!query_taken || query_stream == s)) {
+      query_taken = true;
+      query_stream = s;
+      return;
+    }
+    const int slot = once ? -1 : append_slot(s);
+    if (slot >= 0) {
+      slot_taken[slot] = true;
+      slot_stream[slot] = s;
+      plan(lay.append_rows, lay.aopart, lay.amlpart, slot * lay.append_rows);
+    } else if (n_rows > kSplitMaxTokens) {
+      plan(0, lay.opart, lay.mlpart, 0);
+    }
   }
 
   int prof_begin(int id, hipStream_t s, EventPair *ep) {
@@ -998,9 +1030,7 @@ int hermes_guidance_score(hermes_ctx *ctx, int32_t layer, const void *q, const v
   }
   const int n = (int)list.size();
   mass_splits(cs, n, max_T, ctx->lay.wpart_lstride);
-  attention_plan(at, n_rows, ctx->Hq / ctx->Hkv, ctx->Hkv, n, ctx->D, ctx->lay.part_rows);
-  at.opart = reinterpret_cast<float *>(ctx->ws + ctx->lay.opart);
-  at.mlpart = reinterpret_cast<float *>(ctx->ws + ctx->lay.mlpart);
+  ctx->query_plan(at, n_rows, n, s);
   const int rc = ctx->run(HERMES_K_GUIDE, s, [&] {
     hipError_t e = at.st_units > 0 ? launch_attention_parted(at, n, ctx->D, s)
                                    : launch_attention(at, n, ctx->D, s);
@@ -1241,9 +1271,7 @@ int hermes_query_attend(hermes_ctx *ctx, int32_t layer, const void *q, const voi
     at.e[n] = ctx->attn_entry(l, layer == HERMES_ALL_LAYERS ? l : 0);
     ++n;
   }
-  attention_plan(at, n_q, ctx->Hq / ctx->Hkv, ctx->Hkv, n, ctx->D, ctx->lay.part_rows);
-  at.opart = reinterpret_cast<float *>(ctx->ws + ctx->lay.opart);
-  at.mlpart = reinterpret_cast<float *>(ctx->ws + ctx->lay.mlpart);
+  ctx->query_plan(at, n_q, n, s);
   return ctx->run(HERMES_K_QUERY, s, [&] {
     return at.st_units > 0 ? launch_attention_parted(at, n, ctx->D, s)
                            : launch_attention(at, n, ctx->D, s);

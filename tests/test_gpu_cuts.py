@@ -73,6 +73,41 @@ def test_query_cuts_match_oracle(name, L, Hq, Hkv, d, lens, rows):
     kv.close()
 
 
+@pytest.mark.parametrize("rows", [64, 100])
+def test_queries_on_several_streams_match_oracle(rows):
+    """Layers queried at the same time on four streams of one context: a stream
+    with no room for partial rows of its own takes another cut (at 64 rows such
+    streams share a room, so they wait for each other here)."""
+    from paper_2601_14724_amd import hermes as H
+    L, Hq, Hkv, d, n = 4, 14, 2, 64, 3000
+    say(f"[cuts] queries of {rows} rows on {L} streams")
+    init, host = [], []
+    wl = wk.custom("streams", 500 + rows, L, Hq, Hkv, d, n, 1, (n,) * L, query_len=rows, anchor_period=29)
+    for l in range(L):
+        c, q = wk.gen_cache(wl, l), wk.gen_query(wl, l)
+        host.append((c, q))
+        init.append((streaming.bf16_tensor(c["k"], "cuda"), streaming.bf16_tensor(c["v"], "cuda"),
+                     torch.from_numpy(c["pos"]).cuda()))
+    kv = H.HermesKV(L, Hq, Hkv, d, [n] * L, rows, init=init)
+    t = {k: streaming.bf16_tensor(np.stack([q[k] for _, q in host]), "cuda") for k in ("q", "k", "v")}
+    out = torch.zeros_like(t["q"])
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in range(L)]
+    for _ in range(4):
+        for l, s in enumerate(streams):
+            if rows <= 64 and l > 0:
+                s.wait_stream(streams[l - 1])
+            with torch.cuda.stream(s):
+                kv.query(t["q"][l], t["k"][l], t["v"][l], layer=l, out=out[l])
+        if rows <= 64:
+            streams[0].wait_stream(streams[-1])
+    torch.cuda.synchronize()
+    for l, (c, q) in enumerate(host):
+        o, _ = orc.chunk_attention(f64(q["q"]), f64(c["k"]), f64(c["v"]), f64(q["k"]), f64(q["v"]), want_w=False)
+        check_o(out[l].float().cpu().numpy(), o, f"[cuts] query of {rows} rows, stream {l}")
+    kv.close()
+
+
 @pytest.mark.parametrize("name,Hq,Hkv,d,T0,C", SHAPES)
 def test_append_cuts_match_oracle(name, Hq, Hkv, d, T0, C):
     """Two layers appended one by one, then in one call: outputs and W."""
