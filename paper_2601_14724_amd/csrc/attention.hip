@@ -365,8 +365,10 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 1 : 2) void attn_fwd(AttnArgs a,
     // Lazy rescaling: the running maximum only moves when a row's tile
     // maximum exceeds it by more than 2^8 (in the log2 domain), so
     // probabilities stay <= 256; the test compares the raw maximum with the
-    // precomputed threshold (m_run + 8) / c.
-    if (__any(mx > m_lim)) {
+    // precomputed threshold (m_run + 8) / c.  Rare after the first tiles, so it
+    // lies out of line: 28 layers of 32768 + 3136 rows 56.98 -> 56.81 ms, and
+    // 0.1-0.3% on the other large calls.
+    if (__builtin_expect(__any(mx > m_lim), 0)) {
       const float m_new = fmaxf(m_run, mx * c);
       const float alpha = fast_exp2(m_run - m_new);
       m_run = m_new;
