@@ -29,11 +29,13 @@
  *    return HERMES_ESTATE until it is destroyed and re-initialised.
  *  - One context is driven by one host thread at a time.
  *    Layers may be appended, and queries run, on different streams.  A context
- *    has room for the partial results of one stream's queries and of two
- *    streams' appends (and those streams' queries); further streams and
- *    captured calls take cuts without partial results, except that their
- *    queries and guidance prompts of up to 64 rows share the first room and so
- *    have to follow other queries and prompts of the context on the device.
+ *    has room for the partial results of calls on three streams; a stream takes
+ *    one with its first call that is cut along the keys and keeps it for the
+ *    context's life, so work on it has to be finished before the stream is
+ *    destroyed.  Calls on further streams, on the per-thread default stream and
+ *    under capture take cuts without partial results, except that their queries
+ *    and guidance prompts of up to 64 rows share one room more: these have to
+ *    follow each other on the device, whatever runs on the three streams.
  */
 #ifndef HERMES_H
 #define HERMES_H

@@ -24,13 +24,18 @@ size_t round_up(size_t x) { return (x + kAlign - 1) & ~(kAlign - 1); }
 bool aligned(const void *p, size_t a) { return (reinterpret_cast<uintptr_t>(p) % a) == 0; }
 
 struct Layout {
-  size_t tab, lse, keys, kept, normpart, newc, wpart, spart, sumk, sumv, smeta, flag, opart, mlpart, aopart, amlpart, total;
+  size_t tab, lse, keys, kept, normpart, newc, wpart, spart, sumk, sumv, smeta, flag, shared, rooms, total;
   int64_t lse_lstride, keys_lstride, kept_lstride, wpart_lstride, spart_lstride, normpart_lstride,
       newc_lstride;
-  int64_t part_rows;        // stream-mode partial rows of queries and prompts
-  int64_t append_rows;      // and of appends, for each of append_slots streams (see append_slot)
-  int append_slots;
+  int64_t shared_rows;      // partial rows of the room that passes without one of their own share
+  int64_t room_rows;        // and of each of the n_rooms rooms that belong to a stream
+  int n_rooms;
 };
+
+// Bytes of a room of partial rows: fp32 O, then (max, sum).
+size_t room_bytes(int64_t rows, int head_dim) {
+  return round_up(sizeof(float) * (size_t)rows * head_dim) + round_up(sizeof(float) * 2 * (size_t)rows);
+}
 
 int max_budget(const hermes_config *c) {
   int m = 1;
@@ -82,12 +87,12 @@ int check_config(const hermes_config *c) {
   return HERMES_OK;
 }
 
-// Workspace layout of `c`; part_rows < 0 sizes the stream-mode partial state
-// for the most rows a short pass can write (256 for each of kStreamSlots
-// workgroups, and a block more for each (layer, KV head) pair), else for that
-// many rows.  slots: streams that appends cut along the keys have room for;
-// with none there is no room for sweeps cut along the query rows either.
-Layout layout_of(const hermes_config *c, int64_t part_rows = -1, int slots = kAppendSlots) {
+// Workspace layout of `c`; shared_rows < 0 sizes the shared room for the most
+// rows a short pass can write (256 for each of kStreamSlots workgroups, and a
+// block more for each (layer, KV head) pair), else for that many rows.  rooms:
+// streams that have a room of their own; with none there is no room for sweeps
+// cut along the query rows either.
+Layout layout_of(const hermes_config *c, int64_t shared_rows = -1, int rooms = kStreamRooms) {
   Layout s;
   s.lse_lstride = (int64_t)c->n_q_heads * c->max_chunk;
   s.keys_lstride = c->max_cap;
@@ -110,7 +115,7 @@ Layout layout_of(const hermes_config *c, int64_t part_rows = -1, int slots = kAp
   s.newc = off;
   off = round_up(off + sizeof(int32_t) * 3 * (size_t)s.newc_lstride * c->n_layers);
   s.wpart_lstride = (int64_t)c->n_kv_heads * c->max_cap;
-  if (slots > 0 && s.wpart_lstride < kMassPartials) s.wpart_lstride = kMassPartials;
+  if (rooms > 0 && s.wpart_lstride < kMassPartials) s.wpart_lstride = kMassPartials;
   s.wpart = off;
   off = round_up(off + sizeof(double) * (size_t)s.wpart_lstride * c->n_layers);
   // summary token: fp64 block sums, staged bf16 rows and their metadata
@@ -127,35 +132,33 @@ Layout layout_of(const hermes_config *c, int64_t part_rows = -1, int slots = kAp
   off = round_up(off + sizeof(int32_t) * kSumMeta * (size_t)c->n_layers);
   s.flag = off;
   off = round_up(off + sizeof(int32_t) * 4);
-  // stream-mode partial state of short passes (query, guidance prompt)
+  // partial state of passes whose keys are cut
   const int64_t G = c->n_q_heads / c->n_kv_heads;
-  s.part_rows = part_rows >= 0 ? part_rows
-                               : (int64_t)kStreamSlots * kAttnRowsPerBlock +
-                                     (int64_t)c->n_layers * c->n_kv_heads * kSplitMaxTokens * G;
-  s.opart = off;
-  off = round_up(off + sizeof(float) * (size_t)s.part_rows * c->head_dim);
-  s.mlpart = off;
-  off = round_up(off + sizeof(float) * 2 * (size_t)s.part_rows);
-  // and of appends: at most one block for two key tiles, and two more a pair
+  const int64_t short_rows =
+      (int64_t)kStreamSlots * kAttnRowsPerBlock + (int64_t)c->n_layers * c->n_kv_heads * kSplitMaxTokens * G;
+  s.shared_rows = shared_rows >= 0 ? shared_rows : short_rows;
+  s.shared = off;
+  off = round_up(off + room_bytes(s.shared_rows, c->head_dim));
+  // a stream's room: its short passes, and its longer ones (at most one block
+  // for two key tiles, and two more a pair)
   const int64_t blocks = (int64_t)c->n_layers * c->n_kv_heads * (((int64_t)c->max_cap + 63) / 64 / 2 + 2);
   const int64_t rows = (c->max_chunk * G + 31) / 32 * 32;
-  s.append_slots = slots;
-  s.append_rows = slots == 0 ? 0 : rows > kAppendPartRows / blocks ? kAppendPartRows : blocks * rows;
-  s.aopart = off;
-  off = round_up(off + sizeof(float) * (size_t)s.append_rows * c->head_dim * slots);
-  s.amlpart = off;
-  off = round_up(off + sizeof(float) * 2 * (size_t)s.append_rows * slots);
+  const int64_t long_rows = rows > kRoomRows / blocks ? kRoomRows : blocks * rows;
+  s.n_rooms = rooms;
+  s.room_rows = rooms == 0 ? 0 : short_rows > long_rows ? short_rows : long_rows;
+  s.rooms = off;
+  off = round_up(off + room_bytes(s.room_rows, c->head_dim) * rooms);
   s.total = off;
   return s;
 }
 
 // The layout of `c` in at most `limit` bytes: the default one if it fits,
-// else without the room for splits and with as many stream-mode partial rows
-// as the rest leaves (possibly none: short passes then run the plain kernel).
+// else with fewer streams' rooms, else with none and as many rows in the shared
+// one as the rest leaves (possibly none: short passes then run the plain kernel).
 // false if even that exceeds `limit`.
 bool layout_within(const hermes_config *c, size_t limit, Layout *out) {
-  for (int slots = kAppendSlots; slots >= 0; --slots) {
-    const Layout full = layout_of(c, -1, slots);
+  for (int rooms = kStreamRooms; rooms >= 0; --rooms) {
+    const Layout full = layout_of(c, -1, rooms);
     if (full.total <= limit) {
       *out = full;
       return true;
@@ -198,8 +201,9 @@ bool layout_within(const hermes_config *c, size_t limit, Layout *out) {
 // 35 / 34, 196 on 1024 24 / 17 / 10 / 7 / 12 (14 and 2 of 64).  28 layers of
 // 2048..6144 tokens: one row 57 with eight key groups, 50 stream, 43 split; 16
 // rows 79 stream, 63 split; 64 rows 175 with one key group, 152 stream.
-// Fills key_groups, split and the st_* fields (st_units = 0: the plain kernel).
-void attention_plan(AttnArgs &at, int n_rows, int G, int Hkv, int n_list, int D, int64_t part_rows) {
+// Fills key_groups, split and the st_* fields (st_units = 0: the plain kernel)
+// and returns the estimate.
+double attention_plan(AttnArgs &at, int n_rows, int G, int Hkv, int n_list, int D, int64_t part_rows) {
   const int64_t P = (int64_t)n_rows * G;
   const int64_t pairs = (int64_t)n_list * Hkv;
   at.key_groups = 1;
@@ -231,7 +235,7 @@ void attention_plan(AttnArgs &at, int n_rows, int G, int Hkv, int n_list, int D,
       at.key_groups = 1 << e;
     }
   }
-  if (total > INT32_MAX / 2) return;
+  if (total > INT32_MAX / 2) return best;
   const double mb = 32e-6 * at.part_groups * 4 * (D + 2);   // of one partial block
   const int64_t most = part_rows / (32 * (int64_t)at.part_groups);
   const int plain_groups = at.key_groups;
@@ -306,6 +310,7 @@ void attention_plan(AttnArgs &at, int n_rows, int G, int Hkv, int n_list, int D,
     at.e[n_list].st_off = (int32_t)off;
     at.st_units = (int32_t)range;
   }
+  return best;
 }
 
 // Query-row splits of a mass sweep of n_list layers of at most max_T
@@ -388,13 +393,11 @@ struct hermes_ctx {
   int static_dev = -1;  // device whose static scratch is the workspace (-1: the caller's)
   std::vector<EventPair> used[HERMES_K_COUNT];
   std::vector<EventPair> pool;
-  // Partial rows of appends belong to the stream that first took the slot, for
-  // the context's life: calls on one stream follow each other, and layers
-  // appended on different streams never share them (streams beyond the slots,
-  // the per-thread default stream, whose handle names a stream of each thread,
-  // and captured calls, which may be replayed on any stream, run without).
-  hipStream_t slot_stream[kAppendSlots] = {};
-  bool slot_taken[kAppendSlots] = {};
+  // A room of partial rows belongs to the stream that first has a call cut in
+  // it, for the context's life: calls on one stream follow each other, and those
+  // on different streams never share a room.
+  hipStream_t room_stream[kStreamRooms] = {};
+  bool room_taken[kStreamRooms] = {};
 
   AttnEntry attn_entry(int l, int slot) const {
     const int c = cur[l];
@@ -407,11 +410,17 @@ struct hermes_ctx {
                      (int8_t)slot, (int8_t)alpha, 0};
   }
 
-  int append_slot(hipStream_t s) const {
+  // The room that is stream s's, or that it could take (-1: none).  The
+  // per-thread default stream, whose handle names a stream of each thread, has
+  // none.
+  int room_of(hipStream_t s) const {
     if (s == hipStreamPerThread) return -1;
-    for (int i = 0; i < lay.append_slots; ++i)
-      if (!slot_taken[i] || slot_stream[i] == s) return i;
-    return -1;
+    int free_room = -1;
+    for (int i = lay.n_rooms - 1; i >= 0; --i) {
+      if (room_taken[i] && room_stream[i] == s) return i;
+      if (!room_taken[i]) free_room = i;
+    }
+    return free_room;
   }
   static bool capturing(hipStream_t s) {   // (or not known to be no capture)
     if (s == nullptr) return false;
@@ -420,43 +429,36 @@ struct hermes_ctx {
     (void)hipGetLastError();
     return true;
   }
-  bool take_slot(int i, hipStream_t s) {
-    if (capturing(s)) return false;
-    slot_taken[i] = true;
-    slot_stream[i] = s;
-    return true;
-  }
 
-  // The query room (opart, mlpart) likewise belongs to the stream that first
-  // takes it; queries and prompts on another stream use its append room.  Where
-  // a stream has neither, passes of up to kSplitMaxTokens rows share the query
-  // room, so they have to follow each other on the device, and longer ones run
-  // without.
-  hipStream_t query_stream = nullptr;
-  bool query_taken = false;
-
-  void query_plan(AttnArgs &at, int n_rows, int n, hipStream_t s) {
-    auto plan = [&](int64_t rows, size_t o, size_t ml, int64_t first) {
-      attention_plan(at, n_rows, Hq / Hkv, Hkv, n, D, rows);
-      at.opart = reinterpret_cast<float *>(ws + o) + first * D;
-      at.mlpart = reinterpret_cast<float *>(ws + ml) + first * 2;
+  // Cuts one call's attention pass of n_rows rows over the entries of `at`.
+  // captured() tells whether the call is recorded: it may then be replayed on
+  // any stream, so no room is its own.  Passes without a room run uncut, or,
+  // where they are short (queries and prompts of up to kSplitMaxTokens rows) and
+  // the cut saves a tenth, share one that no other pass touches: those have to
+  // follow each other on the device, and nothing else has to.
+  template <typename F>
+  void cut(AttnArgs &at, int n_rows, int n, bool may_share, hipStream_t s, F &&captured) {
+    auto plan = [&](int64_t rows, size_t base) {
+      const double cost = attention_plan(at, n_rows, Hq / Hkv, Hkv, n, D, rows);
+      at.opart = reinterpret_cast<float *>(ws + base);
+      at.mlpart = reinterpret_cast<float *>(ws + base + round_up(sizeof(float) * (size_t)rows * D));
+      return cost;
     };
-    plan(lay.part_rows, lay.opart, lay.mlpart, 0);
-    if (at.st_units == 0) return;
-    const bool once = s == hipStreamPerThread || capturing(s);   // no stream that a room could belong to
-    if (!once && (!query_taken || query_stream == s)) {
-      query_taken = true;
-      query_stream = s;
-      return;
+    const int room = room_of(s);
+    if (room >= 0) {
+      plan(lay.room_rows, lay.rooms + room * room_bytes(lay.room_rows, D));
+      if (at.st_units == 0) return;
+      if (!captured()) {
+        room_taken[room] = true;
+        room_stream[room] = s;
+        return;
+      }
     }
-    const int slot = once ? -1 : append_slot(s);
-    if (slot >= 0) {
-      slot_taken[slot] = true;
-      slot_stream[slot] = s;
-      plan(lay.append_rows, lay.aopart, lay.amlpart, slot * lay.append_rows);
-    } else if (n_rows > kSplitMaxTokens) {
-      plan(0, lay.opart, lay.mlpart, 0);
-    }
+    const double uncut = plan(0, lay.shared);
+    if (may_share && n_rows <= kSplitMaxTokens && plan(lay.shared_rows, lay.shared) > 0.9 * uncut) plan(0, lay.shared);
+  }
+  void cut(AttnArgs &at, int n_rows, int n, bool may_share, hipStream_t s) {
+    cut(at, n_rows, n, may_share, s, [&] { return capturing(s); });
   }
 
   int prof_begin(int id, hipStream_t s, EventPair *ep) {
@@ -909,15 +911,7 @@ static int append_impl(hermes_ctx *ctx, int32_t layer, const void *q, const void
     }
   }
 
-  {
-    const int n = (int)list.size(), G = ctx->Hq / ctx->Hkv;
-    const int slot = ctx->append_slot(s);
-    attention_plan(at, n_new, G, ctx->Hkv, n, ctx->D, slot < 0 ? 0 : ctx->lay.append_rows);
-    if (at.st_units > 0 && !ctx->take_slot(slot, s)) attention_plan(at, n_new, G, ctx->Hkv, n, ctx->D, 0);
-    const int64_t first = slot < 0 ? 0 : slot * ctx->lay.append_rows;
-    at.opart = reinterpret_cast<float *>(ctx->ws + ctx->lay.aopart) + first * ctx->D;
-    at.mlpart = reinterpret_cast<float *>(ctx->ws + ctx->lay.amlpart) + first * 2;
-  }
+  ctx->cut(at, n_new, (int)list.size(), false, s);
   // (the attention launch copies the new rows too: the class keeps its count)
   int rc = ctx->run(HERMES_K_APPEND, s, [] { return hipSuccess; });
   if (rc != HERMES_OK) return rc;
@@ -1030,7 +1024,7 @@ int hermes_guidance_score(hermes_ctx *ctx, int32_t layer, const void *q, const v
   }
   const int n = (int)list.size();
   mass_splits(cs, n, max_T, ctx->lay.wpart_lstride);
-  ctx->query_plan(at, n_rows, n, s);
+  ctx->cut(at, n_rows, n, true, s);
   const int rc = ctx->run(HERMES_K_GUIDE, s, [&] {
     hipError_t e = at.st_units > 0 ? launch_attention_parted(at, n, ctx->D, s)
                                    : launch_attention(at, n, ctx->D, s);
@@ -1271,7 +1265,7 @@ int hermes_query_attend(hermes_ctx *ctx, int32_t layer, const void *q, const voi
     at.e[n] = ctx->attn_entry(l, layer == HERMES_ALL_LAYERS ? l : 0);
     ++n;
   }
-  ctx->query_plan(at, n_q, n, s);
+  ctx->cut(at, n_q, n, true, s);
   return ctx->run(HERMES_K_QUERY, s, [&] {
     return at.st_units > 0 ? launch_attention_parted(at, n, ctx->D, s)
                            : launch_attention(at, n, ctx->D, s);
@@ -1317,3 +1311,44 @@ int hermes_profile_read(hermes_ctx *ctx, int kernel_id, double *ms_total, int64_
 }
 
 }  // extern "C"
+
+// ---------------------------------------------------------------------------
+// Host-only view of how calls are cut (hermes_internal.h), for tests.
+// ---------------------------------------------------------------------------
+extern "C" int hermes_plan_probe(const hermes_config *cfg, size_t limit, const PlanCall *calls, int n_calls,
+                                 PlanInfo *out) {
+  if (check_config(cfg) != HERMES_OK || calls == nullptr || out == nullptr) return HERMES_EINVAL;
+  hermes_ctx c;
+  c.L = cfg->n_layers;
+  c.Hq = cfg->n_q_heads;
+  c.Hkv = cfg->n_kv_heads;
+  c.D = cfg->head_dim;
+  if (limit == 0) c.lay = layout_of(cfg);
+  else if (!layout_within(cfg, limit, &c.lay)) return HERMES_ECAPACITY;
+  c.ws = reinterpret_cast<char *>(kAlign);   // (no memory: only offsets are looked at)
+  for (int i = 0; i < n_calls; ++i) {
+    const PlanCall &call = calls[i];
+    if (call.n_rows < 1 || call.layer < HERMES_ALL_LAYERS || call.layer >= c.L) return HERMES_EINVAL;
+    AttnArgs at;
+    std::memset(&at, 0, sizeof(at));
+    int n = 0;
+    for (int l = 0; l < c.L; ++l)
+      if (call.layer == HERMES_ALL_LAYERS || call.layer == l) at.e[n++].T0 = call.len[l];
+    at.out = call.kind == PLAN_PROMPT ? nullptr : reinterpret_cast<uint16_t *>(c.ws);
+    c.cut(at, call.n_rows, n, call.kind != PLAN_APPEND, reinterpret_cast<hipStream_t>(call.stream),
+          [&] { return call.captured != 0; });
+    PlanInfo &o = out[i];
+    const int64_t blocks = at.st_units == 0 ? 0 : at.split ? at.e[n].st_off : at.st_units + (int64_t)n * c.Hkv - 1;
+    o.key_groups = at.key_groups;
+    o.mode = at.st_units == 0 ? 0 : at.split ? 2 : 1;
+    o.four_waves = at.split == 1;
+    o.units = at.st_units;
+    o.rows = blocks * at.part_groups * 32;
+    o.o_lo = reinterpret_cast<char *>(at.opart) - c.ws;
+    o.o_hi = o.o_lo + (int64_t)sizeof(float) * o.rows * c.D;
+    o.ml_lo = reinterpret_cast<char *>(at.mlpart) - c.ws;
+    o.ml_hi = o.ml_lo + (int64_t)sizeof(float) * 2 * o.rows;
+    o.total = c.lay.total;
+  }
+  return HERMES_OK;
+}

@@ -268,11 +268,29 @@ constexpr int kColsumKeysPerBlock = 256; // candidates per workgroup of the swee
 constexpr int kMassSplitMax = 32;       // ranges a sweep's query rows are cut into at most
 constexpr int64_t kMassPartials = 1024 * 256;   // fp64 partials a layer keeps for them
 constexpr int kSummaryRows = 128;        // candidates per workgroup of the summary sums
-constexpr int kSplitMaxTokens = 64;      // rows of a query or prompt that the workspace holds the stream state of
-constexpr int64_t kAppendPartRows = 131072;  // partial rows of appends at most (68 MB at head size 128),
-constexpr int kAppendSlots = 2;              // for each of this many streams
+constexpr int kSplitMaxTokens = 64;      // rows of a query or prompt that may share a room of partial rows
+constexpr int64_t kRoomRows = 131072;    // partial rows of a stream's longer passes at most (68 MB at head size 128)
+constexpr int kStreamRooms = 3;          // streams with a room of their own
 constexpr int kStreamSlots = 256;        // resident attention workgroups (one per CU)
 constexpr int kSplitRows = 128;          // packed rows of a split-mode workgroup at most
 constexpr int kNormBlock = 256;         // candidates per fp64 partial of the score normaliser
+
+// How a context cuts calls, worked out on the host alone (no device, no
+// launches): for tests.  limit: bytes of workspace (0: what the configuration
+// asks for).  The calls are taken in order, as one context would see them.
+enum { PLAN_APPEND = 0, PLAN_QUERY = 1, PLAN_PROMPT = 2 };
+struct PlanCall {
+  int32_t kind, n_rows, layer, captured;
+  uint64_t stream;          // the stream's handle (0: the null stream)
+  const int32_t *len;       // [n_layers] cached rows of every layer
+};
+struct PlanInfo {
+  int32_t key_groups, mode, four_waves, units;   // mode 0 plain, 1 stream, 2 split
+  int64_t rows;             // partial rows the pass may write
+  int64_t o_lo, o_hi, ml_lo, ml_hi;   // and where, as bytes of the workspace
+  int64_t total;            // bytes of the layout
+};
+extern "C" int hermes_plan_probe(const hermes_config *cfg, size_t limit, const PlanCall *calls, int n_calls,
+                                 PlanInfo *out);
 
 }  // namespace hermes

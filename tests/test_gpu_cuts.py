@@ -75,9 +75,9 @@ def test_query_cuts_match_oracle(name, L, Hq, Hkv, d, lens, rows):
 
 @pytest.mark.parametrize("rows", [64, 100])
 def test_queries_on_several_streams_match_oracle(rows):
-    """Layers queried at the same time on four streams of one context: a stream
-    with no room for partial rows of its own takes another cut (at 64 rows such
-    streams share a room, so they wait for each other here)."""
+    """Layers queried at the same time on four streams of one context: three have
+    a room for partial rows, the fourth takes the shared one (64 rows) or another
+    cut."""
     from paper_2601_14724_amd import hermes as H
     L, Hq, Hkv, d, n = 4, 14, 2, 64, 3000
     say(f"[cuts] queries of {rows} rows on {L} streams")
@@ -95,16 +95,81 @@ def test_queries_on_several_streams_match_oracle(rows):
     streams = [torch.cuda.Stream() for _ in range(L)]
     for _ in range(4):
         for l, s in enumerate(streams):
-            if rows <= 64 and l > 0:
-                s.wait_stream(streams[l - 1])
             with torch.cuda.stream(s):
                 kv.query(t["q"][l], t["k"][l], t["v"][l], layer=l, out=out[l])
-        if rows <= 64:
-            streams[0].wait_stream(streams[-1])
     torch.cuda.synchronize()
     for l, (c, q) in enumerate(host):
         o, _ = orc.chunk_attention(f64(q["q"]), f64(c["k"]), f64(c["v"]), f64(q["k"]), f64(q["v"]), want_w=False)
         check_o(out[l].float().cpu().numpy(), o, f"[cuts] query of {rows} rows, stream {l}")
+    kv.close()
+
+
+def test_captured_query_beside_a_longer_one_matches_oracle():
+    """A recorded one-row query replayed on one stream while 100-row queries run
+    on another: the recorded one's partial rows have a room that the other stream
+    never writes."""
+    from paper_2601_14724_amd import hermes as H
+    Hq, Hkv, d, n, rows = 28, 4, 128, 4096, (100, 1)
+    say("[cuts] captured query of 1 row beside queries of 100")
+    init, host = [], []
+    for l in range(2):
+        wl = wk.custom("captured", 600 + l, 2, Hq, Hkv, d, n, 1, (n,) * 2, query_len=rows[l], anchor_period=29)
+        c, q = wk.gen_cache(wl, l), wk.gen_query(wl, l)
+        host.append((c, q))
+        init.append((streaming.bf16_tensor(c["k"], "cuda"), streaming.bf16_tensor(c["v"], "cuda"),
+                     torch.from_numpy(c["pos"]).cuda()))
+    kv = H.HermesKV(2, Hq, Hkv, d, [n] * 2, 100, init=init)
+    t = [{k: streaming.bf16_tensor(q[k], "cuda") for k in ("q", "k", "v")} for _, q in host]
+    out = [torch.zeros(40, *t[l]["q"].shape, dtype=torch.bfloat16, device="cuda") for l in range(2)]
+    short = torch.zeros_like(t[1]["q"])
+    a, b = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(a):
+        kv.query(t[0]["q"], t[0]["k"], t[0]["v"], layer=0, out=out[0][0])
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=b):
+        kv.query(t[1]["q"], t[1]["k"], t[1]["v"], layer=1, out=short)
+    for i in range(40):
+        with torch.cuda.stream(a):
+            kv.query(t[0]["q"], t[0]["k"], t[0]["v"], layer=0, out=out[0][i])
+        with torch.cuda.stream(b):
+            graph.replay()
+            out[1][i].copy_(short)
+    torch.cuda.synchronize()
+    for l, (c, q) in enumerate(host):
+        o, _ = orc.chunk_attention(f64(q["q"]), f64(c["k"]), f64(c["v"]), f64(q["k"]), f64(q["v"]), want_w=False)
+        check_o(out[l][0].float().cpu().numpy(), o, f"[cuts] query of {rows[l]} rows")
+        assert (out[l] == out[l][0]).all(), f"{rows[l]} rows: a pass differs from the first"
+    kv.close()
+
+
+def test_appends_on_four_streams_match_oracle():
+    """Layers appended at the same time on four streams: three have a room for
+    partial rows, the fourth runs another cut; outputs and W."""
+    L, Hq, Hkv, d, T0, C = 4, 14, 2, 64, 3000, 196
+    say(f"[cuts] appends of {C} rows on {L} streams")
+    wl = wk.custom("append_streams", 700, L, Hq, Hkv, d, T0, C, (T0 + C,) * L, anchor_period=37)
+    caches, chunks = gen(wl)
+    kv = streaming.make_cache(wl, caches=caches, force_scores=True, layer_class=[2] * L)
+    t = streaming.chunk_tensors({k: np.stack([c[k] for c in chunks]) for k in ("q", "k", "v")} |
+                                {"pos": chunks[0]["pos"]})
+    out = torch.zeros_like(t["q"])
+    streams = [torch.cuda.Stream() for _ in range(L)]
+    for _ in range(4):
+        torch.cuda.synchronize()
+        kv.rewind()
+        for l, s in enumerate(streams):
+            with torch.cuda.stream(s):
+                kv.append(t["q"][l], t["k"][l], t["v"][l], t["pos"], layer=l, out=out[l])
+    torch.cuda.synchronize()
+    oc = oracle_caches(caches)
+    for l in range(L):
+        k, v = f64(chunks[l]["k"]), f64(chunks[l]["v"])
+        o, wr = orc.chunk_attention(f64(chunks[l]["q"]), oc[l].k.reshape(T0, Hkv, d), oc[l].v.reshape(T0, Hkv, d), k, v)
+        check_o(out[l].float().cpu().numpy(), o, f"[cuts] append on stream {l}")
+        rel = float((np.abs(kv.w[l][:T0 + C].cpu().numpy().astype(np.float64) - wr) / wr).max())
+        assert rel <= 1e-3, f"stream {l}: mass off by {rel}"
     kv.close()
 
 

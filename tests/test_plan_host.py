@@ -1,0 +1,139 @@
+"""How calls are cut into workgroups and where their partial results go, worked
+out by the library on the host (no device): which cut a shape takes, that the
+partial rows stay inside the room they were given, and that calls which may run
+at the same time never share a room."""
+import ctypes
+import random
+
+import pytest
+
+from paper_2601_14724_amd import hermes as H
+
+APPEND, QUERY, PROMPT = 0, 1, 2
+PLAIN, STREAM, SPLIT = 0, 1, 2
+
+
+class Call(ctypes.Structure):
+    _fields_ = [("kind", ctypes.c_int32), ("n_rows", ctypes.c_int32), ("layer", ctypes.c_int32),
+                ("captured", ctypes.c_int32), ("stream", ctypes.c_uint64), ("len", ctypes.POINTER(ctypes.c_int32))]
+
+
+class Info(ctypes.Structure):
+    _fields_ = [("key_groups", ctypes.c_int32), ("mode", ctypes.c_int32), ("four_waves", ctypes.c_int32),
+                ("units", ctypes.c_int32)] + [(n, ctypes.c_int64) for n in
+                                              ("rows", "o_lo", "o_hi", "ml_lo", "ml_hi", "total")]
+
+
+H.lib.hermes_plan_probe.argtypes = [ctypes.POINTER(H.HermesConfig), ctypes.c_size_t, ctypes.POINTER(Call),
+                                    ctypes.c_int, ctypes.POINTER(Info)]
+
+
+def config(layers, hq, hkv, d, cap, chunk, **over):
+    cfg = H.HermesConfig()
+    cfg.n_layers, cfg.n_q_heads, cfg.n_kv_heads, cfg.head_dim = layers, hq, hkv, d
+    cfg.max_chunk, cfg.max_cap = chunk, cap
+    cfg._keep = (ctypes.c_int32 * layers)(*([min(cap, 64)] * layers))
+    cfg.budget = ctypes.cast(cfg._keep, ctypes.POINTER(ctypes.c_int32))
+    cfg.omega0, cfg.gamma = 0.75, 0.6
+    for k, v in over.items():
+        setattr(cfg, k, v)
+    return cfg
+
+
+def plan(cfg, calls, limit=0):
+    """calls: (kind, rows, layer, cached rows of the layers, stream, captured)."""
+    cs = (Call * len(calls))()
+    keep = []
+    for c, (kind, rows, layer, lens, stream, captured) in zip(cs, calls):
+        arr = (ctypes.c_int32 * cfg.n_layers)(*lens)
+        keep.append(arr)
+        c.kind, c.n_rows, c.layer, c.captured, c.stream = kind, rows, layer, captured, stream
+        c.len = ctypes.cast(arr, ctypes.POINTER(ctypes.c_int32))
+    out = (Info * len(calls))()
+    assert H.lib.hermes_plan_probe(ctypes.byref(cfg), limit, cs, len(calls), out) == H.OK
+    return list(out)
+
+
+def apart(a, b):
+    def meet(x, y):
+        return x[0] < y[1] and y[0] < x[1]
+    spans = [[(p.o_lo, p.o_hi), (p.ml_lo, p.ml_hi)] for p in (a, b)]
+    return not any(meet(x, y) for x in spans[0] for y in spans[1])
+
+
+SEVEN = (4, 28, 4, 128)   # 4 layers at the 7B shape
+
+
+def test_a_captured_short_query_keeps_out_of_a_long_ones_room():
+    """100 rows on the context's first stream beside a replayed one-row graph."""
+    cfg, lens = config(*SEVEN, 9000, 784), [4096] * 4
+    long_, short = plan(cfg, [(QUERY, 100, 0, lens, 8, 0), (QUERY, 1, 1, lens, 16, 1)])
+    assert long_.rows > 0 and short.rows > 0
+    assert apart(long_, short)
+
+
+@pytest.mark.parametrize("rows", [1, 16, 64, 65, 100, 784])
+def test_streams_never_share_a_room(rows):
+    """Queries, appends and prompts of one to five streams: those of a stream
+    may meet each other, those of two streams never, and a captured or further
+    stream's short ones share a room that none of the others touch."""
+    cfg, lens = config(*SEVEN, 9000, 784), [4096] * 4
+    for owner_rows in (1, 64, 100, 784):
+        calls = [(QUERY, 100, 0, lens, s, 0) for s in (8, 16, 24)]   # (cut: each takes a room)
+        calls += [(k, owner_rows if s < 32 else rows, s // 8 - 1 if s < 40 else 3, lens, s, 0)
+                 for s in (8, 16, 24, 32, 40) for k in (QUERY, APPEND, PROMPT)]
+        calls += [(QUERY, rows, 0, lens, 8, 1), (APPEND, rows, 0, lens, 8, 1)]
+        got = plan(cfg, calls)
+        for (ka, ra, _, _, sa, xa), a in zip(calls, got):
+            for (kb, rb, _, _, sb, xb), b in zip(calls, got):
+                if (sa, xa) == (sb, xb):
+                    continue
+                share = all((x or s > 24) and k != APPEND and r <= 64
+                            for k, r, s, x in ((ka, ra, sa, xa), (kb, rb, sb, xb)))
+                assert share or apart(a, b), (ka, ra, sa, xa, kb, rb, sb, xb)
+        assert all(p.rows == 0 for (k, r, _, _, s, x), p in zip(calls, got) if (x or s > 24) and (k == APPEND or r > 64))
+
+
+def test_a_call_that_is_not_cut_takes_no_room():
+    """Short caches need no cut, so streams that only see those leave the rooms
+    to the streams that do."""
+    cfg, few, many = config(*SEVEN, 9000, 784), [64] * 4, [8000] * 4
+    calls = [(QUERY, 1, 0, few, s, 0) for s in (8, 16, 24)] + [(APPEND, 196, l, many, 32 + 8 * l, 0) for l in range(3)]
+    got = plan(cfg, calls)
+    assert all(p.rows == 0 for p in got[:3]) and all(p.rows > 0 for p in got[3:])
+    assert apart(got[3], got[4]) and apart(got[3], got[5]) and apart(got[4], got[5])
+
+
+def test_the_per_thread_default_stream_has_no_room():
+    cfg, lens = config(*SEVEN, 9000, 784), [4096] * 4
+    got = plan(cfg, [(QUERY, 100, 0, lens, 2, 0), (APPEND, 196, 0, lens, 2, 0), (QUERY, 1, 0, lens, 2, 0)])
+    assert got[0].rows == 0 and got[1].rows == 0
+    assert apart(got[2], plan(cfg, [(QUERY, 1, 0, lens, 8, 0)])[0])
+
+
+def test_partial_rows_stay_in_their_room():
+    """Random shapes, lengths, streams and workspace limits: every pass's partial
+    rows lie inside the workspace, and O and (max, sum) never meet."""
+    rng = random.Random(5)
+    for _ in range(400):
+        layers, hkv = rng.choice((1, 2, 7, 28, 64)), rng.choice((1, 2, 3, 4, 8, 16))
+        g, d, chunk = rng.choice((1, 2, 7, 16)), rng.choice((64, 128)), rng.choice((1, 9, 64, 200, 784, 3136))
+        cap = chunk + int(2 ** rng.uniform(0, 14))
+        cfg = config(layers, hkv * g, hkv, d, cap, chunk)
+        limit = rng.choice((0, 64 << 20, 128 << 20))
+        calls = []
+        for _ in range(8):
+            kind = rng.choice((APPEND, QUERY, PROMPT))
+            lens = [rng.randint(0, cap - chunk) for _ in range(layers)]
+            calls.append((kind, rng.randint(1, chunk), rng.choice((-1, rng.randrange(layers))), lens,
+                          rng.choice((0, 8, 16, 24, 32)), rng.randint(0, 1)))
+        try:
+            got = plan(cfg, calls, limit)
+        except AssertionError:
+            assert limit   # even the rest exceeds it
+            continue
+        for p in got:
+            assert p.key_groups in (1, 2, 4, 8) and (p.rows > 0) == (p.mode != PLAIN)
+            if p.rows:
+                assert 0 <= p.o_lo < p.o_hi <= p.ml_lo < p.ml_hi <= p.total
+                assert limit == 0 or p.total <= limit
