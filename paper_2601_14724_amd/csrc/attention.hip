@@ -160,8 +160,11 @@ __device__ __forceinline__ void copy_share(const AttnArgs &a, int D, int id, int
 // and by latency where a CU has little to read: it takes workgroups of four
 // waves, two a CU, so that one's start and end hide behind the other's loads.
 enum { PLAIN = 0, STREAMED = 1, SPLIT = 2 };
+// (WRITE_O false: at head size 64, and with four key groups, 128 registers are
+// enough without spilling and two workgroups fit a CU)
 template <int D, int NW, int KG, int MODE, bool WRITE_O>
-__global__ __launch_bounds__(64 * NW, NW == 8 ? 1 : 2) void attn_fwd(AttnArgs a, int nqt) {
+__global__ __launch_bounds__(64 * NW, NW != 8 ? 2 : !WRITE_O && (D == 64 || KG == 4) ? 4 : 1)
+void attn_fwd(AttnArgs a, int nqt) {
   constexpr bool STREAM = MODE == STREAMED;
   constexpr int RG = NW / KG;               // 32-row groups (waves of a key group)
   constexpr int BM = 32 * RG;               // packed rows of the workgroup
@@ -265,10 +268,14 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 1 : 2) void attn_fwd(AttnArgs a,
   // transposed by ds_read_b64_tr_b16.  Row pads keep the K reads (16 B per
   // lane) and the transposed V reads (4 rows x 32 B per 16 lanes) spread
   // over the LDS banks.
-  __shared__ __attribute__((aligned(16))) uint16_t tiles[KG * NBUF * BN * (2 * D + KPAD + VPAD)];
+  // A pass for the row LSE alone has no V tiles: 200 rows on 28 layers of 2 K to 6 K
+  // tokens (16 KV heads), 267 us with V loaded and stored all the same, 208 now;
+  // two, four and eight key groups 335 / 504 / 531 and 229 / 214 / 302.
+  __shared__ __attribute__((aligned(16)))
+  uint16_t tiles[KG * NBUF * BN * (D + KPAD + (WRITE_O ? D + VPAD : 0))];
   uint16_t(*Ks)[BN][D + KPAD] = reinterpret_cast<uint16_t(*)[BN][D + KPAD]>(tiles) + kg * NBUF;
   uint16_t(*Vs)[BN][D + VPAD] =
-      reinterpret_cast<uint16_t(*)[BN][D + VPAD]>(tiles + KG * NBUF * BN * (D + KPAD)) + kg * NBUF;
+      reinterpret_cast<uint16_t(*)[BN][D + VPAD]>(tiles + (WRITE_O ? KG * NBUF * BN * (D + KPAD) : 0)) + kg * NBUF;
   uint4 kreg[NLD], vreg[NLD];
   // Tiles load through buffer descriptors whose base is the tile's first row
   // (scalar arithmetic): each load is the descriptor plus the lane's 32-bit
@@ -282,9 +289,11 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 1 : 2) void attn_fwd(AttnArgs a,
 #pragma unroll
     for (int uu = 0; uu < NLD; ++uu) {
       const auto kx = __builtin_amdgcn_raw_buffer_load_b128(kr, (int)cofs, uu * cstep, 0);
-      const auto vx = __builtin_amdgcn_raw_buffer_load_b128(vr, (int)cofs, uu * cstep, 0);
       kreg[uu] = uint4{kx[0], kx[1], kx[2], kx[3]};
-      vreg[uu] = uint4{vx[0], vx[1], vx[2], vx[3]};
+      if constexpr (WRITE_O) {
+        const auto vx = __builtin_amdgcn_raw_buffer_load_b128(vr, (int)cofs, uu * cstep, 0);
+        vreg[uu] = uint4{vx[0], vx[1], vx[2], vx[3]};
+      }
     }
   };
   // Any tile: the descriptor ends with the tile's last row, so that rows past
@@ -302,9 +311,11 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 1 : 2) void attn_fwd(AttnArgs a,
 #pragma unroll
     for (int uu = 0; uu < NLD; ++uu) {
       const auto kx = __builtin_amdgcn_raw_buffer_load_b128(kr, (int)cofs + uu * cstep, 0, 0);
-      const auto vx = __builtin_amdgcn_raw_buffer_load_b128(vr, (int)cofs + uu * cstep, 0, 0);
       kreg[uu] = uint4{kx[0], kx[1], kx[2], kx[3]};
-      vreg[uu] = uint4{vx[0], vx[1], vx[2], vx[3]};
+      if constexpr (WRITE_O) {
+        const auto vx = __builtin_amdgcn_raw_buffer_load_b128(vr, (int)cofs + uu * cstep, 0, 0);
+        vreg[uu] = uint4{vx[0], vx[1], vx[2], vx[3]};
+      }
     }
   };
   // tile t holds a key that some row of the block does not see
@@ -317,7 +328,7 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 1 : 2) void attn_fwd(AttnArgs a,
       const int e = tid + uu * GT;
       const int kr = e / CH, ch = e % CH;
       *reinterpret_cast<uint4 *>(&Ks[b][kr][ch * 8]) = kreg[uu];
-      *reinterpret_cast<uint4 *>(&Vs[b][kr][ch * 8]) = vreg[uu];
+      if constexpr (WRITE_O) *reinterpret_cast<uint4 *>(&Vs[b][kr][ch * 8]) = vreg[uu];
     }
   };
 
@@ -397,8 +408,10 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 1 : 2) void attn_fwd(AttnArgs a,
       m_run = m_new;
       m_lim = (m_run + 8.f) * inv_c;
       l_run *= alpha;
+      if constexpr (WRITE_O) {
 #pragma unroll
-      for (int db = 0; db < D / 32; ++db) o[db] *= alpha;
+        for (int db = 0; db < D / 32; ++db) o[db] *= alpha;
+      }
     }
 
     bf16x8 pf[2 * SUB];
@@ -413,6 +426,7 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 1 : 2) void attn_fwd(AttnArgs a,
       }
     }
     l_run += ls;
+    if constexpr (!WRITE_O) return;
 
     // O^T += V^T P^T.  B element t of lane half hf in key group qq is key
     // 16 qq + 8 (t/4) + 4 hf + t%4; two transposed reads give the matching
@@ -517,9 +531,10 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 1 : 2) void attn_fwd(AttnArgs a,
 #pragma unroll
       for (int c = 0; c < NC; ++c) fn(c, own(c));
     } else {
-      static_assert(NC % KG == 0 && (NW * NC * 64 * 16 + NW * 32 * 8) <= (int)sizeof(tiles), "merge state fits");
+      static_assert(NC % KG == 0 && ((WRITE_O ? NW * NC * 64 * 16 : 0) + NW * 32 * 8) <= (int)sizeof(tiles),
+                    "merge state fits");
       float4 *mo = reinterpret_cast<float4 *>(tiles);
-      float2 *mm = reinterpret_cast<float2 *>(mo + NW * NC * 64);
+      float2 *mm = reinterpret_cast<float2 *>(mo + (WRITE_O ? NW * NC * 64 : 0));
       __syncthreads();   // all tiles are read
       if constexpr (WRITE_O) {
 #pragma unroll
