@@ -742,9 +742,13 @@ template <int D>
 __global__ __launch_bounds__(256, 3) void attn_colsum(ColsumArgs a, int nkb) {
   const int lin = xcd_remap(blockIdx.x, gridDim.x);
   const int kblk = lin % nkb;
-  const int split = (lin / nkb) % a.splits;
-  const int kv_blk = (lin / (nkb * a.splits)) % a.Hkv;
-  const int j = lin / (nkb * a.splits * a.Hkv);
+  int group = lin / nkb, split = 0;
+  if (a.splits > 1) {
+    split = group % a.splits;
+    group /= a.splits;
+  }
+  const int kv_blk = group % a.Hkv;
+  const int j = group / a.Hkv;
   const MassEntry &en = a.e[j];
   const int layer = en.layer;
   const int T0 = en.T0;
@@ -771,9 +775,15 @@ __global__ __launch_bounds__(256, 3) void attn_colsum(ColsumArgs a, int nkb) {
   const int p_first = (k0 < T0 ? 0 : (k0 - T0) * G) & ~(BQS - 1);
   const int ntq = (P - p_first + BQS - 1) / BQS;
   // this split's share of the block's query tiles (possibly none: it then
-  // writes zeros)
-  const int t_lo = (int)((int64_t)split * ntq / a.splits);
-  const int nit = (int)((int64_t)(split + 1) * ntq / a.splits) - t_lo;
+  // writes zeros); at most 32 splits of 2^25 tiles, so 32 bits hold the products
+  // (two 64-bit divisions in every workgroup, split or not, and a branch before
+  // the first tile's loads: 273 us, 259 now, 28 layers of 3 K to 7 K tokens, 16 KV
+  // heads, 200 prompt rows)
+  int t_lo = 0, nit = ntq;
+  if (a.splits > 1) {
+    t_lo = split * ntq / a.splits;
+    nit = (split + 1) * ntq / a.splits - t_lo;
+  }
   const int p_begin = p_first + t_lo * BQS;
 
   const int slot = en.slot;
@@ -905,10 +915,8 @@ __global__ __launch_bounds__(256, 3) void attn_colsum(ColsumArgs a, int nkb) {
   using Edge = std::integral_constant<bool, false>;
   // tiles [0, nfull) lie wholly below P
   const int nfull = min(nit, (P - p_begin) / BQS);
-  if (nit > 0) {
-    load_tile(0, Edge{});
-    store_tile(0);
-  }
+  load_tile(0, Edge{});   // (a split with no tile loads one too, so that no branch parts this from the K loads)
+  store_tile(0);
   if (nit > 1) {
     load_tile(1, Edge{});
     store_tile(1);
