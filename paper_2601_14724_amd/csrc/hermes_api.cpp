@@ -214,7 +214,7 @@ double attention_plan(AttnArgs &at, int n_rows, int G, int Hkv, int n_list, int 
   int64_t total = 0;
   int max_tiles = 1;
   for (int j = 0; j < n_list; ++j) {
-    const int tiles = (at.e[j].T0 + 63) / 64 + (n_rows + 63) / 64;
+    const int tiles = (at.e[j].T0 + n_rows + 63) / 64;
     at.e[j].st_tiles = tiles;
     at.e[j].st_off = (int32_t)total;
     total += (int64_t)Hkv * tiles;
@@ -241,7 +241,7 @@ double attention_plan(AttnArgs &at, int n_rows, int G, int Hkv, int n_list, int 
   const int plain_groups = at.key_groups;
   int64_t range = 0;                        // split mode: steps of a range
   int range_keys = 0;                       // and keys of a step
-  auto steps_of = [&](int j, int keys) { return (at.e[j].T0 + keys - 1) / keys + (n_rows + keys - 1) / keys; };
+  auto steps_of = [&](int j, int keys) { return (at.e[j].T0 + n_rows + keys - 1) / keys; };
   // The shortest ranges of steps of `keys` keys that make at most `room` of
   // them; *count gets how many.
   auto shortest = [&](int keys, int64_t room, int64_t *count) {
