@@ -590,15 +590,16 @@ void attn_fwd(AttnArgs a, int nqt) {
   };
   // unnormalised partial state of the current pair into partial block blk.
   // Each 32-row group is stored as the wave holds it ([4-channel group][lane]),
-  // so that both the stores and the combine's loads are contiguous.
+  // so that both the stores and the combine's loads are contiguous; lanes past
+  // the packed rows write nothing.
   auto flush = [&](int64_t blk) {
     const int64_t rg = blk * a.part_groups + (p0 >> 5) + wave;
     float4 *op = reinterpret_cast<float4 *>(a.opart) + rg * NC * 64 + lane;
     float mt, lsum;
     merge(mt, lsum, [&](int c, float4 x) {
-      if (wave_rows) op[c * 64] = x;
+      if (row_ok) op[c * 64] = x;
     });
-    if (wave_rows && kg == 0 && half == 0)
+    if (row_ok && kg == 0 && half == 0)
       *reinterpret_cast<float2 *>(a.mlpart + 2 * (rg * 32 + l32)) = float2{mt, lsum};
   };
   if constexpr (STREAM) {
@@ -672,9 +673,11 @@ __global__ __launch_bounds__(256) void attn_combine(AttnArgs a) {
   const int u0 = a.split ? (int)f : unit_of(f);
   const int nsp = a.split ? a.e[j].st_tiles : unit_of(f + a.e[j].st_tiles - 1) - u0 + 1;
   const int64_t rg0 = ((int64_t)u0 + (a.split ? 0 : j * a.Hkv + kv)) * a.part_groups + rgi;
-  const float4 *op = reinterpret_cast<const float4 *>(a.opart) + (rg0 * (D / 8) + 4 * db) * 64 + lane;
+  // lanes past the packed rows read the group's first row, which others read too
+  const int p = rgi * 32 + l32, src = p < P ? lane : 32 * half;
+  const float4 *op = reinterpret_cast<const float4 *>(a.opart) + (rg0 * (D / 8) + 4 * db) * 64 + src;
   const int64_t ostep = (int64_t)a.part_groups * (D / 8) * 64, mstep = (int64_t)a.part_groups * 32;
-  const float2 *ml = reinterpret_cast<const float2 *>(a.mlpart) + rg0 * 32 + l32;
+  const float2 *ml = reinterpret_cast<const float2 *>(a.mlpart) + rg0 * 32 + (src & 31);
 
   float m = -1e30f, l = 0.f;
   float4 acc[4];
@@ -740,7 +743,6 @@ __global__ __launch_bounds__(256) void attn_combine(AttnArgs a) {
     t.z += e * y.z;
     t.w += e * y.w;
   }
-  const int p = rgi * 32 + l32;
   if (p >= P) return;
   const int r = p / G, h = kv * G + (p - r * G);
   if (a.out != nullptr) {
