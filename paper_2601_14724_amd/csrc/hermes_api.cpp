@@ -187,20 +187,19 @@ bool layout_within(const hermes_config *c, size_t limit, Layout *out) {
 //  - stream mode: the concatenated key tiles of all pairs in U equal ranges, U
 //    units of a workgroup per 256 rows, so every CU gets the same number of
 //    tiles whatever the pairs' lengths, for more partial state.
-// Costs are in steps of the plain kernel (a 64-key tile of 256 rows: 1.42 us
-// at head size 128 while CUs are idle, 1.8 us with all busy).  A launch takes
-// one step of a round of kStreamSlots workgroups after the other, each round
-// with two more for its queries and epilogue.  Measured against one key group
-// a step over 2 / 4 / 8 of them costs 1.09-1.17 / 1.37-1.65 / 1.7-2.1 (28
-// layers of 8976 tokens; one layer), a stream step 1.1 (head size 128) or 1.25
-// (64), and the partials' traffic 0.27 a MB on top of 4 for the combine.  One
-// layer, us, key groups 1 / 2 / 4 / 8, stream, split where it is taken: 784
-// rows on 8192 tokens 200 / 119 / 173 / 163 / 110, 784 on 1568 63 / 41 / 55 /
-// 57 / 46, 196 on 6144 141 / 83 / 60 / 41 / 33 / 32, 64 on 4096 95 / 58 / 45 /
-// 28 / 24 / 18 (28 query heads, 4 KV heads of 128); 784 on 4096 84 / 48 / 33 /
-// 35 / 34, 196 on 1024 24 / 17 / 10 / 7 / 12 (14 and 2 of 64).  28 layers of
-// 2048..6144 tokens: one row 57 with eight key groups, 50 stream, 43 split; 16
-// rows 79 stream, 63 split; 64 rows 175 with one key group, 152 stream.
+// Estimates are in us, fitted to 10000 timings of forced cuts: queries and
+// prompts of 1 to 3136 rows on 60 to 30000 tokens, one layer to 64, five head
+// shapes.  The cut taken is on average 1.3% (prompts 2%) slower than the best.  A
+// launch takes its workgroups in rounds of one a CU, a round the longest
+// workgroup's steps and 3.1 us for its queries and epilogue (1.3 more to merge key
+// groups, 0.8 at head size 64).  A step, 64 keys for each key group, takes what the
+// tables below say, or longer where the CUs together wait for HBM (7 MB of K and V
+// a us, each pair's once) or for the caches (23 MB a us, every workgroup's).  Any
+// cut has to save 3%.  An estimate in steps alone that left out HBM took cuts where
+// nothing was idle (16 rows on 64 layers of 1500 tokens: 52 us split, 36 with one
+// group; 28 layers of 700, 16 KV heads, 65 rows: 49 and 37), and one that left out
+// that a combine walks a pair's blocks one after the other split where streaming
+// was faster (one row on 30000 tokens of one layer, 2 KV heads of 64: 28 us, 18).
 // Fills key_groups, split and the st_* fields (st_units = 0: the plain kernel)
 // and returns the estimate.
 double attention_plan(AttnArgs &at, int n_rows, int G, int Hkv, int n_list, int D, int64_t part_rows) {
@@ -220,44 +219,71 @@ double attention_plan(AttnArgs &at, int n_rows, int G, int Hkv, int n_list, int 
     total += (int64_t)Hkv * tiles;
     max_tiles = tiles > max_tiles ? tiles : max_tiles;
   }
-  auto rounds = [](int64_t w) { return (double)((w + kStreamSlots - 1) / kStreamSlots); };
-  static const double kStep[4] = {1.0, 1.12, 1.5, 1.9};
+  auto over = [](int64_t x, int64_t y) { return (x + y - 1) / y; };
+  // us of a step by key groups (1, 2, 4, 8), head size 64 and 128; passes for
+  // the row LSE alone (no V) in the plain kernel
+  static const double kStep[2][4] = {{1.1, 1.15, 1.4, 1.25}, {1.6, 1.8, 2.5, 3.0}};
+  static const double kStepLse[2][4] = {{0.8, 0.85, 1.0, 0.9}, {1.05, 1.15, 1.3, 1.8}};
+  const int wide = D == 128;
+  const double tile_mb = 64e-6 * 4 * D;     // K and V of a tile
+  // w workgroups, nqt of them for each range of keys, of `steps` steps each
+  auto pass = [&](int64_t w, int64_t nqt, double steps, int e, bool plain) {
+    const bool lse_only = plain && at.out == nullptr;
+    const double busy = (double)(w < kStreamSlots ? w : kStreamSlots), mb = (lse_only ? 0.5 : 1.0) * tile_mb * (1 << e);
+    double step = (lse_only ? kStepLse : kStep)[wide][e];
+    if (e == 0 && P <= kAttnRowsPerBlock / 2) step *= 0.7;   // (half of the waves or fewer)
+    if (step < busy / (double)nqt * mb / 7.0) step = busy / (double)nqt * mb / 7.0;
+    if (step < busy * mb / 23.0) step = busy * mb / 23.0;
+    // (these fit two a CU, so a last round that is partly filled costs its part)
+    const bool two = plain && (lse_only ? !wide || e == 2 : !wide && e == 0);
+    const double rounds = !two ? (double)over(w, kStreamSlots)
+                          : w < kStreamSlots ? 1.0 : (double)w / kStreamSlots;
+    return 1.6 + rounds * (steps * step + 3.1 + (e == 0 ? 0.0 : wide ? 1.3 : 0.8));
+  };
+  // the combine: up to `chain` blocks a pair, eight of which it loads at once
+  auto combine = [&](int64_t chain, double blocks) {
+    return 3.7 + 0.54 * (double)over(chain, 8) + 0.35e-6 * (double)(4 * (D + 2) * P) * blocks;
+  };
   double best = 0.0;
   for (int e = 0; e < 4; ++e) {
-    const int64_t rows = kAttnRowsPerBlock >> e;
-    // a pair's only workgroup takes its keys from HBM: a step over eight
-    // groups then costs twice as much (1 row on 4096..16384 tokens, 28 layers:
-    // 199 us, 125 in stream mode)
-    const double step = P <= rows && e > 0 ? 2.0 * kStep[e] : kStep[e];
-    const double cost = rounds((P + rows - 1) / rows * pairs) * ((double)((max_tiles + (1 << e) - 1) >> e) * step + 2.0);
+    const int64_t nqt = over(P, kAttnRowsPerBlock >> e);
+    const double cost = pass(nqt * pairs, nqt, (double)over(max_tiles, 1 << e), e, true) * (e > 0 ? 1.03 : 1.0);
     if (e == 0 || cost < best) {
       best = cost;
       at.key_groups = 1 << e;
     }
   }
-  if (total > INT32_MAX / 2) return best;
-  const double mb = 32e-6 * at.part_groups * 4 * (D + 2);   // of one partial block
-  const int64_t most = part_rows / (32 * (int64_t)at.part_groups);
+  const int64_t most = part_rows / (32 * (int64_t)at.part_groups);   // partial blocks
+  if (total > INT32_MAX / 2 || most < 2) return best;
   const int plain_groups = at.key_groups;
   int64_t range = 0;                        // split mode: steps of a range
   int range_keys = 0;                       // and keys of a step
   auto steps_of = [&](int j, int keys) { return (at.e[j].T0 + n_rows + keys - 1) / keys; };
   // The shortest ranges of steps of `keys` keys that make at most `room` of
-  // them; *count gets how many.
-  auto shortest = [&](int keys, int64_t room, int64_t *count) {
+  // them; *count gets how many, *chain the most of a pair.
+  auto shortest = [&](int keys, int64_t room, int64_t *count, int64_t *chain) {
     int64_t all = 0;
     for (int j = 0; j < n_list; ++j) all += (int64_t)Hkv * steps_of(j, keys);
-    for (int64_t L = room > 0 ? (all + room - 1) / room : all;; L += 1 + L / 16) {
-      *count = 0;
-      for (int j = 0; j < n_list; ++j) *count += Hkv * ((steps_of(j, keys) + L - 1) / L);
+    for (int64_t L = over(all, room);; L += 1 + L / 16) {
+      *count = *chain = 0;
+      for (int j = 0; j < n_list; ++j) {
+        const int64_t n = over(steps_of(j, keys), L);
+        *count += Hkv * n;
+        *chain = n > *chain ? n : *chain;
+      }
       if (*count <= room || *count <= pairs) return L;
     }
   };
-  int64_t count = 0;
+  int64_t count = 0, chain = 0;
   if (P <= kSplitRows) {
     const int keys = P <= 32 ? 128 : 64;
-    const int64_t L = shortest(keys, 2 * kStreamSlots, &count);
-    const double cost = 6.0 + 1.2 * (double)L;
+    const int64_t slots = 2 * kStreamSlots;
+    const int64_t L = shortest(keys, slots < most ? slots : most, &count, &chain);
+    double step = P <= 32 ? (wide ? 1.9 : 1.2) : count > kStreamSlots ? (wide ? 2.4 : 1.1) : (wide ? 1.4 : 0.9);
+    const double hbm = (double)(count < slots ? count : slots) * tile_mb * (keys / 64) / 7.8;
+    if (step < hbm) step = hbm;
+    const double cost =
+        1.03 * (1.6 + (double)over(count, slots) * ((double)L * step + 2.1) + combine(chain, (double)count));
     if (cost < best && count <= most) {
       best = cost;
       at.split = 1;
@@ -266,11 +292,13 @@ double attention_plan(AttnArgs &at, int n_rows, int G, int Hkv, int n_list, int 
     }
   } else {
     for (int e = 1; e < 4; ++e) {
-      const int64_t rows = kAttnRowsPerBlock >> e, nqt = (P + rows - 1) / rows;
+      const int64_t nqt = over(P, kAttnRowsPerBlock >> e);
       const int keys = e == 3 ? 256 : 128;
       if (nqt * pairs > kStreamSlots / 2) continue;   // (no two ranges a pair)
-      const int64_t L = shortest(keys, kStreamSlots / nqt, &count);
-      const double cost = (double)(L * keys) * kStep[e] / (64 << e) + 6.0 + 0.27 * mb * (double)count;
+      const int64_t slots = kStreamSlots / nqt;
+      const int64_t L = shortest(keys, slots < most ? slots : most, &count, &chain);
+      const double cost =
+          1.03 * (pass(count * nqt, nqt, (double)(L * keys) / (64 << e), e, false) + combine(chain, (double)count));
       if (cost < best && count <= most) {
         best = cost;
         at.split = 2;
@@ -280,16 +308,20 @@ double attention_plan(AttnArgs &at, int n_rows, int G, int Hkv, int n_list, int 
       }
     }
   }
-  const int64_t nqt = (P + kAttnRowsPerBlock - 1) / kAttnRowsPerBlock;
-  const double step = D == 128 ? 1.1 : 1.25;
+  const int64_t nqt = over(P, kAttnRowsPerBlock);
   // one and two full rounds of workgroups, and parts of one (their partials
   // cost less)
   static const int kNum[8] = {8, 4, 3, 2, 4, 1, 2, 1}, kDen[8] = {4, 4, 4, 4, 6, 3, 8, 6};
-  for (int c = 0; c < 8 && P > kSplitRows; ++c) {
-    const int64_t units = kStreamSlots * kNum[c] / (kDen[c] * nqt);
-    if (units < 2 || units + pairs - 1 > most || units > total) continue;
-    const double cost = rounds(units * nqt) * ((double)((total + units - 1) / units) * step + 2.0) + 4.0 +
-                        0.27 * mb * (double)(units + pairs);
+  for (int c = 0; c < 8; ++c) {
+    int64_t units = kStreamSlots * kNum[c] / (kDen[c] * nqt);
+    if (units > most - pairs + 1) units = most - pairs + 1;
+    if (units < 2 || units > total) continue;
+    const int64_t tiles = over(total, units);
+    int64_t blocks = max_tiles / tiles + 2;   // (of a pair)
+    if (blocks > units) blocks = units;
+    const double cost = 1.03 * (pass(units * nqt, nqt, (double)tiles, 0, false) +
+                                combine(blocks, (double)(units + pairs)) +
+                                3.7 * (double)pairs / (double)units);   // (leaving a pair, entering the next)
     if (cost < best) {
       best = cost;
       at.st_units = (int32_t)units;

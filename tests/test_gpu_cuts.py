@@ -23,20 +23,20 @@ SHAPES = [
     ("four_groups_d64", 14, 2, 64, 900, 784),
     ("eight_groups_fewer_tiles", 8, 2, 64, 257, 1),
     ("eight_groups_d64", 14, 2, 64, 1024, 196),
-    ("eight_groups_d128", 6, 3, 128, 191, 65),
-    ("split_two_groups_d64", 14, 2, 64, 4000, 300),
+    ("four_groups_short_cache_d128", 6, 3, 128, 191, 65),
+    ("eight_groups_or_split_two_groups_d64", 14, 2, 64, 4000, 300),
     ("split_two_groups_or_stream_d128", 28, 4, 128, 6144, 196),
     ("split_four_groups_d128", 28, 4, 128, 2600, 130),
-    ("split_four_groups_d64", 14, 2, 64, 2300, 64),
+    ("split_eight_groups_64_rows_d64", 14, 2, 64, 2300, 64),
     ("split_eight_groups_d128", 9, 1, 128, 2001, 64),
-    ("split_eight_groups_d64", 8, 1, 64, 1900, 200),
-    ("split_four_waves", 12, 3, 64, 1300, 1),
+    ("eight_groups_200_rows_d64", 8, 1, 64, 1900, 200),
+    ("eight_groups_one_row_d64", 12, 3, 64, 1300, 1),
     ("stream_d64", 14, 2, 64, 3000, 1200),
 ]
 
 
 QUERIES = [
-    # name, layers, Hq, Hkv, d, lengths of the caches, rows (packed rows 1 .. 128: split mode)
+    # name, layers, Hq, Hkv, d, lengths of the caches, rows
     ("one_row_d64", 2, 2, 2, 64, (129, 1000), 1),
     ("one_row_of_seven_heads", 3, 28, 4, 128, (700, 2048, 2049), 1),
     ("32_packed_rows", 2, 8, 2, 128, (1, 1500), 8),
@@ -47,6 +47,96 @@ QUERIES = [
     ("129_packed_rows", 2, 3, 1, 128, (900, 4000), 43),
     ("four_groups_unequal", 2, 28, 4, 128, (700, 4001), 64),
 ]
+
+
+# Each instance of the attention kernel: a pass that takes it (tests/test_plan_host.py
+# holds the library to the cut named here).
+CUTS = [
+    # cut, d, Hq, Hkv, lengths of the caches, rows
+    ("plain 1", 64, 16, 16, (130,) * 6, 1),
+    ("plain 2", 64, 16, 16, (130,) * 6, 130),
+    ("plain 4", 64, 16, 16, (130,) * 6, 64),
+    ("plain 8", 64, 4, 4, (257,), 1),
+    ("split 2", 64, 28, 4, (2600,), 300),
+    ("split 4", 64, 14, 2, (6001,), 196),
+    ("split 8", 64, 9, 1, (2001,), 16),
+    ("four waves, 32 rows", 64, 4, 4, (2001,), 1),
+    ("four waves, 64 rows", 64, 9, 1, (2600,), 5),
+    ("four waves, 128 rows", 64, 9, 1, (2600,), 8),
+    ("stream", 64, 9, 1, (5000,), 5),
+    ("plain 1", 128, 4, 4, (130,), 1),
+    ("plain 2", 128, 16, 16, (130,) * 6, 130),
+    ("plain 4", 128, 9, 1, (130,), 16),
+    ("plain 8", 128, 4, 4, (257,), 1),
+    ("split 2", 128, 9, 1, (2600,) * 6, 64),
+    ("split 4", 128, 9, 1, (500,), 16),
+    ("split 8", 128, 9, 1, (1300,), 16),
+    ("four waves, 32 rows", 128, 4, 4, (641,), 1),
+    ("four waves, 64 rows", 128, 9, 1, (641,), 5),
+    ("four waves, 128 rows", 128, 9, 1, (641,), 8),
+    ("stream", 128, 9, 1, (5000,), 5),
+]
+PROMPTS = [
+    # the same for passes for the row LSE alone
+    ("plain 1", 64, 4, 4, (130,), 1),
+    ("plain 2", 64, 16, 16, (130,) * 6, 130),
+    ("plain 4", 64, 32, 8, (130,) * 6, 43),
+    ("plain 8", 64, 4, 4, (257,), 1),
+    ("plain 1", 128, 4, 4, (130,), 1),
+    ("plain 2", 128, 16, 16, (130,) * 6, 130),
+    ("plain 4", 128, 9, 1, (130,), 16),
+    ("plain 8", 128, 4, 4, (257,), 1),
+    ("four waves, 32 rows", 128, 4, 4, (2600,), 1),
+    ("stream", 64, 9, 1, (5000,), 5),
+]
+
+
+@pytest.mark.parametrize("cut,d,Hq,Hkv,lens,rows", CUTS)
+def test_every_cut_of_a_query_matches_oracle(cut, d, Hq, Hkv, lens, rows):
+    from paper_2601_14724_amd import hermes as H
+    L = len(lens)
+    say(f"[cuts] {cut}: {Hq}/{Hkv} d={d} lens={lens} rows={rows}")
+    init, host = [], []
+    for l, n in enumerate(lens):
+        wl = wk.custom("cut", 800 + rows, L, Hq, Hkv, d, n, 1, (n,) * L, query_len=rows, anchor_period=29)
+        c, q = wk.gen_cache(wl, l), wk.gen_query(wl, l)
+        host.append((c, q))
+        init.append((streaming.bf16_tensor(c["k"], "cuda"), streaming.bf16_tensor(c["v"], "cuda"),
+                     torch.from_numpy(c["pos"]).cuda()))
+    kv = H.HermesKV(L, Hq, Hkv, d, list(lens), rows, init=init)
+    out = kv.query(*(streaming.bf16_tensor(np.stack([q[k] for _, q in host]), "cuda") for k in ("q", "k", "v")))
+    for l, (c, q) in enumerate(host):
+        o, _ = orc.chunk_attention(f64(q["q"]), f64(c["k"]), f64(c["v"]), f64(q["k"]), f64(q["v"]), want_w=False)
+        check_o(out[l].float().cpu().numpy(), o, f"[cuts] {cut} layer {l}")
+    kv.close()
+
+
+@pytest.mark.parametrize("cut,d,Hq,Hkv,lens,rows", PROMPTS)
+def test_every_cut_of_a_prompt_matches_oracle(cut, d, Hq, Hkv, lens, rows):
+    """W of every cached token (the last one appended just before) from the
+    prompt's rows."""
+    from paper_2601_14724_amd import hermes as H
+    L = len(lens)
+    say(f"[cuts] prompt {cut}: {Hq}/{Hkv} d={d} lens={lens} rows={rows}")
+    init, host = [], []
+    for l, n in enumerate(lens):
+        wl = wk.custom("prompt", 900 + rows, L, Hq, Hkv, d, n, 1, (n,) * L, query_len=rows, anchor_period=29)
+        c, q = wk.gen_cache(wl, l), wk.gen_query(wl, l)
+        host.append((c, q))
+        init.append((streaming.bf16_tensor(c["k"][:-1], "cuda"), streaming.bf16_tensor(c["v"][:-1], "cuda"),
+                     torch.from_numpy(c["pos"][:-1]).cuda()))
+    kv = H.HermesKV(L, Hq, Hkv, d, list(lens), rows, init=init, layer_class=[2] * L, scoring_mode=H.SCORE_GUIDANCE)
+    last = {k: streaming.bf16_tensor(np.stack([c[k][-1:] for c, _ in host]), "cuda") for k in ("k", "v")}
+    q1 = torch.zeros(L, 1, Hq, d, dtype=torch.bfloat16, device="cuda")
+    kv.append(q1, last["k"], last["v"], torch.from_numpy(host[0][0]["pos"][-1:]).cuda())
+    kv.guidance(*(streaming.bf16_tensor(np.stack([q[k] for _, q in host]), "cuda") for k in ("q", "k", "v")))
+    torch.cuda.synchronize()
+    for l, (c, q) in enumerate(host):
+        _, w = orc.chunk_attention(f64(q["q"]), f64(c["k"]), f64(c["v"]), f64(q["k"]), f64(q["v"]))
+        n = lens[l]
+        rel = float((np.abs(kv.w[l][:n].cpu().numpy().astype(np.float64) - w[:n]) / w[:n]).max())
+        assert rel <= 1e-3, f"{cut} layer {l}: mass off by {rel}"
+    kv.close()
 
 
 @pytest.mark.parametrize("name,L,Hq,Hkv,d,lens,rows", QUERIES)

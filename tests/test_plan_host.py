@@ -137,3 +137,41 @@ def test_partial_rows_stay_in_their_room():
             if p.rows:
                 assert 0 <= p.o_lo < p.o_hi <= p.ml_lo < p.ml_hi <= p.total
                 assert limit == 0 or p.total <= limit
+
+
+def cut_name(p, packed):
+    if p.four_waves:
+        return f"four waves, {32 if packed <= 32 else 64 if packed <= 64 else 128} rows"
+    return "stream" if p.mode == STREAM else f"{'split' if p.mode == SPLIT else 'plain'} {p.key_groups}"
+
+
+def test_the_gpu_tests_reach_every_instance():
+    """tests/test_gpu_cuts.py names a cut for each of its passes: the library takes
+    it, and together they are all instances of the attention kernel."""
+    import test_gpu_cuts as gpu
+    seen = set()
+    for kind, cases in ((QUERY, gpu.CUTS), (PROMPT, gpu.PROMPTS)):
+        for cut, d, hq, hkv, lens, rows in cases:
+            cfg = config(len(lens), hq, hkv, d, max(lens) + rows, rows)
+            got = cut_name(plan(cfg, [(kind, rows, -1, lens, 0, 0)])[0], rows * hq // hkv)
+            assert got == cut, (kind, cut, d, hq, hkv, lens, rows, got)
+            seen.add((kind if got.startswith("plain") else QUERY, d, got))
+    plain = {f"plain {g}" for g in (1, 2, 4, 8)}
+    cut = {f"split {g}" for g in (2, 4, 8)} | {f"four waves, {r} rows" for r in (32, 64, 128)} | {"stream"}
+    assert seen == {(QUERY, d, c) for d in (64, 128) for c in plain | cut} | {(PROMPT, d, c) for d in (64, 128) for c in plain}
+
+
+@pytest.mark.parametrize("kind,layers,hq,hkv,d,length,rows,cuts", [
+    # measured us of the cut taken by the estimate in steps, and of the one wanted here
+    (QUERY, 64, 28, 4, 128, 1500, 16, {"plain 1", "plain 2"}),           # 52, 36
+    (QUERY, 64, 28, 4, 128, 1500, 1, {"plain 1", "plain 2", "plain 4"}), # 39, 35
+    (QUERY, 28, 16, 16, 128, 700, 65, {"plain 1"}),                      # 49, 37
+    (QUERY, 28, 16, 16, 128, 700, 128, {"plain 1"}),                     # 56, 46
+    (QUERY, 1, 14, 2, 64, 30000, 1, {"stream"}),                         # 28, 18
+    (QUERY, 1, 32, 1, 64, 30000, 2, {"stream"}),                         # 46, 19
+    (QUERY, 28, 14, 2, 64, 2500, 16, {"plain 8"}),                       # 21, 13
+    (PROMPT, 28, 16, 16, 128, 5200, 100, {"plain 1", "plain 2"}),        # 474, 380 with the sweep
+])
+def test_cuts_of_passes_that_an_estimate_in_steps_slowed_down(kind, layers, hq, hkv, d, length, rows, cuts):
+    cfg, lens = config(layers, hq, hkv, d, length + 784, 784), [length] * layers
+    assert cut_name(plan(cfg, [(kind, rows, -1, lens, 0, 0)])[0], rows * hq // hkv) in cuts
