@@ -968,7 +968,7 @@ __global__ __launch_bounds__(256, 3) void attn_colsum(ColsumArgs a, int nkb) {
     __syncthreads();
   }
   for (; it < nit; ++it) step(it, std::integral_constant<bool, false>{});
-  double *part = a.wpart + layer * a.wpart_lstride + (int64_t)(kv_blk * a.splits + split) * a.wpart_hstride;
+  double *part = a.wpart + (layer - a.layer0) * a.wpart_lstride + (int64_t)(kv_blk * a.splits + split) * a.wpart_hstride;
 #pragma unroll
   for (int kb = 0; kb < 2; ++kb) {
     const double wsum = wacc[kb] + __shfl_xor(wacc[kb], 32);
@@ -1001,7 +1001,7 @@ __global__ __launch_bounds__(kNormBlock *MG) void mass_reduce(ColsumArgs a) {
   const int n = a.Hkv * a.splits;
   double w = 0.0;
   if (i < T) {
-    const double *part = a.wpart + layer * a.wpart_lstride + i;
+    const double *part = a.wpart + (layer - a.layer0) * a.wpart_lstride + i;
     const int x1 = (grp + 1) * n / MG;
     for (int x0 = grp * n / MG; x0 < x1; x0 += 8) {
       double v[8];

@@ -87,11 +87,32 @@ int check_config(const hermes_config *c) {
   return HERMES_OK;
 }
 
+// Partial rows that a pass of n_rows rows over n_layers layers can use: one block
+// for each workgroup of a full round (two of four waves a CU), and, streamed, one
+// more a pair.  Passes that fill two rounds of the plain kernel stream little
+// better, and have no room for it.
+int64_t partial_rows(const hermes_config *c, int64_t n_rows, int64_t n_layers) {
+  const int64_t P = n_rows * (c->n_q_heads / c->n_kv_heads), group_rows = (P + 31) / 32 * 32;
+  const int64_t nqt = (P + kAttnRowsPerBlock - 1) / kAttnRowsPerBlock;
+  const int64_t pairs = n_layers * c->n_kv_heads, tiles = pairs * (((int64_t)c->max_cap + 63) / 64);
+  int64_t blocks = 0;
+  if (nqt <= kStreamSlots && nqt * pairs <= 2 * kStreamSlots) {
+    const int64_t units = kStreamSlots / nqt, most = (tiles + 1) / 2;   // (of two tiles at least)
+    blocks = (units < most ? units : most) + pairs;
+  }
+  if (P <= kSplitRows) {
+    const int64_t ranges = 2 * kStreamSlots < tiles ? 2 * kStreamSlots : tiles;
+    blocks = blocks > ranges ? blocks : ranges;
+    blocks = blocks > pairs ? blocks : pairs;
+  }
+  return blocks * group_rows;
+}
+
 // Workspace layout of `c`; shared_rows < 0 sizes the shared room for the most
-// rows a short pass can write (256 for each of kStreamSlots workgroups, and a
-// block more for each (layer, KV head) pair), else for that many rows.  rooms:
-// streams that have a room of their own; with none there is no room for sweeps
-// cut along the query rows either.
+// rows a short pass can use, else for that many.  rooms: streams that have a
+// room of their own, for their short passes and for kRoomRows rows of longer ones
+// at most.  Every room also holds a sweep's partials when its query rows are cut
+// (the wpart region holds those of uncut ones).
 Layout layout_of(const hermes_config *c, int64_t shared_rows = -1, int rooms = kStreamRooms) {
   Layout s;
   s.lse_lstride = (int64_t)c->n_q_heads * c->max_chunk;
@@ -115,7 +136,6 @@ Layout layout_of(const hermes_config *c, int64_t shared_rows = -1, int rooms = k
   s.newc = off;
   off = round_up(off + sizeof(int32_t) * 3 * (size_t)s.newc_lstride * c->n_layers);
   s.wpart_lstride = (int64_t)c->n_kv_heads * c->max_cap;
-  if (rooms > 0 && s.wpart_lstride < kMassPartials) s.wpart_lstride = kMassPartials;
   s.wpart = off;
   off = round_up(off + sizeof(double) * (size_t)s.wpart_lstride * c->n_layers);
   // summary token: fp64 block sums, staged bf16 rows and their metadata
@@ -133,17 +153,17 @@ Layout layout_of(const hermes_config *c, int64_t shared_rows = -1, int rooms = k
   s.flag = off;
   off = round_up(off + sizeof(int32_t) * 4);
   // partial state of passes whose keys are cut
-  const int64_t G = c->n_q_heads / c->n_kv_heads;
-  const int64_t short_rows =
-      (int64_t)kStreamSlots * kAttnRowsPerBlock + (int64_t)c->n_layers * c->n_kv_heads * kSplitMaxTokens * G;
+  int64_t short_rows = 0, long_rows = 0;
+  for (int64_t n = 1; n <= c->max_chunk; ++n) {
+    const int64_t one = partial_rows(c, n, 1), all = partial_rows(c, n, c->n_layers), rows = one > all ? one : all;
+    if (n <= kSplitMaxTokens) short_rows = short_rows > rows ? short_rows : rows;
+    else if (rows == 0 || long_rows >= kRoomRows) break;   // (longer passes have none; no more of it)
+    long_rows = long_rows > rows ? long_rows : rows;
+  }
+  if (long_rows > kRoomRows) long_rows = kRoomRows;
   s.shared_rows = shared_rows >= 0 ? shared_rows : short_rows;
   s.shared = off;
   off = round_up(off + room_bytes(s.shared_rows, c->head_dim));
-  // a stream's room: its short passes, and its longer ones (at most one block
-  // for two key tiles, and two more a pair)
-  const int64_t blocks = (int64_t)c->n_layers * c->n_kv_heads * (((int64_t)c->max_cap + 63) / 64 / 2 + 2);
-  const int64_t rows = (c->max_chunk * G + 31) / 32 * 32;
-  const int64_t long_rows = rows > kRoomRows / blocks ? kRoomRows : blocks * rows;
   s.n_rooms = rooms;
   s.room_rows = rooms == 0 ? 0 : short_rows > long_rows ? short_rows : long_rows;
   s.rooms = off;
@@ -462,35 +482,54 @@ struct hermes_ctx {
     return true;
   }
 
-  // Cuts one call's attention pass of n_rows rows over the entries of `at`.
-  // captured() tells whether the call is recorded: it may then be replayed on
-  // any stream, so no room is its own.  Passes without a room run uncut, or,
-  // where they are short (queries and prompts of up to kSplitMaxTokens rows) and
-  // the cut saves a tenth, share one that no other pass touches: those have to
-  // follow each other on the device, and nothing else has to.
+  // Cuts one call's attention pass of n_rows rows over the entries of `at`, and
+  // its sweep of n_cs layers, if any.  captured() tells whether the call is
+  // recorded: it may then be replayed on any stream, so no room is its own.
+  // Passes without a room run uncut, or, where they are short (queries and prompts
+  // of up to kSplitMaxTokens rows) and the cut saves a tenth, share one that no
+  // other pass touches: those have to follow each other on the device, and nothing
+  // else has to.
   template <typename F>
-  void cut(AttnArgs &at, int n_rows, int n, bool may_share, hipStream_t s, F &&captured) {
+  void cut(AttnArgs &at, int n_rows, int n, bool may_share, ColsumArgs *cs, int n_cs, int max_T, hipStream_t s,
+           F &&captured) {
     auto plan = [&](int64_t rows, size_t base) {
       const double cost = attention_plan(at, n_rows, Hq / Hkv, Hkv, n, D, rows);
       at.opart = reinterpret_cast<float *>(ws + base);
       at.mlpart = reinterpret_cast<float *>(ws + base + round_up(sizeof(float) * (size_t)rows * D));
       return cost;
     };
+    // The sweep's partials: a layer's part of the workspace, or (for the layers
+    // first .. last) the room's, which the pass before it is done with.
+    auto sweep = [&](size_t base, size_t bytes) {
+      if (n_cs == 0) return false;
+      const int first = cs->e[0].layer, layers = cs->e[n_cs - 1].layer - first + 1;
+      const int64_t room = (int64_t)(bytes / sizeof(double)) / layers;
+      mass_splits(*cs, n_cs, max_T, room > lay.wpart_lstride ? room : lay.wpart_lstride);
+      const int64_t need = (int64_t)Hkv * cs->splits * max_T;
+      const bool own = need <= lay.wpart_lstride;
+      cs->wpart = reinterpret_cast<double *>(ws + (own ? lay.wpart : base));
+      cs->wpart_lstride = own ? lay.wpart_lstride : need;
+      cs->layer0 = own ? 0 : first;
+      return !own;
+    };
     const int room = room_of(s);
     if (room >= 0) {
-      plan(lay.room_rows, lay.rooms + room * room_bytes(lay.room_rows, D));
-      if (at.st_units == 0) return;
+      const size_t bytes = room_bytes(lay.room_rows, D), base = lay.rooms + room * bytes;
+      plan(lay.room_rows, base);
+      const bool swept = sweep(base, bytes);
+      if (at.st_units == 0 && !swept) return;
       if (!captured()) {
         room_taken[room] = true;
         room_stream[room] = s;
         return;
       }
     }
+    sweep(0, 0);
     const double uncut = plan(0, lay.shared);
     if (may_share && n_rows <= kSplitMaxTokens && plan(lay.shared_rows, lay.shared) > 0.9 * uncut) plan(0, lay.shared);
   }
-  void cut(AttnArgs &at, int n_rows, int n, bool may_share, hipStream_t s) {
-    cut(at, n_rows, n, may_share, s, [&] { return capturing(s); });
+  void cut(AttnArgs &at, int n_rows, int n, bool may_share, ColsumArgs *cs, int n_cs, int max_T, hipStream_t s) {
+    cut(at, n_rows, n, may_share, cs, n_cs, max_T, s, [&] { return capturing(s); });
   }
 
   int prof_begin(int id, hipStream_t s, EventPair *ep) {
@@ -919,8 +958,6 @@ static int append_impl(hermes_ctx *ctx, int32_t layer, const void *q, const void
   cs.q = at.q;
   cs.kn = at.kn;
   cs.lse = at.lse;
-  cs.wpart = reinterpret_cast<double *>(ctx->ws + ctx->lay.wpart);
-  cs.wpart_lstride = ctx->lay.wpart_lstride;
   cs.normpart = reinterpret_cast<double *>(ctx->ws + ctx->lay.normpart);
   cs.normpart_lstride = ctx->lay.normpart_lstride;
   cs.q_lstride = q_ls;
@@ -943,7 +980,7 @@ static int append_impl(hermes_ctx *ctx, int32_t layer, const void *q, const void
     }
   }
 
-  ctx->cut(at, n_new, (int)list.size(), false, s);
+  ctx->cut(at, n_new, (int)list.size(), false, &cs, n_cs, max_T, s);
   // (the attention launch copies the new rows too: the class keeps its count)
   int rc = ctx->run(HERMES_K_APPEND, s, [] { return hipSuccess; });
   if (rc != HERMES_OK) return rc;
@@ -953,7 +990,6 @@ static int append_impl(hermes_ctx *ctx, int32_t layer, const void *q, const void
   });
   if (rc != HERMES_OK) return rc;
   if (n_cs > 0) {
-    mass_splits(cs, n_cs, max_T, ctx->lay.wpart_lstride);
     rc = ctx->run(HERMES_K_COLSUM, s, [&] { return launch_colsum(cs, n_cs, max_T, ctx->D, s); });
     if (rc != HERMES_OK) return rc;
   }
@@ -1035,8 +1071,6 @@ int hermes_guidance_score(hermes_ctx *ctx, int32_t layer, const void *q, const v
   cs.q = at.q;
   cs.kn = at.kn;
   cs.lse = at.lse;
-  cs.wpart = reinterpret_cast<double *>(ctx->ws + ctx->lay.wpart);
-  cs.wpart_lstride = ctx->lay.wpart_lstride;
   cs.normpart = reinterpret_cast<double *>(ctx->ws + ctx->lay.normpart);
   cs.normpart_lstride = ctx->lay.normpart_lstride;
   cs.q_lstride = q_ls;
@@ -1055,8 +1089,7 @@ int hermes_guidance_score(hermes_ctx *ctx, int32_t layer, const void *q, const v
     max_T = ctx->len[l] > max_T ? ctx->len[l] : max_T;
   }
   const int n = (int)list.size();
-  mass_splits(cs, n, max_T, ctx->lay.wpart_lstride);
-  ctx->cut(at, n_rows, n, true, s);
+  ctx->cut(at, n_rows, n, true, &cs, n, max_T, s);
   const int rc = ctx->run(HERMES_K_GUIDE, s, [&] {
     hipError_t e = at.st_units > 0 ? launch_attention_parted(at, n, ctx->D, s)
                                    : launch_attention(at, n, ctx->D, s);
@@ -1297,7 +1330,7 @@ int hermes_query_attend(hermes_ctx *ctx, int32_t layer, const void *q, const voi
     at.e[n] = ctx->attn_entry(l, layer == HERMES_ALL_LAYERS ? l : 0);
     ++n;
   }
-  ctx->cut(at, n_q, n, true, s);
+  ctx->cut(at, n_q, n, true, nullptr, 0, 0, s);
   return ctx->run(HERMES_K_QUERY, s, [&] {
     return at.st_units > 0 ? launch_attention_parted(at, n, ctx->D, s)
                            : launch_attention(at, n, ctx->D, s);
@@ -1367,7 +1400,20 @@ extern "C" int hermes_plan_probe(const hermes_config *cfg, size_t limit, const P
     for (int l = 0; l < c.L; ++l)
       if (call.layer == HERMES_ALL_LAYERS || call.layer == l) at.e[n++].T0 = call.len[l];
     at.out = call.kind == PLAN_PROMPT ? nullptr : reinterpret_cast<uint16_t *>(c.ws);
-    c.cut(at, call.n_rows, n, call.kind != PLAN_APPEND, reinterpret_cast<hipStream_t>(call.stream),
+    ColsumArgs cs;
+    std::memset(&cs, 0, sizeof(cs));
+    cs.Hq = c.Hq;
+    cs.Hkv = c.Hkv;
+    cs.C = call.n_rows;
+    int n_cs = 0, max_T = 0;
+    for (int l = 0; l < c.L && call.kind != PLAN_QUERY; ++l) {   // (an append's as if every layer were swept)
+      if (call.layer != HERMES_ALL_LAYERS && call.layer != l) continue;
+      const int T = call.len[l] + (call.kind == PLAN_APPEND ? call.n_rows : 0);
+      cs.e[n_cs++].layer = (int8_t)l;
+      max_T = T > max_T ? T : max_T;
+    }
+    if (max_T == 0) n_cs = 0;
+    c.cut(at, call.n_rows, n, call.kind != PLAN_APPEND, &cs, n_cs, max_T, reinterpret_cast<hipStream_t>(call.stream),
           [&] { return call.captured != 0; });
     PlanInfo &o = out[i];
     const int64_t blocks = at.st_units == 0 ? 0 : at.split ? at.e[n].st_off : at.st_units + (int64_t)n * c.Hkv - 1;
@@ -1380,6 +1426,14 @@ extern "C" int hermes_plan_probe(const hermes_config *cfg, size_t limit, const P
     o.o_hi = o.o_lo + (int64_t)sizeof(float) * o.rows * c.D;
     o.ml_lo = reinterpret_cast<char *>(at.mlpart) - c.ws;
     o.ml_hi = o.ml_lo + (int64_t)sizeof(float) * 2 * o.rows;
+    o.splits = n_cs > 0 ? cs.splits : 0;
+    o.sweep_lo = o.sweep_hi = 0;
+    if (n_cs > 0) {
+      const int64_t used = (int64_t)c.Hkv * cs.splits * max_T;
+      o.sweep_lo = reinterpret_cast<char *>(cs.wpart + (cs.e[0].layer - cs.layer0) * cs.wpart_lstride) - c.ws;
+      o.sweep_hi = o.sweep_lo + (int64_t)sizeof(double) *
+                                    ((cs.e[n_cs - 1].layer - cs.e[0].layer) * cs.wpart_lstride + used);
+    }
     o.total = c.lay.total;
   }
   return HERMES_OK;

@@ -99,7 +99,7 @@ struct MassEntry {
 // Attention-mass sweep: W_i for the candidates i < ncand of each entry's layer
 // (ncand = T0 + C for the chunk's own mass, T0 for a guidance prompt, whose
 // rows are not candidates).  Each KV head's share, cut into
-// `splits` ranges of its query rows, goes to wpart[layer][kv * splits +
+// `splits` ranges of its query rows, goes to wpart[layer - layer0][kv * splits +
 // split][i] (fp64, rows of wpart_hstride), then is summed into the layer's w
 // buffer in that order.
 struct ColsumArgs {
@@ -110,6 +110,7 @@ struct ColsumArgs {
   int64_t q_lstride, kv_lstride, lse_lstride, wpart_lstride, wpart_hstride, normpart_lstride;
   int32_t Hq, Hkv, C;
   int32_t splits;           // workgroups that share a block's query rows (1: none)
+  int32_t layer0;           // the layer whose partials wpart starts with
   float scale_log2;
   MassEntry e[kMaxLayers];
 };
@@ -266,7 +267,6 @@ hipError_t launch_mrope_rank(const RankArgs &a, hipStream_t s);
 constexpr int kAttnRowsPerBlock = 256;   // packed (row, head) pairs per attention workgroup
 constexpr int kColsumKeysPerBlock = 256; // candidates per workgroup of the sweep
 constexpr int kMassSplitMax = 32;       // ranges a sweep's query rows are cut into at most
-constexpr int64_t kMassPartials = 1024 * 256;   // fp64 partials a layer keeps for them
 constexpr int kSummaryRows = 128;        // candidates per workgroup of the summary sums
 constexpr int kSplitMaxTokens = 64;      // rows of a query or prompt that may share a room of partial rows
 constexpr int64_t kRoomRows = 131072;    // partial rows of a stream's longer passes at most (68 MB at head size 128)
@@ -286,8 +286,10 @@ struct PlanCall {
 };
 struct PlanInfo {
   int32_t key_groups, mode, four_waves, units;   // mode 0 plain, 1 stream, 2 split
+  int32_t splits, pad_;     // of the sweep (0: none)
   int64_t rows;             // partial rows the pass may write
   int64_t o_lo, o_hi, ml_lo, ml_hi;   // and where, as bytes of the workspace
+  int64_t sweep_lo, sweep_hi;         // and the sweep's partials
   int64_t total;            // bytes of the layout
 };
 extern "C" int hermes_plan_probe(const hermes_config *cfg, size_t limit, const PlanCall *calls, int n_calls,

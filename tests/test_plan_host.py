@@ -20,8 +20,9 @@ class Call(ctypes.Structure):
 
 class Info(ctypes.Structure):
     _fields_ = [("key_groups", ctypes.c_int32), ("mode", ctypes.c_int32), ("four_waves", ctypes.c_int32),
-                ("units", ctypes.c_int32)] + [(n, ctypes.c_int64) for n in
-                                              ("rows", "o_lo", "o_hi", "ml_lo", "ml_hi", "total")]
+                ("units", ctypes.c_int32), ("splits", ctypes.c_int32), ("pad_", ctypes.c_int32)] + [
+                    (n, ctypes.c_int64) for n in
+                    ("rows", "o_lo", "o_hi", "ml_lo", "ml_hi", "sweep_lo", "sweep_hi", "total")]
 
 
 H.lib.hermes_plan_probe.argtypes = [ctypes.POINTER(H.HermesConfig), ctypes.c_size_t, ctypes.POINTER(Call),
@@ -54,10 +55,10 @@ def plan(cfg, calls, limit=0):
     return list(out)
 
 
-def apart(a, b):
+def apart(a, b, sweeps=True):
     def meet(x, y):
         return x[0] < y[1] and y[0] < x[1]
-    spans = [[(p.o_lo, p.o_hi), (p.ml_lo, p.ml_hi)] for p in (a, b)]
+    spans = [[(p.o_lo, p.o_hi), (p.ml_lo, p.ml_hi)] + ([(p.sweep_lo, p.sweep_hi)] if sweeps else []) for p in (a, b)]
     return not any(meet(x, y) for x in spans[0] for y in spans[1])
 
 
@@ -84,13 +85,14 @@ def test_streams_never_share_a_room(rows):
                  for s in (8, 16, 24, 32, 40) for k in (QUERY, APPEND, PROMPT)]
         calls += [(QUERY, rows, 0, lens, 8, 1), (APPEND, rows, 0, lens, 8, 1)]
         got = plan(cfg, calls)
-        for (ka, ra, _, _, sa, xa), a in zip(calls, got):
-            for (kb, rb, _, _, sb, xb), b in zip(calls, got):
+        for (ka, ra, la, _, sa, xa), a in zip(calls, got):
+            for (kb, rb, lb, _, sb, xb), b in zip(calls, got):
                 if (sa, xa) == (sb, xb):
                     continue
                 share = all((x or s > 24) and k != APPEND and r <= 64
                             for k, r, s, x in ((ka, ra, sa, xa), (kb, rb, sb, xb)))
-                assert share or apart(a, b), (ka, ra, sa, xa, kb, rb, sb, xb)
+                # (a layer is swept by one call at a time)
+                assert share or apart(a, b, la != lb), (ka, ra, sa, xa, kb, rb, sb, xb)
         assert all(p.rows == 0 for (k, r, _, _, s, x), p in zip(calls, got) if (x or s > 24) and (k == APPEND or r > 64))
 
 
@@ -136,7 +138,8 @@ def test_partial_rows_stay_in_their_room():
             assert p.key_groups in (1, 2, 4, 8) and (p.rows > 0) == (p.mode != PLAIN)
             if p.rows:
                 assert 0 <= p.o_lo < p.o_hi <= p.ml_lo < p.ml_hi <= p.total
-                assert limit == 0 or p.total <= limit
+            assert 0 <= p.sweep_lo <= p.sweep_hi <= p.total
+            assert limit == 0 or p.total <= limit
 
 
 def cut_name(p, packed):
@@ -175,3 +178,20 @@ def test_the_gpu_tests_reach_every_instance():
 def test_cuts_of_passes_that_an_estimate_in_steps_slowed_down(kind, layers, hq, hkv, d, length, rows, cuts):
     cfg, lens = config(layers, hq, hkv, d, length + 784, 784), [length] * layers
     assert cut_name(plan(cfg, [(kind, rows, -1, lens, 0, 0)])[0], rows * hq // hkv) in cuts
+
+
+def bytes_of(*shape, **over):
+    cfg = config(*shape, **over)
+    return H.lib.hermes_workspace_bytes(ctypes.byref(cfg))
+
+
+def test_the_workspace_is_sized_by_what_its_passes_can_use():
+    """A context that only decodes, or is small, does not reserve the room of
+    large passes; the sweeps' partials lie in the streams' rooms."""
+    mib = 1 << 20
+    assert bytes_of(28, 28, 4, 128, 8976, 784) < 264 * mib
+    assert bytes_of(24, 14, 2, 64, 4880, 784) < 136 * mib
+    assert bytes_of(28, 28, 4, 128, 8193, 1) < 48 * mib
+    assert bytes_of(2, 4, 2, 64, 100, 16) < mib
+    got = plan(config(28, 28, 4, 128, 8976, 784), [(APPEND, 784, 5, [8192] * 28, 8, 0), (APPEND, 784, 5, [8192] * 28, 8, 1)])
+    assert got[0].splits > 1 and got[1].splits == 1   # (a captured one has no room to cut its sweep in)
