@@ -366,13 +366,18 @@ double attention_plan(AttnArgs &at, int n_rows, int G, int Hkv, int n_list, int 
 }
 
 // Query-row splits of a mass sweep of n_list layers of at most max_T
-// candidates, and the row length of its partials.  A workgroup alone on its
-// CU takes about 1.5 times as long for a query tile as each of three that
-// share it (0.73 and 0.475 us at head size 128, 784 x 7 rows): a launch of
-// one layer (144 workgroups at 8976 candidates and 4 KV heads) leaves CUs
-// empty and the others waiting for latency.  So the cost of k workgroups a
-// CU is max(3, 2 k) halves of a tile's shared time; each also pays about six
-// tiles for its K fragments and the first tiles of its ring.
+// candidates, and the row length of its partials, of which there is room for
+// `partials` a layer.  A workgroup alone on its CU takes about 1.5 times as long
+// for a query tile as each of three that share it (0.73 and 0.475 us at head size
+// 128, 784 x 7 rows): a launch of one layer (144 workgroups at 8976 candidates and
+// 4 KV heads) leaves CUs empty and the others waiting for latency.  So the cost of
+// k workgroups a CU is max(3, 2 k) halves of a tile's shared time; each also pays
+// about six tiles for its K fragments and the first tiles of its ring.  Splits
+// write and read that many times the partials and pay for more of them in the
+// reduction: 1% and about a microsecond.  (Without that, 16 rows of 8 KV heads on
+// 1000 tokens took two splits, 23.9 us an append against 22.1, and 25 layers of
+// 8976 two for the sake of a remainder: twice the partials for 0.07% by the
+// estimate, and no faster, 3427 us an append against 3404.)
 void mass_splits(ColsumArgs &cs, int n_list, int max_T, int64_t partials) {
   const int G = cs.Hq / cs.Hkv;
   const int64_t groups = (int64_t)((max_T + kColsumKeysPerBlock - 1) / kColsumKeysPerBlock) * cs.Hkv * n_list;
@@ -384,7 +389,8 @@ void mass_splits(ColsumArgs &cs, int n_list, int max_T, int64_t partials) {
   cs.splits = 1;
   for (int64_t n = 1; n <= most && n <= kMassSplitMax; ++n) {
     const double k = (double)((groups * n + 255) / 256);
-    const double cost = ((double)((tiles + n - 1) / n) + 6.0) * (2.0 * k > 3.0 ? 2.0 * k : 3.0);
+    double cost = ((double)((tiles + n - 1) / n) + 6.0) * (2.0 * k > 3.0 ? 2.0 * k : 3.0);
+    if (n > 1) cost = 1.01 * cost + 4.0;
     if (n == 1 || cost < best) {
       best = cost;
       cs.splits = (int32_t)n;

@@ -195,3 +195,15 @@ def test_the_workspace_is_sized_by_what_its_passes_can_use():
     assert bytes_of(2, 4, 2, 64, 100, 16) < mib
     got = plan(config(28, 28, 4, 128, 8976, 784), [(APPEND, 784, 5, [8192] * 28, 8, 0), (APPEND, 784, 5, [8192] * 28, 8, 1)])
     assert got[0].splits > 1 and got[1].splits == 1   # (a captured one has no room to cut its sweep in)
+
+
+@pytest.mark.parametrize("layers,hq,hkv,d,length,rows,splits", [
+    (25, 28, 4, 128, 8192, 784, 1),    # two promised 0.07%: 3427 us, one 3404 (noise is 1%)
+    (1, 32, 8, 128, 1000, 16, 1),      # two: 23.9 us, one 22.1
+    (1, 32, 8, 128, 0, 16, 1),         # two: 15.6, one 14.3
+    (1, 28, 4, 128, 8192, 784, 5),     # one: 235 us, five 171
+])
+def test_sweeps_are_cut_where_it_pays(layers, hq, hkv, d, length, rows, splits):
+    cfg = config(layers, hq, hkv, d, length + 784, 784)
+    got = plan(cfg, [(APPEND, rows, -1, [length] * layers, 0, 0)])[0].splits
+    assert got == splits if splits == 1 else got > 1
