@@ -202,14 +202,16 @@ int hermes_kv_init(const hermes_config *cfg, const hermes_layer_buffers *layers,
  * device returns HERMES_ESTATE while the first is alive, since both would
  * share (and race on) the one array; nothing in it needs to start at zero
  * (every word is written before it is read).  When the configuration's
- * workspace (hermes_workspace_bytes) exceeds the scratch, the room for the
- * partial results of appends goes first, then that of queries and guidance
- * prompts is cut to what fits (those passes are then cut otherwise: same
- * results up to rounding order);
+ * workspace (hermes_workspace_bytes) exceeds the scratch, the streams' rooms for
+ * partial results go first, one after the other, then the shared one is cut to
+ * what fits (those passes are then cut otherwise: same results up to rounding
+ * order).  Where a stream's room as large as the shared one does not fit beside
+ * it (28 layers of 32/8 heads of 128, say), queries and prompts of up to 64 rows on
+ * any stream share, and have to follow each other on the device;
  * HERMES_ECAPACITY when even the rest exceeds it.  Errors otherwise as
  * hermes_kv_init (ENOTSUP also beyond 64 devices).
  */
-enum { HERMES_STATIC_WORKSPACE_BYTES = 64 << 20 };
+enum { HERMES_STATIC_WORKSPACE_BYTES = 128 << 20 };
 int hermes_kv_init_static(const hermes_config *cfg, const hermes_layer_buffers *layers,
                           hermes_ctx **out);
 

@@ -110,10 +110,11 @@ int64_t partial_rows(const hermes_config *c, int64_t n_rows, int64_t n_layers) {
 
 // Workspace layout of `c`; shared_rows < 0 sizes the shared room for the most
 // rows a short pass can use, else for that many.  rooms: streams that have a
-// room of their own, for their short passes and for kRoomRows rows of longer ones
-// at most.  Every room also holds a sweep's partials when its query rows are cut
+// room of their own, of room_rows rows (< 0: what short passes can use, and longer
+// ones up to kRoomRows).  Every room also holds a sweep's partials when its query rows are cut
 // (the wpart region holds those of uncut ones).
-Layout layout_of(const hermes_config *c, int64_t shared_rows = -1, int rooms = kStreamRooms) {
+Layout layout_of(const hermes_config *c, int64_t shared_rows = -1, int rooms = kStreamRooms,
+                 int64_t room_rows = -1) {
   Layout s;
   s.lse_lstride = (int64_t)c->n_q_heads * c->max_chunk;
   s.keys_lstride = c->max_cap;
@@ -165,31 +166,31 @@ Layout layout_of(const hermes_config *c, int64_t shared_rows = -1, int rooms = k
   s.shared = off;
   off = round_up(off + room_bytes(s.shared_rows, c->head_dim));
   s.n_rooms = rooms;
-  s.room_rows = rooms == 0 ? 0 : short_rows > long_rows ? short_rows : long_rows;
+  s.room_rows = rooms == 0 ? 0 : room_rows >= 0 ? room_rows : short_rows > long_rows ? short_rows : long_rows;
   s.rooms = off;
   off = round_up(off + room_bytes(s.room_rows, c->head_dim) * rooms);
   s.total = off;
   return s;
 }
 
-// The layout of `c` in at most `limit` bytes: the default one if it fits,
-// else with fewer streams' rooms, else with none and as many rows in the shared
-// one as the rest leaves (possibly none: short passes then run the plain kernel).
-// false if even that exceeds `limit`.
+// The layout of `c` in at most `limit` bytes: the default one if it fits, else
+// with fewer streams' rooms, or one of what the rest leaves (for longer passes
+// only, if that is less than short ones can use), else with none and as many rows
+// in the shared one as the rest leaves (possibly none: short passes then run the
+// plain kernel).  false if even that exceeds `limit`.
 bool layout_within(const hermes_config *c, size_t limit, Layout *out) {
-  for (int rooms = kStreamRooms; rooms >= 0; --rooms) {
-    const Layout full = layout_of(c, -1, rooms);
-    if (full.total <= limit) {
-      *out = full;
-      return true;
-    }
+  for (int rooms = kStreamRooms; rooms > 0; --rooms) {
+    *out = layout_of(c, -1, rooms);
+    if (out->total <= limit) return true;
   }
-  const Layout none = layout_of(c, 0, 0);
+  const Layout shared = layout_of(c, -1, 0), none = layout_of(c, 0, 0);
   if (none.total > limit) return false;
-  int64_t rows = (int64_t)((limit - none.total) / (sizeof(float) * (c->head_dim + 2)));
+  const bool all_shared = shared.total <= limit;
+  int64_t rows = (int64_t)((limit - (all_shared ? shared : none).total) / (sizeof(float) * (c->head_dim + 2)));
+  auto with = [&](int64_t n) { return all_shared ? layout_of(c, -1, 1, n) : layout_of(c, n, 0); };
   // the two regions are rounded up separately: back off until it fits
-  while (rows > 0 && layout_of(c, rows, 0).total > limit) rows = rows > 64 ? rows - 64 : 0;
-  *out = layout_of(c, rows, 0);
+  while (rows > 0 && with(rows).total > limit) rows = rows > 64 ? rows - 64 : 0;
+  *out = rows > 0 || !all_shared ? with(rows) : shared;
   return true;
 }
 
@@ -494,7 +495,8 @@ struct hermes_ctx {
   // Passes without a room run uncut, or, where they are short (queries and prompts
   // of up to kSplitMaxTokens rows) and the cut saves a tenth, share one that no
   // other pass touches: those have to follow each other on the device, and nothing
-  // else has to.
+  // else has to.  (In a workspace whose streams' rooms are too small for them, or
+  // none, every short pass shares, whatever its cut saves.)
   template <typename F>
   void cut(AttnArgs &at, int n_rows, int n, bool may_share, ColsumArgs *cs, int n_cs, int max_T, hipStream_t s,
            F &&captured) {
@@ -518,7 +520,8 @@ struct hermes_ctx {
       cs->layer0 = own ? 0 : first;
       return !own;
     };
-    const int room = room_of(s);
+    const bool shares = may_share && n_rows <= kSplitMaxTokens, small = lay.room_rows < lay.shared_rows;
+    const int room = shares && small ? -1 : room_of(s);
     if (room >= 0) {
       const size_t bytes = room_bytes(lay.room_rows, D), base = lay.rooms + room * bytes;
       plan(lay.room_rows, base);
@@ -531,8 +534,8 @@ struct hermes_ctx {
       }
     }
     sweep(0, 0);
-    const double uncut = plan(0, lay.shared);
-    if (may_share && n_rows <= kSplitMaxTokens && plan(lay.shared_rows, lay.shared) > 0.9 * uncut) plan(0, lay.shared);
+    const double uncut = plan(0, lay.shared), worth = small ? 1.0 : 0.9;
+    if (shares && plan(lay.shared_rows, lay.shared) > worth * uncut) plan(0, lay.shared);
   }
   void cut(AttnArgs &at, int n_rows, int n, bool may_share, ColsumArgs *cs, int n_cs, int max_T, hipStream_t s) {
     cut(at, n_rows, n, may_share, cs, n_cs, max_T, s, [&] { return capturing(s); });

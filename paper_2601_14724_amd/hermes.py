@@ -36,7 +36,7 @@ EXPORTED = ("hermes_workspace_bytes", "hermes_kv_init", "hermes_append_chunk",
             "hermes_budget_from_weights", "hermes_kv_destroy", "hermes_strerror",
             "hermes_select_topk", "hermes_profile_enable", "hermes_profile_read",
             "hermes_check_enable", "hermes_kv_init_static")
-STATIC_WORKSPACE_BYTES = 64 << 20
+STATIC_WORKSPACE_BYTES = 128 << 20
 
 
 class HermesConfig(ctypes.Structure):

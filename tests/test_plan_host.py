@@ -71,6 +71,11 @@ def test_a_captured_short_query_keeps_out_of_a_long_ones_room():
     long_, short = plan(cfg, [(QUERY, 100, 0, lens, 8, 0), (QUERY, 1, 1, lens, 16, 1)])
     assert long_.rows > 0 and short.rows > 0
     assert apart(long_, short)
+    # the same where the scratch has less for a stream than short passes can use
+    cfg, lens = config(28, 32, 8, 128, 8976, 784), [4096] * 28
+    long_, mine, short = plan(cfg, [(QUERY, 100, 0, lens, 8, 0), (QUERY, 1, 1, lens, 8, 0), (QUERY, 1, 1, lens, 16, 1)],
+                              H.STATIC_WORKSPACE_BYTES)
+    assert long_.rows > 0 and short.rows > 0 and apart(long_, short) and not apart(mine, short)
 
 
 @pytest.mark.parametrize("rows", [1, 16, 64, 65, 100, 784])
@@ -207,3 +212,47 @@ def test_sweeps_are_cut_where_it_pays(layers, hq, hkv, d, length, rows, splits):
     cfg = config(layers, hq, hkv, d, length + 784, 784)
     got = plan(cfg, [(APPEND, rows, -1, [length] * layers, 0, 0)])[0].splits
     assert got == splits if splits == 1 else got > 1
+
+
+def former_bytes(layers, hq, hkv, d, cap, chunk):
+    """The workspace while partial state was bf16 and one room: what the static
+    scratch of 64 MiB was measured against."""
+    def up(x):
+        return (x + 255) // 256 * 256
+    off = up(152 * layers)
+    for n in (4 * hq * chunk * layers, 4 * cap * layers, 4 * min(cap, 64) * layers, 8 * ((cap + 255) // 256) * layers,
+              8 * hkv * cap * layers, 32 * layers, 16):
+        off = up(off + n)
+    rows = (layers * hkv + 256) * 64 * (hq // hkv)
+    return up(up(off + 2 * rows * d) + 8 * rows)
+
+
+def test_the_static_scratch_cuts_short_passes_as_a_full_workspace_does():
+    """Every configuration whose whole workspace fitted the scratch of 64 MiB while
+    partial rows were bf16 cuts its short passes in the present one as with a
+    workspace of its own (28 layers of the 7B shape: 128 units of 64 rows)."""
+    rng = random.Random(9)
+    shapes = [(28, 28, 4, 128, 8976, 784), (28, 28, 4, 128, 19000, 784), (24, 14, 2, 64, 4880, 784)]
+    for _ in range(300):
+        hkv, g = rng.choice((1, 2, 4, 8, 16)), rng.choice((1, 2, 4, 7, 8))
+        chunk = rng.choice((64, 196, 784, 3136))
+        shapes.append((rng.choice((1, 8, 28, 48, 64)), hkv * g, hkv, rng.choice((64, 128)),
+                       chunk + int(2 ** rng.uniform(6, 15)), chunk))
+    tried = 0
+    for shape in shapes:
+        if former_bytes(*shape) > 64 << 20:
+            continue
+        tried += 1
+        cfg, cap = config(*shape), shape[4] - shape[5]
+        lens = [rng.randint(cap // 3, cap) for _ in range(shape[0])]
+        for rows in (1, 16, 33, 64):
+            calls = [(kind, rows, layer, lens, 0, captured) for kind in (QUERY, PROMPT) for layer in (-1, 0)
+                     for captured in (0, 1)]
+            for call, a, b in zip(calls, plan(cfg, calls), plan(cfg, calls, H.STATIC_WORKSPACE_BYTES)):
+                # (with no stream's room at all, recorded calls are cut where others are)
+                same = (a.mode, a.key_groups, a.units) == (b.mode, b.key_groups, b.units)
+                assert same or (call[5] and a.mode == PLAIN), (shape, call, (a.mode, a.units), (b.mode, b.units))
+    assert tried > 100
+    seven = plan(config(28, 28, 4, 128, 8976, 784), [(QUERY, 64, -1, [2048 + 151 * i for i in range(28)], 0, 0)],
+                 H.STATIC_WORKSPACE_BYTES)[0]
+    assert (seven.mode, seven.units) == (STREAM, 128)
