@@ -223,7 +223,7 @@ def main() -> int:
     kernels = {}
     for kid, name in enumerate(H.KERNEL_NAMES):
         ms, cnt = kv.profile_read(kid)
-        if cnt:   # per step: a group may hold several launches
+        if cnt and ms:   # per step: a group may hold several launches (the append copy has none of its own)
             kernels[name] = {"avg_ms": ms / args.steps, "launches": cnt}
     kv.profile(False)
 
@@ -409,7 +409,7 @@ def c5_bench(steps: int, warmup: int) -> dict:
     kernels = {}
     for kid, name in enumerate(H.KERNEL_NAMES):
         ms, cnt = kv.profile_read(kid)
-        if cnt:
+        if cnt and ms:
             kernels[name] = round(ms / steps, 4)
     kv.profile(False)
     fl = attention_flops(wl)
@@ -504,7 +504,7 @@ def extension_bench(wl, caches, t, steps: int, warmup: int, prompt_rows: int = 6
         ks = {}
         for kid, name in enumerate(H.KERNEL_NAMES):
             ms, cnt = kv.profile_read(kid)
-            if cnt:   # per step: a group may hold several launches
+            if cnt and ms:   # per step: a group may hold several launches
                 ks[name] = round(ms / steps, 4)
         kv.profile(False)
         return dt, ks

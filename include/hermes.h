@@ -396,7 +396,7 @@ int hermes_check_enable(hermes_ctx *ctx, int on);
 /*
  * Kernel timing with HIP events recorded on the launch stream around every
  * launch of one kernel class while enabled.  Kernel ids: 0 append copy (done
- * inside the attention launch, whose time holds it: counted, with about 0 ms),
+ * inside the attention launch, whose time holds it: counted, with 0 ms),
  * 1 chunk attention, 2 attention-mass sweep, 3 score+select, 4 gather (and
  * re-indexing), 5 query attention, 6 summary reduction, 7 guidance scoring.  hermes_profile_read waits for the recorded events and
  * returns the summed milliseconds and the launch count since the last read.

@@ -4,8 +4,9 @@
 //              [cache; new rows]: O and the per-row log-sum-exp.
 // attn_colsum  attention mass W_i = sum over heads and rows of the softmax
 //              probability on candidate i (Sec. 3.1, deep-layer score),
-//              recomputed key-major from the row LSE so that every W_i is
-//              summed by exactly one wave, in a fixed order, with no partials.
+//              recomputed key-major from the row LSE so that every W_i's
+//              share of a KV head (or of a range of its rows) is summed by
+//              exactly one wave, in a fixed order; mass_reduce adds the shares.
 //
 // Query rows are packed per KV head: packed row p = r * G + g holds chunk row
 // r of query head kv * G + g, so the G heads that share a KV head share every

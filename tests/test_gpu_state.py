@@ -87,6 +87,7 @@ def test_profiling_counts_launches():
     assert n == 1 and ms > 0
     ms, n = kv.profile_read(H.K_GATHER)
     assert n == 1
+    assert kv.profile_read(H.K_APPEND) == (0.0, 1) and kv.profile_read(H.K_APPEND) == (0.0, 0)   # inside attention
     ms, n = kv.profile_read(H.K_ATTN)
     assert n == 0 and ms == 0
     kv.close()
